@@ -131,6 +131,7 @@ WsLayout make_layout(const Counts& c, int64_t cap, bool frags) {
   L.table = take(sizeof(SessionDev) * RTGS_MAX_SESSIONS);
   L.counters = take(64);
   L.rec = take(64 * n);
+  L.ext = take(8 * n);
   L.rect = take(16 * n);
   L.cnt = take(4 * n);
   L.goff = take(4 * n);
@@ -139,16 +140,24 @@ WsLayout make_layout(const Counts& c, int64_t cap, bool frags) {
   L.pose_part = take(128 * (uint64_t)c.b_total);
   L.chunk_total = take(4 * (uint64_t)(c.c_total + 1));
   L.chunk_off = take(4 * (uint64_t)(c.c_total + 1));
+  const uint64_t windows = (uint64_t)cap / kWindow + (uint64_t)c.c_total;
+  L.win_off = take(4 * (uint64_t)(c.c_total + 1));
+  L.vlist = take(8 * (uint64_t)c.c_total * (kChunk + 1));
+  L.window = take(16 * windows);
+  L.edge = take(80 * windows);
   L.hist = take(4 * (uint64_t)c.h_total);
   L.gsum = take(4 * 16 * t);
   L.tile_count = take(4 * (t + 1));
   L.tile_start = take(4 * (t + 1));
   L.big_tiles = take(4 * (t + 1));
-  L.keys = take(8 * (uint64_t)cap);
-  L.keys_tm = take(8 * (uint64_t)cap);
   L.ids = take(4 * (uint64_t)cap);
   L.qmask = take((uint64_t)cap);
-  L.partial = take(4 * 10 * (uint64_t)cap);
+  L.partial = take(4 * 4 * 10 * (uint64_t)cap + 2 * kAlign);
+  // the keys are dead once the lists are sorted, the sums live from the raster
+  // backward to the merge: they share memory
+  L.keys = L.partial;
+  L.keys_tm = L.partial + align_up(8 * (uint64_t)cap);
+  L.live = take(4 * (uint64_t)cap);
   L.state_t = take(4 * (uint64_t)c.px_total);
   L.state_last = take(4 * (uint64_t)c.px_total);
   L.lane_perm = take(256 * t);
@@ -171,6 +180,7 @@ WsPtrs ws_ptrs(void* ws, const WsLayout& L) {
   w.table = reinterpret_cast<SessionDev*>(base + L.table);
   w.counters = reinterpret_cast<long long*>(base + L.counters);
   w.rec = reinterpret_cast<GaussRec*>(base + L.rec);
+  w.ext = reinterpret_cast<float2*>(base + L.ext);
   w.rect = reinterpret_cast<int4*>(base + L.rect);
   w.cnt = reinterpret_cast<uint32_t*>(base + L.cnt);
   w.goff = reinterpret_cast<uint32_t*>(base + L.goff);
@@ -179,6 +189,10 @@ WsPtrs ws_ptrs(void* ws, const WsLayout& L) {
   w.pose_part = reinterpret_cast<double*>(base + L.pose_part);
   w.chunk_total = reinterpret_cast<uint32_t*>(base + L.chunk_total);
   w.chunk_off = reinterpret_cast<uint32_t*>(base + L.chunk_off);
+  w.win_off = reinterpret_cast<uint32_t*>(base + L.win_off);
+  w.vlist = reinterpret_cast<uint2*>(base + L.vlist);
+  w.window = reinterpret_cast<uint4*>(base + L.window);
+  w.edge = reinterpret_cast<float*>(base + L.edge);
   w.hist = reinterpret_cast<uint32_t*>(base + L.hist);
   w.gsum = reinterpret_cast<uint32_t*>(base + L.gsum);
   w.tile_count = reinterpret_cast<uint32_t*>(base + L.tile_count);
@@ -189,6 +203,7 @@ WsPtrs ws_ptrs(void* ws, const WsLayout& L) {
   w.ids = reinterpret_cast<uint32_t*>(base + L.ids);
   w.qmask = reinterpret_cast<uint8_t*>(base + L.qmask);
   w.partial = reinterpret_cast<float*>(base + L.partial);
+  w.live = reinterpret_cast<uint8_t*>(base + L.live);
   w.state_t = reinterpret_cast<float*>(base + L.state_t);
   w.state_last = reinterpret_cast<int32_t*>(base + L.state_last);
   w.lane_perm = reinterpret_cast<uint8_t*>(base + L.lane_perm);
@@ -305,7 +320,7 @@ int32_t upload_table(rtgs_handle_t h, const rtgs_session* ss, int ns, const WsPt
   hipError_t e = hipEventSynchronize(h->ring_ev[slot]);
   if (e != hipSuccess) return hip_fail(e, "hipEventSynchronize");
   SessionDev* t = h->h_ring + (size_t)slot * RTGS_MAX_SESSIONS;
-  int32_t gbase = 0, bbase = 0, tbase = 0, cbase = 0, tmax = 0;
+  int32_t gbase = 0, bbase = 0, tbase = 0, cbase = 0, tmax = 0, any_sub = 0;
   int64_t pbase = 0, hbase = 0;
   for (int i = 0; i < ns; ++i) {
     const rtgs_session& s = ss[i];
@@ -396,6 +411,7 @@ int32_t upload_table(rtgs_handle_t h, const rtgs_session* ss, int ns, const WsPt
       d.g_viewmat = (flags & RTGS_GRAD_POSE) ? s.g_viewmat : nullptr;
     }
     t[i] = d;
+    any_sub |= s.sample_log2;
     gbase += s.g.n;
     bbase += (int32_t)blocks_of(s.g.n);
     const int32_t ts = (int32_t)tiles_of(s.cam.width, s.cam.height, s.sample_log2);
@@ -425,6 +441,7 @@ int32_t upload_table(rtgs_handle_t h, const rtgs_session* ss, int ns, const WsPt
   B.b_total = bbase;
   B.c_total = cbase;
   B.t_max = tmax;
+  B.any_sub = any_sub;
   return RTGS_OK;
 }
 

@@ -120,6 +120,7 @@ __global__ __launch_bounds__(kGaussPerBlock) void k_preprocess(Batch B, WsPtrs W
   Proj P;
   project_one(S, vm, li, o, P);
   int4 rect = make_int4(0, 0, -1, -1);
+  GaussRec r;
   if (P.ok) {
     const double det = P.sxx * P.syy - P.sxy * P.sxy;
     const double inv = 1.0 / det;
@@ -131,13 +132,12 @@ __global__ __launch_bounds__(kGaussPerBlock) void k_preprocess(Batch B, WsPtrs W
     const double t = 2.0 * (double)logf((float)(255.0 * o));
     const float ex = (float)sqrt(t * P.sxx);
     const float ey = (float)sqrt(t * P.syy);
-    GaussRec r;
     r.pos = make_float4(uh, vh, ul, vl);
     r.conic = make_float4((float)(P.syy * inv), (float)(-P.sxy * inv), (float)(P.sxx * inv),
                           (float)o);
     r.col = make_float4(S.colors[3 * li + 0], S.colors[3 * li + 1], S.colors[3 * li + 2], zf);
-    r.ext = make_float4(ex, ey, (float)t, 0.f);
-    W.rec[gid] = r;
+    r.ext.z = (float)t;
+    W.ext[gid] = make_float2(ex, ey);
     // padded pixel range in float32, fixed operation order (see the replay)
     const float lox = floorf((uh - ex) - 1.5f), hix = ceilf((uh + ex) + 0.5f);
     const float loy = floorf((vh - ey) - 1.5f), hiy = ceilf((vh + ey) + 0.5f);
@@ -148,18 +148,23 @@ __global__ __launch_bounds__(kGaussPerBlock) void k_preprocess(Batch B, WsPtrs W
       rect = make_int4(i0 >> shx, j0 >> shy, i1 >> shx, j1 >> shy);
     }
   } else {
-    GaussRec r;
     r.pos = make_float4(0.f, 0.f, 0.f, 0.f);
     r.conic = make_float4(0.f, 0.f, 0.f, 0.f);
     r.col = make_float4(0.f, 0.f, 0.f, (float)P.z);
     // a negative alpha-ellipse bound fails every quadrant test: a culled or
     // masked Gaussian left in a reused list costs the rasterizer nothing
-    r.ext = make_float4(0.f, 0.f, -1.f, 0.f);
-    W.rec[gid] = r;
+    r.ext.z = -1.f;
+    W.ext[gid] = make_float2(0.f, 0.f);
   }
+  if (REUSE) rect = W.rect[gid];
+  // the lists' rectangle, from which the raster backward takes the pair's slot
+  const int rw = rect.z - rect.x + 1;
+  r.ext.x = __int_as_float(rect.y * rw + rect.x);
+  r.ext.y = __int_as_float(rw);
+  r.ext.w = 0.f;
+  W.rec[gid] = r;
   if (REUSE) {
-    const int4 ref = W.rect[gid];
-    if (S.visible) S.visible[li] = ref.z >= ref.x ? 1 : 0;
+    if (S.visible) S.visible[li] = rect.z >= rect.x ? 1 : 0;
     return;
   }
   W.rect[gid] = rect;
@@ -411,6 +416,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tiles(WsPtrs W, int t_tot
                                                              unsigned long long* max_pairs) {
   __shared__ uint32_t part[kScanThreads / 64];
   __shared__ uint32_t s_t[kScanPer * kScanThreads], s_c[kScanPer * kScanThreads];
+  __shared__ uint32_t s_wn[kScanPer * kScanThreads];
   const int tid = threadIdx.x;
   uint32_t total;
   if (t_total <= kScanPer * kScanThreads && c_total <= kScanPer * kScanThreads) {
@@ -426,29 +432,36 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tiles(WsPtrs W, int t_tot
       s_c[t] = t < c_total ? W.chunk_total[t] : 0u;
     }
     __syncthreads();
-    uint32_t tv[kScanPer], cv[kScanPer];
+    uint32_t tv[kScanPer], cv[kScanPer], wv[kScanPer];
 #pragma unroll
     for (int i = 0; i < kScanPer; ++i) {
       tv[i] = s_t[tid * kScanPer + i];
       cv[i] = s_c[tid * kScanPer + i];
+      wv[i] = (cv[i] + kWindow - 1) / kWindow;
     }
     total = block_scan_regs<kScanPer>(tv, part);        // its barriers order the LDS reuse
     const uint32_t ctot = block_scan_regs<kScanPer>(cv, part);
+    const uint32_t wtot = block_scan_regs<kScanPer>(wv, part);
 #pragma unroll
     for (int i = 0; i < kScanPer; ++i) {
       s_t[tid * kScanPer + i] = tv[i];
       s_c[tid * kScanPer + i] = cv[i];
+      s_wn[tid * kScanPer + i] = wv[i];
     }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kScanPer; ++k) {
       const int t = k * kScanThreads + tid;
       if (t < t_total) W.tile_start[t] = s_t[t];
-      if (t < c_total) W.chunk_off[t] = s_c[t];
+      if (t < c_total) {
+        W.chunk_off[t] = s_c[t];
+        W.win_off[t] = s_wn[t];
+      }
     }
     if (tid == 0) {
       W.tile_start[t_total] = total;
       W.chunk_off[c_total] = ctot;
+      W.win_off[c_total] = wtot;
     }
     __syncthreads();                      // tile_start complete before an overflow clears it
   } else {
@@ -461,6 +474,11 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tiles(WsPtrs W, int t_tot
     __syncthreads();
     total = block_scan_1024(W.tile_count, W.tile_start, t_total, part);
     block_scan_1024(W.chunk_total, W.chunk_off, c_total, part);
+    // the chunks' windows, counted in place of their offsets first
+    for (int c = tid; c < c_total; c += kScanThreads)
+      W.win_off[c] = (W.chunk_total[c] + kWindow - 1) / kWindow;
+    __syncthreads();
+    block_scan_1024(W.win_off, W.win_off, c_total, part);
   }
   if ((int64_t)total > W.cap)
     for (int t = threadIdx.x; t <= t_total; t += kScanThreads) W.tile_start[t] = 0u;
@@ -471,6 +489,42 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tiles(WsPtrs W, int t_tot
     atomicMax(&max_pairs[0], (unsigned long long)total);
     if ((int64_t)total > W.cap) atomicMax(&max_pairs[1], (unsigned long long)total);
   }
+}
+
+// For the backward's merge: the chunk's Gaussians that have pairs, in order
+// (vlist, closed by the chunk's end), and the chunk's windows of kWindow pairs
+// with the vlist entries they meet.  s_off: the Gaussians' pair offsets in the
+// chunk; s_wave: LDS of a word per wave.
+__device__ void list_windows(const WsPtrs& W, int chunk, int gauss0, uint32_t base, uint32_t total,
+                             const uint32_t* s_off, uint32_t* s_wave) {
+  static_assert(kChunkRounds == 1, "one Gaussian per thread");
+  const int i = threadIdx.x, lane = i & 63, wave = i >> 6;
+  const uint32_t o = s_off[i], e = s_off[i + 1];
+  const bool has = e > o;
+  const unsigned long long m = __ballot(has);
+  if (lane == 0) s_wave[wave] = (uint32_t)__popcll(m);
+  __syncthreads();
+  uint32_t rank = (uint32_t)__popcll(m & ((1ull << lane) - 1ull)), count = 0;
+  for (int q = 0; q < kBinThreads / 64; ++q) {
+    rank += q < wave ? s_wave[q] : 0u;
+    count += s_wave[q];
+  }
+  const uint32_t v0 = (uint32_t)chunk * (kChunk + 1);
+  if (has) {
+    W.vlist[v0 + rank] = make_uint2((uint32_t)(gauss0 + i), base + o);
+    uint32_t* win = reinterpret_cast<uint32_t*>(W.window + W.win_off[chunk]);
+    // windows that begin in this Gaussian's pairs, and those that end in them
+    for (uint32_t k = (o + kWindow - 1) / kWindow; k * kWindow < e; ++k) {
+      win[4 * k] = base + k * kWindow;
+      win[4 * k + 1] = base + min(total, (k + 1) * kWindow);
+      win[4 * k + 2] = v0 + rank;
+    }
+    for (uint32_t k = o / kWindow; k * kWindow < e; ++k) {
+      const uint32_t end = min(total, (k + 1) * kWindow);
+      if (end > o && end <= e) win[4 * k + 3] = v0 + rank;
+    }
+  }
+  if (i == 0) W.vlist[v0 + count] = make_uint2(0u, base + total);
 }
 
 // Per chunk: each Gaussian's first Gaussian-major slot; the chunk's pairs
@@ -548,6 +602,11 @@ __global__ __launch_bounds__(kBinThreads) void k_emit(Batch B, WsPtrs W) {
     const int li = c * kChunk + i;
     if (li < S.n) W.goff[S.gauss_base + li] = base + s_off[i];
   }
+  if (W.chunk_off[B.c_total] <= (uint64_t)W.cap)
+    list_windows(W, blockIdx.x, S.gauss_base + c * kChunk, base, total, s_off, s_wave);
+  // no pair of this call's lists has sums yet
+  for (uint32_t k = threadIdx.x; k < total; k += kBinThreads)
+    if ((int64_t)base + k < W.cap) reinterpret_cast<uint32_t*>(W.live)[base + k] = 0u;
   const uint32_t g0 = S.gauss_base + c * kChunk;
   const bool staged = total <= kStagePairs;
   chunk_pairs(S, s_rect, c, s_off, total, [&](int i, int tile) {
@@ -895,7 +954,8 @@ __global__ void k_debug_stage(Batch B, WsPtrs W, float* stage, int* rect, int* r
   if (i < B.n_total) {
     if (stage) {
       const GaussRec R = W.rec[i];
-      const float4 r0 = R.pos, r1 = R.conic, r2 = R.col, e = R.ext;
+      const float4 r0 = R.pos, r1 = R.conic, r2 = R.col;
+      const float2 e = W.ext[i];
       float* o = stage + 12 * (int64_t)i;
       o[0] = r0.x; o[1] = r0.y; o[2] = r1.x; o[3] = r1.y; o[4] = r1.z; o[5] = r1.w;
       o[6] = r2.w; o[7] = e.x; o[8] = e.y; o[9] = r2.x; o[10] = r2.y; o[11] = r2.z;
@@ -923,14 +983,16 @@ __global__ void k_wave_sum_test(const float* in, float* out, int n_waves) {
   float v[NV], x[3];
 #pragma unroll
   for (int i = 0; i < NV; ++i) v[i] = in[((int64_t)w * NV + i) * 64 + lane];
-  wave_reduce_scatter<NV>(v, x);
-  if ((lane & 15) == 15) {
-    const int row = lane >> 4;
+  rows8_reduce_scatter<NV>(v, x);
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      const int idx = wave_scatter_index(NV, row, j);
-      if (idx >= 0) out[(int64_t)w * NV + idx] = x[j];
-    }
+  for (int j = 0; j < 3; ++j)
+    for (int off = 4; off >= 1; off >>= 1) x[j] += __shfl_xor(x[j], off);
+  if ((lane & 15) == 0) {
+    const int odd = (lane >> 4) & 1;
+    float* o = out + (int64_t)w * NV + (lane >> 5) * (NV / 2);
+#pragma unroll
+    for (int j = 0; j < NV / 4; ++j) o[odd + 2 * j] = x[j];
+    if (!odd) o[NV / 2 - 1] = x[NV / 4];
   }
 }
 

@@ -7,8 +7,7 @@
 //
 // Two kernels.  The tile -> Gaussian merge (the role of the paper's Stage
 // Buffer): each Gaussian's 2D gradient is the fixed-order sum of its
-// (tile, Gaussian) pair slots, 40 B each; a streaming kernel at full
-// occupancy.  Then one thread per Gaussian in float64 through the
+// (tile, Gaussian, quadrant) slots, 40 B each.  Then one thread per Gaussian in float64 through the
 // projection (56 B of parameters and 40 B of merged gradient in), writing
 // the gradients (56 B) or, fused, applying Adam to the Gaussian's 14
 // parameters right away (parameters and both moments read and written,
@@ -35,43 +34,6 @@
 namespace rtgs {
 namespace {
 
-// Tile -> Gaussian merge: kMergeLanes lanes (part of a DPP row) per Gaussian
-// sum its pair slots, strided, then a fixed DPP tree; the last of them stores
-// the NV totals.  A Gaussian with more than kMergeBig slots (a few hundred of 300k
-// touch up to ~1400 tiles) would make its row the kernel's critical path, so
-// its row hands it to the whole workgroup, whose 256 lanes sum it after the
-// rows are done.  Every sum is in a fixed order: deterministic.
-constexpr int kMergeBig = 128;
-constexpr int kMergeLanes = 8;            // lanes per Gaussian (a half DPP row)
-constexpr int kMergePerBlock = 256 / kMergeLanes;
-
-// Lane `lane` of `width` adds slots lane, lane + width, ... of the n slots at
-// `first`; four slots are loaded per round, so that a long list does not
-// serialise on one load at a time.
-template <int NV>
-__device__ __forceinline__ void sum_slots(const WsPtrs& W, int64_t first, int64_t n, int lane,
-                                          int width, float (&acc)[NV]) {
-  for (int64_t k0 = lane; k0 < n; k0 += 4 * width) {
-    float v[4][NV];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int64_t k = k0 + (int64_t)width * j;
-      // a slot is NV floats at an 8-byte aligned offset: NV / 2 8-byte loads
-      const float2* p = reinterpret_cast<const float2*>(W.partial + (first + k) * NV);
-#pragma unroll
-      for (int i = 0; i < NV / 2; ++i) {
-        const float2 x = k < n ? p[i] : make_float2(0.f, 0.f);
-        v[j][2 * i] = x.x;
-        v[j][2 * i + 1] = x.y;
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int i = 0; i < NV; ++i) acc[i] += v[j][i];
-  }
-}
-
 // Sums over runs of LANES (8 or 16) lanes of each DPP row; the run's last
 // lane holds its total.
 template <int LANES, int NV>
@@ -87,58 +49,185 @@ __device__ __forceinline__ void row_sums(float (&acc)[NV]) {
   }
 }
 
+// Tile -> Gaussian merge: the quadrant sums of each Gaussian's pairs added up.
+// A pair's four flag bytes say which of its sums the raster backward wrote (at
+// 1200x680 / 300k three pairs in ten have any); only those are read, and the
+// flags are zeroed for the next backward.
+//
+// Bound by memory latency (the sums' loads depend on the flags') and by the
+// spread of the work: a Gaussian touches from one pair to over a thousand, and
+// following each Gaussian's flags with lanes of its own makes the largest
+// Gaussians' chains of dependent loads the kernel's time.  So the work is cut
+// by pairs: a window is kWindow consecutive pairs of one binning chunk (the
+// emit lists the windows, and each chunk's Gaussians that have pairs).  A
+// workgroup reads a window's flags together and lists the items (pair,
+// quadrant) found in LDS; then 8 lanes per Gaussian, or a wave for one with
+// more than kItemsWave items, add its items.  A Gaussian that crosses a
+// window's end leaves a partial sum per window in `edge`, added up in window
+// order by the preprocessing backward.  Every sum is in a fixed order:
+// deterministic.
+constexpr int kItemsWave = 32;
+
+// A pair's flag bytes (0 or 1) as four bits.
+__device__ __forceinline__ uint32_t live_bits(uint32_t f) {
+  return (f & 1u) | ((f >> 7) & 2u) | ((f >> 14) & 4u) | ((f >> 21) & 8u);
+}
+
+// acc += the sums of items lo + lane, lo + lane + LANES, ... below hi of the
+// list, U loads in flight; src: the window's first slot.
+template <int NV, int LANES, int U>
+__device__ __forceinline__ void add_items(const float2* src, const uint16_t* list, int lo, int hi,
+                                          int lane, float (&acc)[NV]) {
+  for (int i0 = lo + lane; i0 < hi; i0 += U * LANES) {
+    float2 v[U][NV / 2];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      // NV floats at an 8-byte aligned offset: NV / 2 8-byte loads
+      const bool on = i0 + j * LANES < hi;
+      const int item = on ? (int)list[i0 + j * LANES] : 0;
+#pragma unroll
+      for (int i = 0; i < NV / 2; ++i)
+        v[j][i] = on ? src[item * (NV / 2) + i] : make_float2(0.f, 0.f);
+    }
+#pragma unroll
+    for (int j = 0; j < U; ++j)
+#pragma unroll
+      for (int i = 0; i < NV / 2; ++i) {
+        acc[2 * i] += v[j][i].x;
+        acc[2 * i + 1] += v[j][i].y;
+      }
+  }
+}
+
+// Where the sums over window w (pairs [p0, p1)) of the Gaussian with pairs
+// [first, last) go: grad2d, or the window's edge it crosses (see edge_sum).
+__device__ __forceinline__ float* merge_dst(const WsPtrs& W, int w, uint32_t p0, uint32_t p1,
+                                            uint32_t gid, uint32_t first, uint32_t last) {
+  if (first >= p0 && last <= p1) return W.grad2d + (int64_t)gid * 10;
+  return W.edge + ((int64_t)w * 2 + (first < p0 ? 0 : 1)) * 10;
+}
+
 template <int NV>
-__global__ __launch_bounds__(256) void k_merge(Batch B, WsPtrs W) {
-  __shared__ int s_big[kMergePerBlock];
-  __shared__ int s_nbig;
-  __shared__ float s_row[16][NV];
-  const int row = threadIdx.x >> 4;
-  const int gid = blockIdx.x * kMergePerBlock + (int)threadIdx.x / kMergeLanes;
-  const int sub = threadIdx.x % kMergeLanes;
-  if (threadIdx.x == 0) s_nbig = 0;
-  __syncthreads();
-  float acc[NV];
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
+void k_merge(Batch B, WsPtrs W) {
+  static_assert(kWindow == 512, "two pairs a thread");
+  __shared__ uint16_t s_item[4 * kWindow];            // 4 pair + quadrant, in order
+  __shared__ uint16_t s_cum[kWindow + 1];             // items before each pair
+  __shared__ uint32_t s_w[4];
+  __shared__ int s_big[4 * kWindow / kItemsWave], s_nbig;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, sub = tid & 7;
+  uint32_t* const live = reinterpret_cast<uint32_t*>(W.live);
+  if (W.counters[0] > W.cap) return;                  // no lists
+  const int n_win = (int)W.win_off[B.c_total];
+  for (int w = blockIdx.x; w < n_win; w += gridDim.x) {
+    const uint4 d = W.window[w];                      // pairs [x, y), list entries [z, w]
+    const uint32_t p0 = d.x, p1 = d.y;
+    const uint32_t a = p0 + tid, b = a + 256;
+    const uint32_t fa = a < p1 ? live[a] : 0u, fb = b < p1 ? live[b] : 0u;
+    if (tid == 0) s_nbig = 0;
+    // items before each pair: one scan for the two halves of the pairs
+    const uint32_t have = (uint32_t)__popc(fa) | ((uint32_t)__popc(fb) << 16);
+    uint32_t x = have;
 #pragma unroll
-  for (int i = 0; i < NV; ++i) acc[i] = 0.f;
-  bool mine = gid < B.n_total;
-  if (mine) {
-    const int64_t first = W.goff[gid];
-    // slots past the pair capacity were never written
-    const int64_t n = min((int64_t)W.cnt[gid], W.cap - first);
-    if (n > kMergeBig) {
-      mine = false;
-      if (sub == 0) s_big[atomicAdd(&s_nbig, 1)] = gid;
-    } else {
-      sum_slots<NV>(W, first, n, sub, kMergeLanes, acc);
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t y = __shfl_up(x, off, 64);
+      if (lane >= off) x += y;
     }
-  }
-  row_sums<kMergeLanes, NV>(acc);
-  if (sub == kMergeLanes - 1 && mine) {
-    float* d = W.grad2d + (int64_t)gid * 10;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) d[i] = acc[i];
-  }
-  __syncthreads();
-  const int nbig = s_nbig;
-  for (int q = 0; q < nbig; ++q) {
-    // s_big's order depends on timing; each Gaussian's sum does not
-    const int g = s_big[q];
-    const int64_t first = W.goff[g];
-    const int64_t n = min((int64_t)W.cnt[g], W.cap - first);
-#pragma unroll
-    for (int i = 0; i < NV; ++i) acc[i] = 0.f;
-    sum_slots<NV>(W, first, n, (int)threadIdx.x, 256, acc);
-    row_sums<16, NV>(acc);
-    if ((threadIdx.x & 15) == 15)
-#pragma unroll
-      for (int i = 0; i < NV; ++i) s_row[row][i] = acc[i];
+    if (lane == 63) s_w[wave] = x;
     __syncthreads();
-    if (threadIdx.x < NV) {
-      float t = 0.f;
-      for (int r = 0; r < 16; ++r) t += s_row[r][threadIdx.x];
-      W.grad2d[(int64_t)g * 10 + threadIdx.x] = t;
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      before += q < wave ? s_w[q] : 0u;
+      all += s_w[q];
     }
-    __syncthreads();                      // s_row is reused by the next one
+    const uint32_t ex = before + x - have;
+    const int na = (int)(all & 0xffffu);
+    int at = (int)(ex & 0xffffu);
+    s_cum[tid] = (uint16_t)at;
+    for (uint32_t m = live_bits(fa); m; m &= m - 1)
+      s_item[at++] = (uint16_t)(4 * tid + __builtin_ctz(m));
+    at = na + (int)(ex >> 16);
+    s_cum[256 + tid] = (uint16_t)at;
+    for (uint32_t m = live_bits(fb); m; m &= m - 1)
+      s_item[at++] = (uint16_t)(4 * (256 + tid) + __builtin_ctz(m));
+    if (tid == 0) s_cum[kWindow] = (uint16_t)(na + (int)(all >> 16));
+    __syncthreads();
+    if (fa) live[a] = 0u;
+    if (fb) live[b] = 0u;
+    const float2* const src = reinterpret_cast<const float2*>(W.partial + (int64_t)p0 * 4 * NV);
+    for (uint32_t e0 = d.z; e0 <= d.w; e0 += 256 / 8) {
+      const uint32_t e = e0 + tid / 8;
+      uint2 g = make_uint2(0, 0);
+      uint32_t last = 0;
+      int lo = 0, hi = 0;
+      bool mine = e <= d.w;
+      if (mine) {
+        g = W.vlist[e];                               // Gaussian, its first pair
+        last = W.vlist[e + 1].y;                      // the next one's, or the chunk's end
+        lo = s_cum[g.y > p0 ? g.y - p0 : 0u];
+        hi = s_cum[min(last - p0, (uint32_t)kWindow)];
+        if (hi - lo > kItemsWave) {
+          if (sub == 0) s_big[atomicAdd(&s_nbig, 1)] = (int)e;
+          mine = false;
+          hi = lo;
+        }
+      }
+      float acc[NV];
+#pragma unroll
+      for (int i = 0; i < NV; ++i) acc[i] = 0.f;
+      add_items<NV, 8, 2>(src, s_item, lo, hi, sub, acc);
+      row_sums<8, NV>(acc);
+      if (mine && sub == 7) {
+        float* o = merge_dst(W, w, p0, p1, g.x, g.y, last);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) o[i] = acc[i];
+      }
+    }
+    __syncthreads();
+    // the list's order depends on timing; each Gaussian's sum does not
+    const int nbig = s_nbig;
+    for (int q = wave; q < nbig; q += 4) {
+      const uint32_t e = (uint32_t)s_big[q];
+      const uint2 g = W.vlist[e];
+      const uint32_t last = W.vlist[e + 1].y;
+      const int lo = s_cum[g.y > p0 ? g.y - p0 : 0u], hi = s_cum[min(last - p0, (uint32_t)kWindow)];
+      float acc[NV];
+#pragma unroll
+      for (int i = 0; i < NV; ++i) acc[i] = 0.f;
+      add_items<NV, 64, 2>(src, s_item, lo, hi, lane, acc);
+      row_sums<16, NV>(acc);
+      // the four rows' totals in order
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+        acc[i] = ((__shfl(acc[i], 15) + __shfl(acc[i], 31)) + __shfl(acc[i], 47)) +
+                 __shfl(acc[i], 63);
+      if (lane == 0) {
+        float* o = merge_dst(W, w, p0, p1, g.x, g.y, last);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) o[i] = acc[i];
+      }
+    }
+    __syncthreads();                                  // the LDS lists are reused
+  }
+}
+
+// The merged sums of a Gaussian: of its one window, or its partial sums over
+// the windows it crosses, in order (the end of the first, the beginning of
+// each following one).  c: its chunk; [first, last): its pairs.
+template <int NV>
+__device__ __forceinline__ void merged_sums(const WsPtrs& W, int c, int64_t gid, uint32_t first,
+                                            uint32_t n, float (&m)[NV]) {
+  const uint32_t c0 = W.chunk_off[c];
+  const int w0 = (int)(W.win_off[c] + (first - c0) / kWindow);
+  const int w1 = (int)(W.win_off[c] + (first + n - 1 - c0) / kWindow);
+  const float* p = w0 == w1 ? W.grad2d + gid * 10 : W.edge + ((int64_t)w0 * 2 + 1) * 10;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) m[i] = p[i];
+  for (int w = w0 + 1; w <= w1; ++w) {
+    p = W.edge + (int64_t)w * 2 * 10;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) m[i] += p[i];
   }
 }
 
@@ -163,17 +252,22 @@ __global__ __launch_bounds__(kGaussPerBlock) void k_gauss_bwd(Batch B, WsPtrs W,
     double gm[3] = {0, 0, 0}, gl[3] = {0, 0, 0}, gq[4] = {0, 0, 0, 0}, go_eta = 0;
     double gcol[3] = {0, 0, 0}, gsig[6] = {0, 0, 0, 0, 0, 0};
     if (rect.z >= rect.x) {
-      // the merged 2D gradient: (u, v, a, b, c, o, r, g, b, z), or with the
-      // pose-only merge (u, v, a, b, c, z)
+      // the Gaussian's sums of the raster backward; pose only: without those
+      // of the opacity and the colours
       float g2[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-      const float* m = W.grad2d + (int64_t)gid * 10;
-      if (NV == 10) {
-        for (int i = 0; i < 10; ++i) g2[i] = m[i];
-      } else {
-        for (int i = 0; i < 5; ++i) g2[i] = m[i];
-        g2[9] = m[5];
+      if (W.counters[0] <= W.cap) {       // no pairs have sums after an overflow
+        float m[NV];
+        merged_sums<NV>(W, S.chunk_base + li0 / kChunk, gid, W.goff[gid],
+                        (uint32_t)((rect.z - rect.x + 1) * (rect.w - rect.y + 1)), m);
+        if (NV == 10) {
+#pragma unroll
+          for (int i = 0; i < 10; ++i) g2[i] = m[sum_at(NV, i)];
+        } else {
+#pragma unroll
+          for (int i = 0; i < 5; ++i) g2[i] = m[sum_at(NV, i)];
+          g2[9] = m[sum_at(NV, 5)];
+        }
       }
-      const double gu = g2[0], gv = g2[1], ga = g2[2], gb = g2[3], gc = g2[4], go = g2[5];
       gcol[0] = g2[6]; gcol[1] = g2[7]; gcol[2] = g2[8];
       const double gdep = g2[9];
       double vm[12];
@@ -216,6 +310,9 @@ __global__ __launch_bounds__(kGaussPerBlock) void k_gauss_bwd(Batch B, WsPtrs W,
       const double syy = A1[0] * A1[0] + A1[1] * A1[1] + A1[2] * A1[2] + kDilation;
       const double inv = 1.0 / (sxx * syy - sxy * sxy);
       const double ca = syy * inv, cb = -sxy * inv, cc = sxx * inv;
+      // the conic and the opacity applied to the sums over pixels
+      const double gu = ca * g2[0] + cb * g2[1], gv = cb * g2[0] + cc * g2[1];
+      const double ga = 0.5 * g2[2], gb = g2[3], gc = 0.5 * g2[4];
       // dL/dSigma' (symmetric matrix entries)
       const double Gxx = -(ga * ca * ca + gb * ca * cb + gc * cb * cb);
       const double Gyy = -(ga * cb * cb + gb * cb * cc + gc * cc * cc);
@@ -288,7 +385,7 @@ __global__ __launch_bounds__(kGaussPerBlock) void k_gauss_bwd(Batch B, WsPtrs W,
         gq[1] = (gx4 - a * dot) * iqn;
         gq[2] = (gy4 - b * dot) * iqn;
         gq[3] = (gz4 - c * dot) * iqn;
-        go_eta = go * o * (1.0 - o);
+        go_eta = -(double)g2[5] * (1.0 - o);       // dL/do = -(sum of n) / o
         if (want_cov) {
           // dL/dSigma = T^T G' T
           double GT0[3], GT1[3];
@@ -454,7 +551,11 @@ hipError_t launch_preprocess_bwd(const Batch& b, const WsPtrs& w, int grad_flags
                                  StageTimer* tm) {
   if (b.n_total > 0) {
     Scope sc(tm, kStMerge, st);
-    const int grid = (b.n_total + kMergePerBlock - 1) / kMergePerBlock;
+    // windows: at most one per kWindow pairs of capacity and one per chunk; a
+    // workgroup takes several where the capacity leaves far more than the chip
+    // holds at once
+    const int64_t most = w.cap / kWindow + b.c_total;
+    const int grid = (int)(most < 16384 ? most : 16384);
     if (grad_flags & RTGS_GRAD_MAP)
       k_merge<10><<<grid, 256, 0, st>>>(b, w);
     else

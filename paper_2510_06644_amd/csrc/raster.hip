@@ -15,17 +15,15 @@
 // With a session's loss targets it also writes the gradient of the L1 loss
 // (Eq. 6) of every pixel it writes, so no loss pass reads the image back.
 //
-// Backward: walks the list from the block's largest saved position down,
-// recovering T before each blended fragment as T / (1 - alpha) (Eq. 5 read
-// as the reverse recurrence) and the normalised suffix colour/depth; the
-// per-fragment 2D gradients of one list entry are summed over the wave by a
-// reduce-scatter (lane swaps across halves and rows, then DPP row sums), the
-// four waves' sums are added in LDS in a fixed order, and the tile's total for
-// that Gaussian is stored in the pair's own slot: the pixel -> tile merge of
-// the paper's Gradient Merging Unit (Sec. 5.3) done with cross-lane
-// operations.  The tile -> Gaussian merge (its Stage Buffer) is a segmented
-// sum over the Gaussian's slots in the preprocessing backward; no float
-// atomics anywhere, so gradients are bitwise reproducible.
+// Backward: one wave per quadrant walks its part of the list from its last
+// blended position down, recovering T before each blended fragment as
+// T / (1 - alpha) (Eq. 5 read as the reverse recurrence) and the normalised
+// suffix colour/depth.  The pixels' gradients of a list entry are summed per
+// quadrant (k_raster_bwd) and stored in a slot of the (tile, Gaussian,
+// quadrant): the pixel -> tile merge of the paper's Gradient Merging Unit
+// (Sec. 5.3).  The tile -> Gaussian merge (its Stage Buffer) adds a Gaussian's
+// slots in the preprocessing backward; no float atomics anywhere, so gradients
+// are bitwise reproducible.
 #include "rtgs_internal.h"
 
 namespace rtgs {
@@ -50,12 +48,10 @@ struct TileCtx {
   bool inside;                  // the block lies (partly) in the image
   bool has;                     // a sample pixel exists (mask) in the block
   int pix;
-  unsigned wbit;
 };
 
-// The sample a thread takes by default: wave w the 8x8 quadrant w.
-__device__ __forceinline__ int quadrant_sample() {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+// The sample a lane takes by default: wave w the 8x8 quadrant w.
+__device__ __forceinline__ int quadrant_sample(int wave, int lane) {
   return ((wave >> 1) * 8 + (lane >> 3)) * 16 + (wave & 1) * 8 + (lane & 7);
 }
 
@@ -70,7 +66,6 @@ __device__ __forceinline__ TileCtx tile_ctx(const Batch& B, int tile, int sidx) 
   c.lt = tile - S.tile_base;
   c.tile_x0 = (c.lt % S.tiles_x) << (4 + S.sub_sx);
   c.tile_y0 = (c.lt / S.tiles_x) << (4 + S.sub_sy);
-  const int wave = (int)threadIdx.x >> 6;
   const int sx = sidx & 15, sy = sidx >> 4;
   c.bx0 = c.tile_x0 + (sx << S.sub_sx);
   c.by0 = c.tile_y0 + (sy << S.sub_sy);
@@ -93,7 +88,6 @@ __device__ __forceinline__ TileCtx tile_ctx(const Batch& B, int tile, int sidx) 
         }
   }
   c.pix = c.py * S.width + c.px;
-  c.wbit = 1u << wave;
   return c;
 }
 
@@ -234,7 +228,7 @@ __global__ __launch_bounds__(kBlock) void k_raster_fwd(Batch B, WsPtrs W) {
   __shared__ int4 s_box[4];
   const int tile = tile_of_block(B.t_total);
   if (tile >= B.t_total) return;
-  int sidx = quadrant_sample();
+  int sidx = quadrant_sample((int)threadIdx.x >> 6, (int)threadIdx.x & 63);
   if (BAL) {
     const TileCtx c0 = tile_ctx<ONE>(B, tile, sidx);
     sidx = lane_schedule(batch_session<ONE>(B, c0.s), W, tile, c0.tile_x0, c0.tile_y0, s_key,
@@ -282,7 +276,7 @@ __global__ __launch_bounds__(kBlock) void k_raster_fwd(Batch B, WsPtrs W) {
     // (16 k, the address the step reads anyway)
     int last16 = -1;
     for (int q = 0; q < kBlock / 64; ++q) {
-      unsigned long long m = wave_entries(s_m, 64 * q, cnt, c.wbit);
+      unsigned long long m = wave_entries(s_m, 64 * q, cnt, 1u << fwave);
       // every lane evaluates each entry; the decisions are selects, not
       // branches: skip (alpha < 1/255), stop (T would fall below 1e-4; the
       // fragment is excluded) or blend
@@ -377,23 +371,61 @@ __global__ __launch_bounds__(kBlock) void k_raster_fwd(Batch B, WsPtrs W) {
     }
 }
 
-constexpr int kBwdBatch = 64;            // list entries staged per batch
+constexpr int kBwdBatch = 64;            // list entries per staging step (one per lane)
 
-// Gaussian-major slot of the pair (Gaussian g, tile (tx, ty)): g's first slot
-// plus the tile's row-major index inside g's tile rectangle.
-__device__ __forceinline__ int64_t pair_slot(const WsPtrs& W, uint32_t g, int tx, int ty) {
-  const int4 r = W.rect[g];
-  return (int64_t)W.goff[g] + (ty - r.y) * (r.z - r.x + 1) + (tx - r.x);
+// Entries per group of the backward's two passes, and the LDS swizzle of a
+// group's (-dL/dpower, w) pairs.  Pass 1 writes entry `slot`, sample (row r,
+// column c) of the wave's 8x8 samples; pass 2's lane (entry e, row r) reads
+// two columns at a time (16 bytes).  XOR by the slot and by the row's parity
+// spreads a quarter wave's 16-byte reads over all banks.
+constexpr int kGrp = 8;
+
+// Byte offset in a group's 64 pairs of sample (r, c), slot bits excluded: the
+// slot enters by XOR with slot_bits(slot).
+__device__ __forceinline__ unsigned pair_off(int r, int c) {
+  return 128u * (unsigned)((c >> 1) ^ (r & 1)) + 16u * (unsigned)r + 8u * (unsigned)(c & 1);
+}
+__device__ __forceinline__ unsigned slot_bits(int slot) { return 528u * (unsigned)slot; }
+
+// LDS traffic between the lanes of one wave: a wave's LDS operations execute
+// in order, so only the compiler has to be held.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// NV = 10 (all parameters: u, v, a, b, c, o, r, g, b, z) or 6 (pose only:
-// u, v, a, b, c, z).  GA: some session has an alpha-image gradient (without
-// one, its term of dL/dalpha is left out rather than added as zero).  Each
-// (tile, Gaussian) pair gets the sum of its pixels' gradients in slot
-// pair_slot(); the sum is formed in a fixed order (lane swaps and DPP row sums
-// inside each wave, then the four waves in order), so the result is bitwise
-// reproducible and no float atomics are used.  Eight waves per SIMD: the
-// compiler is held to 64 VGPRs.
+// NV = 10 (all parameters) or 6 (pose only) sums per list entry.  GA: some
+// session has an alpha-image gradient (without one, its term of dL/dalpha is
+// left out rather than added as zero).
+//
+// One wave per workgroup, for one 8x8 quadrant of a tile: nothing is shared
+// between the quadrants, so no wave waits at a barrier for a busier one and a
+// finished wave's place is refilled at once.  Each (tile, Gaussian, quadrant)
+// that some pixel blended gets the sums of its pixels in a slot of its own and
+// a flag byte; everything else is neither written nor read.
+//
+// Bound by VALU issue, so the design minimises instructions per (list entry,
+// wave).  Two passes over groups of kGrp entries:
+//  1. lane = pixel: alpha again, T and the suffix recovered, giving two values
+//     per (entry, pixel), n = -dL/dpower and the blend weight w, stored to LDS;
+//  2. lane = (entry, row of 8 pixels): the NV sums over the row's pixels as
+//     plain FMAs, the offsets to the Gaussian's centre shared along rows and
+//     columns; then one reduce-scatter over the 8 rows for all 8 entries.
+// The sums, d = centre - pixel: n dx, n dy, n dx^2, n dx dy, n dy^2, n (NV = 10
+// only), w g_r, w g_g, w g_b (NV = 10 only), w g_z; the conic and the opacity
+// are applied once per Gaussian by the preprocessing backward:
+//   d power / d(u, v) = -(a dx + b dy, b dx + c dy), d power / d(a, b, c) =
+//   -(dx^2 / 2, dx dy, dy^2 / 2), dL/do = sum alpha dL/dalpha / o.
+// All sums are formed in a fixed order: bitwise reproducible, no float atomics.
+//
+// Measured at 1200x680 / 300k, NV = 10: 241 -> 165 us (109M -> 79M wave VALU
+// instructions, 438 -> 141 MB moved); pose only at 640x480 / 100k: 109 -> 84 us.
+// Before, four waves of a tile met at two barriers per 64 entries, summed ten
+// values over the wave per entry (lane swaps and DPP, 29 instructions), and
+// every pair without a gradient was written as zeros.  The two passes alone,
+// still with the barriers: 239 us.
+//
 // FRAG: the forward saved its fragments (frag_base): each entry's blending
 // lanes and their (alpha, 1 - alpha) are read instead of re-evaluating alpha,
 // and entries no lane of the wave blended are skipped without arithmetic; the
@@ -401,28 +433,33 @@ __device__ __forceinline__ int64_t pair_slot(const WsPtrs& W, uint32_t g, int tx
 // of the re-evaluating form.
 // BAL: the forward assigned lanes by previous work (lane_schedule); the same
 // samples go to the same lanes here (the saved quadrant bits are per wave).
-template <int NV, bool GA, bool FRAG, bool BAL, bool ONE>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8)))
+// IRR: some tile's samples may not form the 8x8 pixel grid of its quadrants
+// (downsampled frames, BAL); pass 2 then takes each sample's own centre.
+template <int NV, bool GA, bool FRAG, bool BAL, bool ONE, bool IRR>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5)))
 void k_raster_bwd(Batch B, WsPtrs W) {
-  constexpr int kStride = NV + 1;          // odd stride: conflict-free epilogue reads
-  __shared__ float4 s_r0[kBwdBatch], s_r1[kBwdBatch], s_r2[kBwdBatch], s_cn[kBwdBatch];
-  __shared__ unsigned s_m[kBwdBatch];
-  __shared__ unsigned long long s_fm[FRAG ? 4 : 1][FRAG ? kBwdBatch : 1];
-  // per wave: kStride floats per entry, then one float that takes the
-  // reduce-scatter outputs no entry needs; rows padded to 16 bytes so they
-  // are cleared with 16-byte stores
-  constexpr int kPartRow = (kBwdBatch * kStride + 1 + 3) & ~3;
-  __shared__ __align__(16) float s_part[4][kPartRow];
-  __shared__ int s_hi;
-  const int tile = tile_of_block(B.t_total);
+  constexpr int NG = NV == 10 ? 4 : 1;     // upstream values pass 2 needs of a pixel
+  __shared__ float4 s_r0[kBwdBatch], s_r1[kBwdBatch], s_r2[kBwdBatch];
+  __shared__ uint32_t s_slot[kBwdBatch];
+  __shared__ unsigned long long s_fm[FRAG ? kBwdBatch : 1];
+  __shared__ __align__(16) float2 s_pair[kGrp * 64];        // the group's (n, w)
+  __shared__ float2 s_xy[IRR ? 64 : 1];                     // sample centres
+  // the XCD's band of tiles (as tile_of_block), its four waves in a row
+  const int per = (B.t_total + 7) >> 3;
+  const int tile = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 5);
+  const int wave = ((int)blockIdx.x >> 3) & 3;
   if (tile >= B.t_total) return;
-  const int sidx = BAL ? (int)W.lane_perm[(int64_t)tile * kBlock + threadIdx.x] : quadrant_sample();
+  const int lane = threadIdx.x;
+  const int sidx = BAL ? (int)W.lane_perm[(int64_t)tile * kBlock + wave * 64 + lane]
+                       : quadrant_sample(wave, lane);
   const TileCtx c = tile_ctx<ONE>(B, tile, sidx);
   const SessionDev& S = batch_session<ONE>(B, c.s);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int ltx = c.lt % S.tiles_x, lty = c.lt / S.tiles_x;
   const bool active = c.has && (S.pmask == nullptr || S.pmask[c.pix] != 0);
+  const bool grid8 = !IRR || (!BAL && (S.sub_sx | S.sub_sy) == 0);   // samples are 8x8 pixels
   const int64_t hw = (int64_t)S.width * S.height;
+  const int start = (int)min((int64_t)W.tile_start[tile], W.cap);
+  const int end = (int)min((int64_t)W.tile_start[tile + 1], W.cap);
   int last = -1;
   float Tc = 1.f, g0 = 0.f, g1 = 0.f, g2 = 0.f, gD = 0.f, gA = 0.f;
   if (active) {
@@ -435,96 +472,119 @@ void k_raster_bwd(Batch B, WsPtrs W) {
     if (GA && S.dl_alpha) gA = S.dl_alpha[c.pix];
   }
   const float gAT = gA * Tc;        // dA/dalpha_j = T_final / (1 - alpha_j)
-  if (tid == 0) s_hi = -1;
-  __syncthreads();
-  if (last >= 0) atomicMax(&s_hi, last);
-  __syncthreads();
-  const int start = (int)min((int64_t)W.tile_start[tile], W.cap);
-  const int end = (int)min((int64_t)W.tile_start[tile + 1], W.cap);
-  // a saved position outside this tile's list (state of another forward) is
-  // never followed past the list
-  const int hi = min(s_hi, end - 1);
+  // the wave's last blended position; one outside this tile's list (state of
+  // another forward) is never followed past the list
+  int hi = last;
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) hi = max(hi, __shfl_xor(hi, off));
+  hi = __builtin_amdgcn_readfirstlane(min(hi, end - 1));
+  if (hi < start) return;
   const float pxf = (float)c.px + 0.5f, pyf = (float)c.py + 0.5f;
-  // saved fragments: this wave's last blended position, its stream and cursor
-  int wave_last = last;
+  // saved fragments: the wave's stream and cursor
   uint32_t fcur = 0;
   int64_t fbase = 0;
   if (FRAG) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) wave_last = max(wave_last, __shfl_xor(wave_last, off));
     fcur = W.fcount[(int64_t)tile * 4 + wave];
     fbase = frag_base(start, end, wave);
   }
+  // pass 2: this lane's entry of a group, its row of samples, and the row's
+  // upstream gradients (exchanged through LDS once, then kept)
+  const int ge = lane & 7, gr = lane >> 3;
+  float G[8][NG];
+  {
+    float4* sg = reinterpret_cast<float4*>(s_pair);
+    sg[lane] = make_float4(g0, g1, g2, gD);
+    if (IRR) s_xy[lane] = make_float2(pxf, pyf);
+    wave_lds_order();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const float4 v = sg[8 * gr + q];
+      if (NV == 10) {
+        G[q][0] = v.x;
+        G[q][1 % NG] = v.y;
+        G[q][2 % NG] = v.z;
+        G[q][3 % NG] = v.w;
+      } else {
+        G[q][0] = v.w;
+      }
+    }
+    wave_lds_order();
+  }
+  const float qx0 = (float)(c.tile_x0 + (wave & 1) * 8) + 0.5f;      // grid8: first column
+  const float qyr = (float)(c.tile_y0 + (wave >> 1) * 8 + gr) + 0.5f;   // grid8: this row
+  char* const pair_base = reinterpret_cast<char*>(s_pair);
+  const unsigned w_off = pair_off(lane >> 3, lane & 7);
+  const unsigned r_off0 = pair_off(gr, 0) ^ slot_bits(ge), r_off1 = pair_off(gr, 2) ^ slot_bits(ge);
   // S_j . g: the colour and depth of the fragments behind j, normalised by
   // the transmittance T_{j+1} they start from, dotted with the upstream gradient
   float SG = 0.f;
-  float* part = s_part[wave];
-  // the Gaussian id this thread stages next (loaded one batch ahead)
+  // quadrant mask and Gaussian of the entry this lane stages next
+  int b0 = max(hi + 1 - kBwdBatch, start);
+  unsigned nq = 0;
   uint32_t nid = 0;
-  {
-    const int b0 = max(hi + 1 - kBwdBatch, start);
-    if (tid < hi + 1 - b0) nid = W.ids[b0 + tid];
+  if (lane < hi + 1 - b0) {
+    nq = W.qmask[b0 + lane];
+    nid = W.ids[b0 + lane];
   }
   for (int bend = hi + 1; bend > start; bend -= kBwdBatch) {
-    const int b0 = max(bend - kBwdBatch, start);
-    const int cnt = bend - b0;
-    const int lrel = last - b0;     // entries k <= lrel lie before the pixel's stop
-    const uint32_t gid = nid;       // Gaussian of entry b0 + tid (tid < cnt)
-    __syncthreads();
-    if (tid < cnt) {
-      const GaussRec r = W.rec[gid];
-      s_r0[tid] = r.pos;
-      s_r1[tid] = conic_log2(r.conic);
-      s_r2[tid] = r.col;
-      s_cn[tid] = r.conic;
-      // the forward staged every entry up to the last blended one of any
-      // pixel of the tile, and saved its quadrant mask
-      s_m[tid] = W.qmask[b0 + tid];
-      if (FRAG) {
-        // blend masks; a wave reads only entries up to its last blend, all of
-        // which its forward evaluated and wrote
-        const ulonglong2* fm = reinterpret_cast<const ulonglong2*>(W.fmask + (int64_t)(b0 + tid) * 4);
-        const ulonglong2 a = fm[0], b = fm[1];
-        s_fm[0][tid] = a.x;
-        s_fm[1][tid] = a.y;
-        s_fm[2][tid] = b.x;
-        s_fm[3][tid] = b.y;
-      }
+    b0 = max(bend - kBwdBatch, start);
+    const int lrel = last - b0;     // entries at or before lrel lie before the pixel's stop
+    // the forward staged every entry up to the last blended one of any pixel
+    // of the tile, and saved which quadrants it can reach
+    bool hit = lane < bend - b0 && ((nq >> wave) & 1u) != 0;
+    unsigned long long fm = 0;
+    if (FRAG && hit) {
+      fm = W.fmask[(int64_t)(b0 + lane) * 4 + wave];
+      hit = fm != 0;                // no lane of the wave blended it
+    }
+    unsigned long long m = __ballot(hit);
+    int k = __popcll(m);            // staged entries, in list order
+    if (hit) {
+      const int at = (int)lane_rank(m);
+      const GaussRec r = W.rec[nid];
+      s_r0[at] = r.pos;
+      s_r1[at] = conic_log2(r.conic);
+      s_r2[at] = r.col;
+      // the pair's slot: Gaussian-major, then row-major in its tile rectangle
+      s_slot[at] = W.goff[nid] + (uint32_t)(lty * __float_as_int(r.ext.y) + ltx) -
+                   __float_as_uint(r.ext.x);
+      if (FRAG) s_fm[at] = fm;
     }
     {
       const int nb0 = max(b0 - kBwdBatch, start);
-      if (tid < b0 - nb0) nid = W.ids[nb0 + tid];
+      if (lane < b0 - nb0) {
+        nq = W.qmask[nb0 + lane];
+        nid = W.ids[nb0 + lane];
+      }
     }
-    // zero this batch's partial sums (each wave its own)
-    for (int i = lane; i < kBwdBatch * kStride / 4; i += 64)
-      reinterpret_cast<float4*>(part)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    __syncthreads();
-    for (int q = kBwdBatch / 64 - 1; q >= 0; --q) {
-      unsigned long long m = wave_entries(s_m, 64 * q, cnt, c.wbit);
-      auto step = [&](int k) {
-        const float4 k4 = s_r1[k];
-        Frag f;
-        bool contrib, clamped;
-        if (FRAG) {
-          if (b0 + k > wave_last) return;                // after every blend of the wave
-          const unsigned long long bm = s_fm[wave][k];
-          if (bm == 0) return;                           // no lane blended this entry
-          fcur -= (uint32_t)__popcll(bm);
-          contrib = ((bm >> lane) & 1ull) != 0;
-          float2 rec = make_float2(0.f, 1.f);
-          if (contrib) rec = W.fdata[fbase + fcur + lane_rank(bm)];
-          const float4 r0 = s_r0[k];
-          f.dx = (r0.x - pxf) + r0.z;
-          f.dy = (r0.y - pyf) + r0.w;
-          f.alpha = fabsf(rec.x);
-          f.om = rec.y;
-          clamped = rec.x < 0.f;
-        } else {
-          f = frag_alpha(s_r0[k], k4, pxf, pyf);
-          contrib = k <= lrel && !(f.alpha < kAlphaMin);
-          if (__ballot(contrib) == 0) return;            // no lane blended this entry
-          clamped = k4.w * f.e > kAlphaMax;
-        }
+    wave_lds_order();
+    int slot = 0;                   // entries in the group
+    unsigned long long kpack = 0;   // their staged positions, 8 bits each
+    while (m) {
+      // descending list order: entry b0 + pos, staged at k
+      const int pos = 63 - __builtin_clzll(m);
+      m &= ~(1ull << pos);
+      --k;
+      // ---- pass 1
+      const float4 k4 = s_r1[k];
+      Frag f;
+      bool contrib, clamped, some = true;
+      if (FRAG) {
+        const unsigned long long bm = s_fm[k];
+        fcur -= (uint32_t)__popcll(bm);
+        contrib = ((bm >> lane) & 1ull) != 0;
+        float2 rec = make_float2(0.f, 1.f);
+        if (contrib) rec = W.fdata[fbase + fcur + lane_rank(bm)];
+        f.alpha = fabsf(rec.x);
+        f.om = rec.y;
+        clamped = rec.x < 0.f;
+      } else {
+        f = frag_alpha(s_r0[k], k4, pxf, pyf);
+        contrib = pos <= lrel && !(f.alpha < kAlphaMin);
+        some = __ballot(contrib) != 0;
+        clamped = k4.w * f.e > kAlphaMax;
+      }
+      if (some) {                   // some lane blended this entry
         // lanes that did not blend it take alpha = 0 and 1 - alpha = 1, so
         // every update below leaves their state unchanged and their
         // gradients exactly zero (selects, not branches)
@@ -545,92 +605,93 @@ void k_raster_bwd(Batch B, WsPtrs W) {
         Tc = Tj;
         // the clamp alpha = 0.99 has no gradient to o or to the power
         const bool live = contrib && !clamped;
-        const float ng = live ? -(f.alpha * dla) : 0.f;  // -dL/dpower
-        const float pg = ng * f.dx, qg = ng * f.dy;
-        // summed over the tile's pixels, these give the 2D gradients once
-        // the Gaussian's conic is applied (epilogue)
-        float v[NV];
-        v[0] = pg;
-        v[1] = qg;
-        v[2] = pg * f.dx;
-        v[3] = pg * f.dy;
-        v[4] = qg * f.dy;
-        v[NV - 1] = w * gD;                               // depth slot (last)
-        if (NV == 10) {
-          v[5] = ng;                                      // o dL/do (epilogue)
-          v[6] = w * g0;
-          v[7] = w * g1;
-          v[8] = w * g2;
-        }
-        float x[3];
-        wave_reduce_scatter<NV>(v, x);
-        if ((lane & 15) == 15) {
-          const int row = lane >> 4;
-          // x[j] is value wave_scatter_index(NV, row, j): that of j = 0 plus
-          // 2 j, or for the output only odd rows carry, that minus 1; even
-          // rows write that output to the spare float, so every store is
-          // made by all four row ends at once
-          float* dst = part + k * kStride + wave_scatter_index(NV, row, 0);
+        const float n = live ? -(f.alpha * dla) : 0.f;   // -dL/dpower
+        *reinterpret_cast<float2*>(pair_base + (w_off ^ slot_bits(slot))) = make_float2(n, w);
+        kpack |= (unsigned long long)k << (8 * slot);
+        ++slot;
+      }
+      if (slot != kGrp && (m || slot == 0)) continue;
+      // ---- pass 2: the group's entries (fewer than kGrp at the end of a step)
+      wave_lds_order();
+      const int ke = (int)(kpack >> (8 * ge)) & (kBwdBatch - 1);
+      const float4 r0 = s_r0[ke];
+      float v[NV];
 #pragma unroll
-          for (int j = 0; j < 3; ++j) {
-            if (1 + 2 * j < NV / 2)
-              dst[2 * j] = x[j];
-            else if (2 * j < NV / 2)
-              ((row & 1) ? dst : part + kBwdBatch * kStride + 1 - 2 * j)[2 * j - 1] = x[j];
+      for (int i = 0; i < NV; ++i) v[i] = 0.f;
+      if (grid8) {
+        // sums of n, n dx, n dx^2 along the row
+        float a0 = 0.f, a1 = 0.f, a2 = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float4 p = *reinterpret_cast<const float4*>(
+              pair_base + ((q & 1) ? r_off1 : r_off0) + 256 * (q >> 1));
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const int col = 2 * q + j;
+            const float n = j ? p.z : p.x, w = j ? p.w : p.y;
+            const float dx = (r0.x - (qx0 + (float)col)) + r0.z;
+            const float nd = n * dx;
+            a0 += n;
+            a1 += nd;
+            a2 = __builtin_fmaf(nd, dx, a2);
+            if (NV == 10) {
+#pragma unroll
+              for (int t = 0; t < 3; ++t) v[6 + t] = __builtin_fmaf(w, G[col][t % NG], v[6 + t]);
+            }
+            v[NV - 1] = __builtin_fmaf(w, G[col][NG - 1], v[NV - 1]);
           }
         }
-      };
-      while (m) {
-        // descending list order, two entries per iteration (their alpha
-        // evaluations are independent and can overlap)
-        const int b1 = 63 - __builtin_clzll(m);
-        m &= ~(1ull << b1);
-        step(64 * q + b1);
-        if (m) {
-          const int b2 = 63 - __builtin_clzll(m);
-          m &= ~(1ull << b2);
-          step(64 * q + b2);
+        const float dy = (r0.y - qyr) + r0.w;
+        v[0] = a1;
+        v[1] = dy * a0;
+        v[2] = a2;
+        v[3] = dy * a1;
+        v[4] = dy * v[1];
+        if (NV == 10) v[5] = a0;
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float4 p = *reinterpret_cast<const float4*>(
+              pair_base + ((q & 1) ? r_off1 : r_off0) + 256 * (q >> 1));
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const int col = 2 * q + j;
+            const float n = j ? p.z : p.x, w = j ? p.w : p.y;
+            const float2 xy = s_xy[(8 * gr + col) % (IRR ? 64 : 1)];
+            const float dx = (r0.x - xy.x) + r0.z, dy = (r0.y - xy.y) + r0.w;
+            const float nx = n * dx, ny = n * dy;
+            v[0] += nx;
+            v[1] += ny;
+            v[2] = __builtin_fmaf(nx, dx, v[2]);
+            v[3] = __builtin_fmaf(nx, dy, v[3]);
+            v[4] = __builtin_fmaf(ny, dy, v[4]);
+            if (NV == 10) {
+              v[5] += n;
+#pragma unroll
+              for (int t = 0; t < 3; ++t) v[6 + t] = __builtin_fmaf(w, G[col][t % NG], v[6 + t]);
+            }
+            v[NV - 1] = __builtin_fmaf(w, G[col][NG - 1], v[NV - 1]);
+          }
         }
       }
-    }
-    __syncthreads();
-    if (tid < cnt) {
-      const int64_t slot = pair_slot(W, gid, ltx, lty);
-      if (slot < W.cap) {
-        float t[NV];
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-          const int o = tid * kStride + i;
-          t[i] = ((s_part[0][o] + s_part[1][o]) + s_part[2][o]) + s_part[3][o];
-        }
-        // d power / d(u, v) = -(a dx + b dy, b dx + c dy) and
-        // d power / d(a, b, c) = -(dx^2 / 2, dx dy, dy^2 / 2): the sums of
-        // p = -g dx and q = -g dy (g = dL/dpower) and of p dx, p dy, q dy
-        // become the 2D gradients with the conic applied once here
-        const float4 cn = s_cn[tid];
-        float* dst = W.partial + slot * NV;
-        dst[0] = __builtin_fmaf(cn.x, t[0], cn.y * t[1]);
-        dst[1] = __builtin_fmaf(cn.y, t[0], cn.z * t[1]);
-        dst[2] = 0.5f * t[2];
-        dst[3] = t[3];
-        dst[4] = 0.5f * t[4];
-        // alpha = o e below the clamp, so dalpha/do = e = alpha / o and
-        // dL/do = sum alpha dL/dalpha / o = -(sum of -dL/dpower) / o
-        if (NV == 10) dst[5] = -t[5] / cn.w;
-#pragma unroll
-        for (int i = NV == 10 ? 6 : 5; i < NV; ++i) dst[i] = t[i];
+      float x[3];
+      rows8_reduce_scatter<NV>(v, x);
+      if (!(lane & 8) && ge < slot && (int64_t)s_slot[ke] < W.cap) {
+        // slot layout: quarter h = lane / 16 holds its two (one) paired totals
+        // together, the unpaired totals of the two halves follow (sum_at)
+        const int64_t at = ((int64_t)s_slot[ke] * 4 + wave) * NV;
+        float* dst = W.partial + at;
+        const int h = lane >> 4;
+        if (NV == 10)
+          *reinterpret_cast<float2*>(dst + 2 * h) = make_float2(x[0], x[1]);
+        else
+          dst[h] = x[0];
+        if (!(h & 1)) dst[NV - 2 + (h >> 1)] = NV == 10 ? x[2] : x[1];
+        if (h == 0) W.live[(int64_t)s_slot[ke] * 4 + wave] = 1;
       }
-    }
-  }
-  // pairs after the last blended fragment of every pixel carry no gradient
-  const int z0 = max(hi + 1, start);
-  for (int pos = z0 + tid; pos < end; pos += kBlock) {
-    const uint32_t g = W.ids[pos];
-    const int64_t slot = pair_slot(W, g, ltx, lty);
-    if (slot < W.cap) {
-      float* dst = W.partial + slot * NV;
-#pragma unroll
-      for (int i = 0; i < NV; ++i) dst[i] = 0.f;
+      wave_lds_order();
+      slot = 0;
+      kpack = 0;
     }
   }
 }
@@ -670,18 +731,24 @@ hipError_t launch_raster_fwd(const Batch& b, const WsPtrs& w, bool stats, bool f
 template <int NV, bool GA>
 static void raster_bwd_variant(const Batch& b, const WsPtrs& w, bool frags, bool bal, int grid,
                                hipStream_t st) {
+  const bool one = b.n_sessions == 1, irr = b.any_sub != 0;
   if (frags) {
     if (bal)
-      k_raster_bwd<NV, GA, true, true, false><<<grid, kBlock, 0, st>>>(b, w);
+      k_raster_bwd<NV, GA, true, true, false, true><<<4 * grid, 64, 0, st>>>(b, w);
     else
-      k_raster_bwd<NV, GA, true, false, false><<<grid, kBlock, 0, st>>>(b, w);
+      k_raster_bwd<NV, GA, true, false, false, true><<<4 * grid, 64, 0, st>>>(b, w);
+  } else if (bal) {
+    k_raster_bwd<NV, GA, false, true, false, true><<<4 * grid, 64, 0, st>>>(b, w);
+  } else if (irr) {
+    if (one)
+      k_raster_bwd<NV, GA, false, false, true, true><<<4 * grid, 64, 0, st>>>(b, w);
+    else
+      k_raster_bwd<NV, GA, false, false, false, true><<<4 * grid, 64, 0, st>>>(b, w);
   } else {
-    if (bal)
-      k_raster_bwd<NV, GA, false, true, false><<<grid, kBlock, 0, st>>>(b, w);
-    else if (b.n_sessions == 1)
-      k_raster_bwd<NV, GA, false, false, true><<<grid, kBlock, 0, st>>>(b, w);
+    if (one)
+      k_raster_bwd<NV, GA, false, false, true, false><<<4 * grid, 64, 0, st>>>(b, w);
     else
-      k_raster_bwd<NV, GA, false, false, false><<<grid, kBlock, 0, st>>>(b, w);
+      k_raster_bwd<NV, GA, false, false, false, false><<<4 * grid, 64, 0, st>>>(b, w);
   }
 }
 

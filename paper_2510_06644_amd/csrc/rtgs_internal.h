@@ -19,6 +19,7 @@ constexpr double kNearZ = 0.2;
 constexpr double kDilation = 0.3;
 constexpr double kFovClamp = 1.3;
 constexpr int kChunk = 1024;              // Gaussians per binning chunk (1 per thread)
+constexpr int kWindow = 512;              // pairs per window of the tile -> Gaussian merge
 constexpr int kMaxTilesPerSession = 12288; // LDS tile histogram of one session (48 KB)
 
 // Adam state of a session's map for an update fused into the backward
@@ -95,25 +96,32 @@ struct WsLayout {
   uint64_t table;       // SessionDev[RTGS_MAX_SESSIONS]
   uint64_t counters;    // int64[8]: 0 pairs of this call, 2 entries of big_tiles
   uint64_t rec;         // GaussRec[N]: the 64-byte raster record of each Gaussian
+  uint64_t ext;         // float2[N]: half-widths of the alpha = 1/255 box (debug output)
   uint64_t rect;        // int4[N]: tile rectangle
   uint64_t cnt;         // uint32[N]: tiles touched
   uint64_t goff;        // uint32[N]: first slot of the Gaussian's pairs, Gaussian-major
   uint64_t zkey;        // uint32[N]: depth bits of the Gaussian's sort key (projection)
-  uint64_t grad2d;      // float[N][10]: merged dL/d(u, v, a, b, c, o, r, g, b, z)
+  uint64_t grad2d;      // float[N][10]: the pair sums of each Gaussian added up (order: sum_at)
   uint64_t pose_part;   // double[B][16]: per-block view-matrix gradient partial sums
   uint64_t chunk_total; // uint32[C + 1]: pairs per chunk
   uint64_t chunk_off;   // uint32[C + 1]: exclusive scan of chunk_total
+  uint64_t win_off;     // uint32[C + 1]: exclusive scan of the chunks' merge windows
+  uint64_t vlist;       // uint2[C][kChunk + 1]: (Gaussian, first pair) of a chunk's Gaussians
+                        // with pairs, in order; then (0, the chunk's end)
+  uint64_t window;      // uint4[cap / kWindow + C]: a window's pairs [x, y), vlist entries [z, w]
+  uint64_t edge;        // float[windows][2][10]: sums of Gaussians crossing a window's ends
   uint64_t hist;        // uint32[sum_s C_s T_s]: per (chunk, tile) counts, then each
                         // chunk's exclusive scan over its tiles (run offsets in the chunk)
   uint64_t gsum;        // uint32[16][T]: per (group of chunks, tile) sums
   uint64_t tile_count;  // uint32[T + 1]
   uint64_t tile_start;  // uint32[T + 1]
   uint64_t big_tiles;   // uint32[T]: tiles whose list is too long for the one-pass sort
-  uint64_t keys;        // uint64[cap]: (depth bits << 32 | id), chunk-major
-  uint64_t keys_tm;     // uint64[cap]: the long lists gathered tile-major for their sort
+  uint64_t keys;        // uint64[cap]: (depth bits << 32 | id), chunk-major; in partial's memory
+  uint64_t keys_tm;     // uint64[cap]: the long lists gathered tile-major for their sort; likewise
   uint64_t ids;         // uint32[cap]
   uint64_t qmask;       // uint8[cap]: quadrants of its tile each list entry can reach
-  uint64_t partial;     // float[cap][10]: per (tile, Gaussian) merged 2D gradient
+  uint64_t partial;     // float[cap][4][10]: sums of each (tile, Gaussian) pair's quadrants
+  uint64_t live;        // uint8[cap][4]: 1 where partial holds sums (zero between backwards)
   uint64_t state_t;     // float[pixels]: recomputed final T
   uint64_t state_last;  // int32[pixels]: recomputed last position
   uint64_t lane_perm;   // uint8[T][256]: sample of each lane (lanes assigned by previous work)
@@ -141,15 +149,25 @@ struct alignas(64) GaussRec {
   float4 pos;     // u_hi, v_hi, u_lo, v_lo (centre as a float32 pair)
   float4 conic;   // a, b, c (inverse 2D covariance), opacity
   float4 col;     // r, g, b, depth z
-  float4 ext;     // e_x, e_y (half-widths of the alpha = 1/255 box), t = 2 ln(255 o), 0
+  float4 ext;     // tile rectangle as bits: y0 * width + x0, width (int); t = 2 ln(255 o); 0
 };
 static_assert(sizeof(GaussRec) == 64, "one line per record");
+
+// Place in a slot of partial (and in grad2d) of sum v of the raster backward
+// (k_raster_bwd; NV sums, H = NV / 2): what rows8_reduce_scatter leaves in a
+// quarter wave is stored together, the last sum of each half at the end.
+constexpr int sum_at(int nv, int v) {
+  const int h = nv / 2, half = v / h, i = v % h;
+  if (i == h - 1) return nv - 2 + half;
+  return (h / 2) * (2 * half + (i & 1)) + (i >> 1);
+}
 
 // Pointers derived from a workspace.
 struct WsPtrs {
   SessionDev* table;
   long long* counters;
   GaussRec* rec;
+  float2* ext;
   int4* rect;
   uint32_t* cnt;
   uint32_t* goff;
@@ -158,6 +176,10 @@ struct WsPtrs {
   double* pose_part;
   uint32_t* chunk_total;
   uint32_t* chunk_off;
+  uint32_t* win_off;
+  uint2* vlist;
+  uint4* window;
+  float* edge;
   uint32_t* hist;
   uint32_t* gsum;
   uint32_t* tile_count;
@@ -168,6 +190,7 @@ struct WsPtrs {
   uint32_t* ids;
   uint8_t* qmask;
   float* partial;
+  uint8_t* live;
   float* state_t;
   int32_t* state_last;
   uint8_t* lane_perm;
@@ -188,6 +211,7 @@ struct Batch {
   int32_t b_total;      // per-Gaussian blocks over all sessions
   int32_t c_total;      // binning chunks over all sessions
   int32_t t_max;        // largest tile count of one session
+  int32_t any_sub;      // some session is downsampled (one sample per block of pixels)
   SessionDev one;       // the session of a one-session batch, passed with the launch
                         // arguments instead of through a table upload
 };
@@ -380,26 +404,12 @@ constexpr int kDppRowShr1 = 0x111;
 constexpr int kDppRowShr2 = 0x112;
 constexpr int kDppRowShr4 = 0x114;
 constexpr int kDppRowShr8 = 0x118;
-constexpr int kDppRowBcast15 = 0x142;
-constexpr int kDppRowBcast31 = 0x143;
+constexpr int kDppRowRor8 = 0x128;
 
 template <int CTRL, int ROW_MASK, bool BOUND_ZERO>
 __device__ __forceinline__ float dpp_f(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
       0, __builtin_bit_cast(int, v), CTRL, ROW_MASK, 0xf, BOUND_ZERO));
-}
-
-// Sum of a 16-lane row, inclusive scan by shifted adds (out-of-row sources
-// read 0): lane 15 of each row ends with the row total.
-__device__ __forceinline__ float row_sum_to_lane15(float v) {
-  v += dpp_f<kDppRowShr1, 0xf, true>(v);
-  v += dpp_f<kDppRowShr2, 0xf, true>(v);
-  v += dpp_f<kDppRowShr4, 0xf, true>(v);
-  v += dpp_f<kDppRowShr8, 0xf, true>(v);
-  // keep the last step a single DPP add in every lane: otherwise the add is
-  // sunk into the caller's lane-15-only branch as a separate move and add
-  asm volatile("" : "+v"(v));
-  return v;
 }
 
 // a + b for a pair of registers after v_permlane32_swap: lanes 0-31 get
@@ -422,45 +432,30 @@ __device__ __forceinline__ float swap16_add(float a, float b) {
   return __uint_as_float(x) + __uint_as_float(y);
 }
 
-// Wavefront reduce-scatter of NV (even, <= 12) per-lane values.  Two
-// lane-swap steps each halve the number of values a lane carries while
-// adding pairs of lanes; the (at most 3) values left are then summed along
-// each 16-lane row.  With NV / 2 odd, the last value after the first swap has
-// no partner for the second: it is summed along each row as it is, and the
-// total of row 2i is added into row 2i + 1 by a row broadcast.  Lane 16 r + 15
-// (row r) ends with, in x[s], the wavefront total of value
-// wave_scatter_index(NV, r, s) where that is >= 0.  About 3 NV instructions
-// instead of the 6 NV of a full tree per value.
+// Reduce-scatter of NV (even, NV / 2 odd, <= 10) per-lane values over the 8
+// lanes l, l + 8, ..., l + 56 of each l < 8: two lane-swap steps each halve
+// the number of values a lane carries while adding pairs of lanes, the last
+// value after the first step is summed over both rows, and a rotation by 8
+// inside each 16-lane row adds the last pair.  Lane 32 h + 16 p + 8 x + l (any
+// x) ends with the totals of values h NV / 2 + p + 2 j in x[j] for
+// j < NV / 4, and of value h NV / 2 + NV / 2 - 1 in x[NV / 4] (any p).
 template <int NV>
-__device__ __forceinline__ void wave_reduce_scatter(const float (&v)[NV], float (&x)[3]) {
+__device__ __forceinline__ void rows8_reduce_scatter(const float (&v)[NV], float (&x)[3]) {
   constexpr int H = NV / 2;
-  static_assert(NV % 2 == 0 && H <= 6, "even value count up to 12");
+  static_assert(NV % 2 == 0 && H % 2 == 1 && H <= 5, "two halves of an odd count");
   float w[H];
 #pragma unroll
   for (int i = 0; i < H; ++i) w[i] = swap32_add(v[i], v[i + H]);
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
-    if (2 * j + 1 < H) {
-      x[j] = row_sum_to_lane15(swap16_add(w[2 * j], w[2 * j + 1]));
-    } else if (2 * j < H) {
-      x[j] = row_sum_to_lane15(w[2 * j]);
-      // rows 1 and 3 add lane 15 of rows 0 and 2 (even rows end with
-      // something meaningless, which wave_scatter_index excludes)
-      x[j] += dpp_f<kDppRowBcast15, 0xf, true>(x[j]);
-      asm volatile("" : "+v"(x[j]));   // one DPP add in every lane (see above)
+    if (2 * j < H) {
+      const float s = 2 * j + 1 < H ? swap16_add(w[2 * j], w[(2 * j + 1) % H])
+                                    : swap16_add(w[2 * j], w[2 * j]);
+      x[j] = s + dpp_f<kDppRowRor8, 0xf, true>(s);
     } else {
       x[j] = 0.f;
     }
   }
-}
-
-// The value whose total lane 16 row + 15 holds in x[s] after
-// wave_reduce_scatter<NV>, or -1 if that output carries none.
-__device__ __forceinline__ int wave_scatter_index(int nv, int row, int s) {
-  const int h = nv / 2;
-  if (2 * s + 1 < h) return (row >> 1) * h + (row & 1) + 2 * s;
-  if (2 * s < h) return (row & 1) ? (row >> 1) * h + 2 * s : -1;
-  return -1;
 }
 
 // One Adam element update (t the step count after it):
