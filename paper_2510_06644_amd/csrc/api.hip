@@ -151,7 +151,7 @@ WsLayout make_layout(const Counts& c, int64_t cap, bool frags) {
   L.tile_start = take(4 * (t + 1));
   L.big_tiles = take(4 * (t + 1));
   L.ids = take(4 * (uint64_t)cap);
-  L.qmask = take((uint64_t)cap);
+  L.hits = take(32 * ((uint64_t)cap / 64 + t + 1));
   L.partial = take(4 * 4 * 10 * (uint64_t)cap + 2 * kAlign);
   // the keys are dead once the lists are sorted, the sums live from the raster
   // backward to the merge: they share memory
@@ -161,6 +161,8 @@ WsLayout make_layout(const Counts& c, int64_t cap, bool frags) {
   L.state_t = take(4 * (uint64_t)c.px_total);
   L.state_last = take(4 * (uint64_t)c.px_total);
   L.lane_perm = take(256 * t);
+  L.order_n = take(4 * 8 * kOrderClasses);
+  L.order = take(4 * 8 * kOrderClasses * 4 * ((t + 7) / 8));
   if (frags) {
     L.fmask = take(8 * 4 * (uint64_t)cap);
     L.fcount = take(4 * 4 * t);
@@ -201,12 +203,14 @@ WsPtrs ws_ptrs(void* ws, const WsLayout& L) {
   w.keys = reinterpret_cast<unsigned long long*>(base + L.keys);
   w.keys_tm = reinterpret_cast<unsigned long long*>(base + L.keys_tm);
   w.ids = reinterpret_cast<uint32_t*>(base + L.ids);
-  w.qmask = reinterpret_cast<uint8_t*>(base + L.qmask);
+  w.hits = reinterpret_cast<unsigned long long*>(base + L.hits);
   w.partial = reinterpret_cast<float*>(base + L.partial);
   w.live = reinterpret_cast<uint8_t*>(base + L.live);
   w.state_t = reinterpret_cast<float*>(base + L.state_t);
   w.state_last = reinterpret_cast<int32_t*>(base + L.state_last);
   w.lane_perm = reinterpret_cast<uint8_t*>(base + L.lane_perm);
+  w.order_n = reinterpret_cast<uint32_t*>(base + L.order_n);
+  w.order = reinterpret_cast<uint32_t*>(base + L.order);
   if (L.fdata) {
     w.fmask = reinterpret_cast<unsigned long long*>(base + L.fmask);
     w.fcount = reinterpret_cast<uint32_t*>(base + L.fcount);
@@ -618,7 +622,11 @@ int32_t render_bwd_batched(rtgs_handle_t h, const rtgs_session* ss, int32_t ns, 
   if (r) return r;
   StageTimer* tm = h->timer.mask ? &h->timer : nullptr;
   hipError_t e = hipSuccess;
-  if (flags & RTGS_GRAD_RECOMPUTE_STATE) e = launch_raster_fwd(B, w, false, false, false, st, tm);
+  if (flags & RTGS_GRAD_RECOMPUTE_STATE) {
+    WsPtrs again = w;                 // the forward has filed the quadrants' work already
+    again.order = nullptr;
+    e = launch_raster_fwd(B, again, false, false, false, st, tm);
+  }
   bool alpha_grad = false;            // some session passes dL/dA
   for (int i = 0; i < ns; ++i) alpha_grad = alpha_grad || ss[i].dL_dalpha != nullptr;
   if (e == hipSuccess)

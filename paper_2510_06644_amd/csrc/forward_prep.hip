@@ -29,8 +29,9 @@ namespace {
 
 constexpr int kScanThreads = 1024;
 
-__global__ void k_init(long long* counters) {
-  if (threadIdx.x < 8) counters[threadIdx.x] = 0;
+__global__ void k_init(WsPtrs W) {
+  if (threadIdx.x < 8) W.counters[threadIdx.x] = 0;
+  W.order_n[threadIdx.x] = 0u;
 }
 
 struct Proj {
@@ -111,6 +112,8 @@ __global__ __launch_bounds__(kGaussPerBlock) void k_preprocess(Batch B, WsPtrs W
   const int li = ((int)blockIdx.x - S.block_base) * kGaussPerBlock + (int)threadIdx.x;
   // the call's counters start at zero (the binning passes run after this kernel)
   if (!REUSE && blockIdx.x == 0 && threadIdx.x < 8) W.counters[threadIdx.x] = 0;
+  static_assert(8 * kOrderClasses == kGaussPerBlock, "a thread per class");
+  if (blockIdx.x == 0) W.order_n[threadIdx.x] = 0u;
   if (li >= S.n) return;
   const int gid = S.gauss_base + li;
   float vm[12];
@@ -1015,7 +1018,7 @@ hipError_t launch_forward_prep(const Batch& b, const WsPtrs& w, unsigned long lo
   if (b.b_total <= 0) {
     // no Gaussians: k_preprocess (which zeroes the counters) does not run
     Scope sc(tm, kStInit, st);
-    k_init<<<1, 64, 0, st>>>(w.counters);
+    k_init<<<1, 8 * kOrderClasses, 0, st>>>(w);
   }
   if (b.b_total > 0) {
     Scope sc(tm, kStPreprocess, st);

@@ -29,11 +29,56 @@
 namespace rtgs {
 namespace {
 
-__device__ __forceinline__ int tile_of_block(int t_total) {
-  // Workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous
-  // band of tiles so neighbouring tiles share its L2.
+// The tile and quadrant of a one-wave workgroup of the forward.  Workgroups
+// are dealt round-robin to the 8 XCDs; each XCD gets a contiguous band of
+// tiles, the four quadrants of a tile in a row, so neighbours share its L2
+// (runs of 4 or 16 tiles dealt in turn: 3 of 88 us slower).
+__device__ __forceinline__ bool wave_of_block(int t_total, int& tile, int& wave) {
   const int per = (t_total + 7) >> 3;
-  return ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
+  tile = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 5);
+  wave = ((int)blockIdx.x >> 3) & 3;
+  return (int)(blockIdx.x >> 5) < per && tile < t_total;
+}
+
+// The backward takes a band's quadrants by falling work: at 12.9k waves on
+// 5120 places the last waves to start decide when the kernel ends (taken in
+// tile order it drained for 62 of 166 us at 1200x680 / 300k).  The forward
+// files each quadrant under the entries it walked up to its last blended one,
+// kOrderStep to a class; quadrants without work are not filed.
+constexpr int kOrderStep = 16;
+static_assert(kOrderClasses == 32, "a class per lane of half a wave");
+
+__device__ __forceinline__ void file_work(const WsPtrs& W, int t_total, int tile, int wave,
+                                          int entries) {
+  const int per = (t_total + 7) >> 3, band = (int)blockIdx.x & 7;
+  const int cls = band * kOrderClasses + min(entries / kOrderStep, kOrderClasses - 1);
+  const uint32_t at = atomicAdd(&W.order_n[cls], 1u);
+  W.order[(int64_t)cls * 4 * per + at] = (uint32_t)(4 * tile + wave);
+}
+
+// The tile and quadrant of a workgroup of the backward: the band's next one,
+// classes from the largest; tile order without an order (see raster_order).
+__device__ __forceinline__ bool wave_by_work(const WsPtrs& W, int t_total, int& tile, int& wave) {
+  const int per = (t_total + 7) >> 3, band = (int)blockIdx.x & 7, lane = threadIdx.x;
+  if (!W.order) return wave_of_block(t_total, tile, wave);
+  const uint32_t i = blockIdx.x >> 3;
+  const int cls = band * kOrderClasses + kOrderClasses - 1 - (lane & (kOrderClasses - 1));
+  const uint32_t n = W.order_n[cls];
+  uint32_t x = n;                          // inclusive scan from the largest class
+#pragma unroll
+  for (int off = 1; off < kOrderClasses; off <<= 1) {
+    const uint32_t y = __shfl_up(x, off, kOrderClasses);
+    if ((lane & (kOrderClasses - 1)) >= off) x += y;
+  }
+  const unsigned long long past = __ballot(x > i);
+  if (past == 0) return false;
+  const int c = __builtin_ctzll(past);     // lane of the class
+  const uint32_t before = (uint32_t)__shfl(x - n, c);
+  const int64_t list = (int64_t)(band * kOrderClasses + kOrderClasses - 1 - c) * 4 * per;
+  const uint32_t q = __builtin_amdgcn_readfirstlane(W.order[list + (i - before)]);
+  tile = (int)(q >> 2);
+  wave = (int)(q & 3u);
+  return tile < t_total;
 }
 
 // A tile holds 16x16 samples: one per pixel normally, or one per block of
@@ -92,76 +137,44 @@ __device__ __forceinline__ TileCtx tile_ctx(const Batch& B, int tile, int sidx) 
 }
 
 // Smallest value of the quadratic form q(d) = a dx^2 + 2 b dx dy + c dy^2
-// over the box [x0, x1] x [y0, y1] of offsets d (a convex quadratic: zero if
-// the box holds the centre, otherwise reached on an edge, where it is a 1D
-// quadratic minimised in closed form and clamped to the edge).
-// ia, ic: 1/a and 1/c (0 where a or c is not positive), shared by the four
-// quadrants of an entry.
+// over the box [x0, x1] x [y0, y1] of offsets d.  q decreases towards the
+// centre (d = 0), so the least value lies where the box faces it: on the line
+// dx = X, X the box's dx nearest 0, or dy = Y, each a 1D quadratic minimised
+// in closed form and clamped to the box (both at d = 0 if the box holds it).
+// ia, ic: 1/a and 1/c (0 where a or c is not positive).
 __device__ __forceinline__ float box_min_quad(float a, float b, float c, float ia, float ic,
                                               float x0, float x1, float y0, float y1) {
-  if (x0 <= 0.f && x1 >= 0.f && y0 <= 0.f && y1 >= 0.f) return 0.f;
-  float m = 3.0e38f;
-  const float xs[2] = {x0, x1}, ys[2] = {y0, y1};
-#pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    const float X = xs[e];                           // edge dx = X
-    const float dy = fminf(y1, fmaxf(y0, -b * X * ic));
-    m = fminf(m, a * X * X + 2.f * b * X * dy + c * dy * dy);
-    const float Y = ys[e];                           // edge dy = Y
-    const float dx = fminf(x1, fmaxf(x0, -b * Y * ia));
-    m = fminf(m, a * dx * dx + 2.f * b * dx * Y + c * Y * Y);
-  }
-  return m;
+  const float X = fminf(x1, fmaxf(x0, 0.f)), Y = fminf(y1, fmaxf(y0, 0.f));
+  const float dy = fminf(y1, fmaxf(y0, -b * X * ic));
+  const float dx = fminf(x1, fmaxf(x0, -b * Y * ia));
+  const float b2 = 2.f * b;
+  const float qx = __builtin_fmaf(a * X, X, dy * __builtin_fmaf(c, dy, b2 * X));
+  const float qy = __builtin_fmaf(c * Y, Y, dx * __builtin_fmaf(a, dx, b2 * Y));
+  return fminf(qx, qy);
 }
 
-// Bit w set when the alpha >= 1/255 ellipse (q <= t) of the Gaussian can
-// reach a pixel centre of the quadrant of wave w (8x8 sample blocks of
-// 2^sx x 2^sy pixels).  The margin keeps the test conservative against the
-// float32 evaluation of alpha.
-__device__ __forceinline__ unsigned quad_mask(float4 r0, float4 r1, float4 ex, int tx0, int ty0,
-                                              int sx, int sy) {
+// Whether the alpha >= 1/255 ellipse (q <= t) of the Gaussian can reach a
+// pixel centre of the box of samples (x0, y0) to (x1, y1) of a tile at pixel
+// (tx0, ty0), sample blocks of 2^sx x 2^sy pixels.  The margin keeps the test
+// conservative against the float32 evaluation of alpha and of the test.
+__device__ __forceinline__ bool box_hit(float4 r0, float4 r1, float level, int tx0, int ty0, int sx,
+                                        int sy, int x0, int y0, int x1, int y1) {
   const float u = r0.x + r0.z, v = r0.y + r0.w;
-  const float t = ex.z * (1.f + 1e-3f) + 1e-3f;
-  const float wx = (float)((8 << sx) - 1), wy = (float)((8 << sy) - 1);
-  const float ia = r1.x > 0.f ? 1.f / r1.x : 0.f, ic = r1.z > 0.f ? 1.f / r1.z : 0.f;
-  unsigned m = 0;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const float qx = (float)(tx0 + ((w & 1) * 8 << sx)) + 0.5f - u;
-    const float qy = (float)(ty0 + ((w >> 1) * 8 << sy)) + 0.5f - v;
-    const float q = box_min_quad(r1.x, r1.y, r1.z, ia, ic, qx, qx + wx, qy, qy + wy);
-    m |= (q <= t) ? (1u << w) : 0u;
-  }
-  return m;
+  const float t = __builtin_fmaf(level, 1.f + 1e-3f, 1e-3f);
+  const float ia = r1.x > 0.f ? __builtin_amdgcn_rcpf(r1.x) : 0.f;
+  const float ic = r1.z > 0.f ? __builtin_amdgcn_rcpf(r1.z) : 0.f;
+  const float qx0 = (float)(tx0 + (x0 << sx)) + 0.5f - u;
+  const float qy0 = (float)(ty0 + (y0 << sy)) + 0.5f - v;
+  const float qx1 = (float)(tx0 + ((x1 + 1) << sx) - 1) + 0.5f - u;
+  const float qy1 = (float)(ty0 + ((y1 + 1) << sy) - 1) + 0.5f - v;
+  return box_min_quad(r1.x, r1.y, r1.z, ia, ic, qx0, qx1, qy0, qy1) <= t;
 }
 
-// The same test against four boxes of samples, (x0, y0, x1, y1) inclusive,
-// one per wave (the lanes of a wave assigned by previous work).
-__device__ __forceinline__ unsigned box_mask(float4 r0, float4 r1, float4 ex, int tx0, int ty0,
-                                             int sx, int sy, const int4* boxes) {
-  const float u = r0.x + r0.z, v = r0.y + r0.w;
-  const float t = ex.z * (1.f + 1e-3f) + 1e-3f;
-  const float ia = r1.x > 0.f ? 1.f / r1.x : 0.f, ic = r1.z > 0.f ? 1.f / r1.z : 0.f;
-  unsigned m = 0;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const int4 bx = boxes[w];
-    const float qx0 = (float)(tx0 + (bx.x << sx)) + 0.5f - u;
-    const float qy0 = (float)(ty0 + (bx.y << sy)) + 0.5f - v;
-    const float qx1 = (float)(tx0 + ((bx.z + 1) << sx) - 1) + 0.5f - u;
-    const float qy1 = (float)(ty0 + ((bx.w + 1) << sy) - 1) + 0.5f - v;
-    const float q = box_min_quad(r1.x, r1.y, r1.z, ia, ic, qx0, qx1, qy0, qy1);
-    m |= (q <= t) ? (1u << w) : 0u;
-  }
-  return m;
-}
-
-// 64-bit ballot of "entry (base + lane) is in this wave's quadrant".
-__device__ __forceinline__ unsigned long long wave_entries(const unsigned* s_m, int base, int cnt,
-                                                           unsigned wbit) {
-  const int k = base + (int)(threadIdx.x & 63);
-  const bool hit = k < cnt && (s_m[k] & wbit) != 0;
-  return __ballot(hit);
+// Index of the mask of list entries b0 to b0 + 63 (b0 = start + 64 j) that
+// quadrant `wave` of a tile can reach: a tile's masks begin at
+// start / 64 + tile, which leaves every tile room for its last, partial mask.
+__device__ __forceinline__ int64_t hits_at(int start, int tile, int b0, int wave) {
+  return ((int64_t)(start >> 6) + tile + ((b0 - start) >> 6)) * 4 + wave;
 }
 
 // Saved fragments (the per-fragment state of the paper's R&B buffer): for
@@ -183,149 +196,241 @@ __device__ __forceinline__ uint32_t lane_rank(unsigned long long m) {
 // scheduling unit, Sec. 5.2): the tile's 256 samples sorted by the list
 // entries each walked in a previous forward (S.lane_work; ties and missing
 // values by sample index), wave w taking ranks 64 w to 64 w + 63, so each
-// wave's lanes finish together.  Each wave culls against the bounding box of
-// its samples.  Writes the permutation for the backward and the boxes to LDS.
-__device__ __forceinline__ int lane_schedule(const SessionDev& S, const WsPtrs& W, int tile,
-                                             int tile_x0, int tile_y0, uint32_t* s_key,
-                                             uint8_t* s_pix, int4* s_box) {
-  const int tid = threadIdx.x;
-  const int bx = tile_x0 + ((tid & 15) << S.sub_sx), by = tile_y0 + ((tid >> 4) << S.sub_sy);
+// wave's lanes finish together.  Writes the permutation for both rasterizers.
+__global__ __launch_bounds__(kBlock) void k_lane_schedule(Batch B, WsPtrs W) {
+  __shared__ uint32_t s_key[kBlock];
+  const int tile = blockIdx.x, tid = threadIdx.x;
+  const TileCtx c = tile_ctx<false>(B, tile, tid);
+  const SessionDev& S = batch_session<false>(B, c.s);
   uint32_t work = 0;
-  if (S.lane_work && bx < S.width && by < S.height) work = S.lane_work[by * S.width + bx];
+  if (S.lane_work && c.inside) work = S.lane_work[c.by0 * S.width + c.bx0];
   const uint32_t key = (work << 8) | (uint32_t)tid;
   s_key[tid] = key;
   __syncthreads();
   int rank = 0;
   for (int j = 0; j < kBlock; ++j) rank += s_key[j] < key ? 1 : 0;
-  s_pix[rank] = (uint8_t)tid;
-  __syncthreads();
-  const int sidx = s_pix[tid];
-  W.lane_perm[(int64_t)tile * kBlock + tid] = (uint8_t)sidx;
-  int x0 = sidx & 15, x1 = x0, y0 = sidx >> 4, y1 = y0;
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    x0 = min(x0, __shfl_xor(x0, off));
-    x1 = max(x1, __shfl_xor(x1, off));
-    y0 = min(y0, __shfl_xor(y0, off));
-    y1 = max(y1, __shfl_xor(y1, off));
-  }
-  if ((tid & 63) == 0) s_box[tid >> 6] = make_int4(x0, y0, x1, y1);
-  __syncthreads();
-  return sidx;
+  W.lane_perm[(int64_t)tile * kBlock + rank] = (uint8_t)tid;
 }
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// LDS traffic between the lanes of one wave: a wave's LDS operations execute
+// in order, so only the compiler has to be held.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+constexpr int kFwdStage = 16;             // entries walked at a time (16, 32, 8: 87, 90, 100 us)
+constexpr int kFwdQueue = kFwdStage + 64; // < kFwdStage left over + 64 new ones
+constexpr int kTabWords = 26;             // words of an entry's table (even; spreads the banks)
+
+// One wave per workgroup, for one 8x8 quadrant of a tile (as the backward).
+// It tests 64 list entries at a time, one a lane, against its quadrant (the
+// mask is saved for the backward), queues the ones that reach it in LDS, and
+// lets its pixels walk the queue kFwdStage entries at a time.
+//
+// Bound by VALU issue: instructions per walked entry are what counts.
+//  * The offsets of the 8 columns and, of the 8 rows, the two terms of the
+//    exponent that depend on the row alone are formed once per entry, by four
+//    lanes an entry, so that a pixel's exponent is two FMAs on three LDS
+//    values instead of nine operations; the values are frag_alpha's, bit for
+//    bit.  Samples that are not on the pixel grid (IRR: downsampled frames,
+//    BAL) use frag_alpha itself.
+//  * C += w (r, g, b, z) is one 4x4x1 MFMA: block i of four lanes multiplies
+//    the entry's four values (row j: value j) with its lanes' four weights,
+//    an exact FMA per element; the A operand of four entries is one LDS read,
+//    lane l holding value l & 3 of entry (l >> 2) & 3, broadcast by blocks.
+//  * A stopped pixel's T is negative, so `T' < 1e-4` also keeps it stopped.
+// Measured at 1200x680 / 300k: 92 -> 88 us (51.8M -> 36M wave VALU
+// instructions; 71 us of issue, exp at quarter rate included, the rest the
+// last waves draining); 640x480 / 100k 55 -> 49 us, 320x240 / 20k 21.6 -> 18 us.
+// Before, four waves of a tile shared batches of 256 entries, 29 VALU
+// instructions a walked entry.
+//
 // STATS: also count, per pixel, the fragments blended and the list entries
 // visited (the work counts of a frame); off in ordinary renders.
 // FRAG: also save the fragments' alpha (see frag_base).
-// BAL: lanes assigned by previous work (lane_schedule); also writes each
+// BAL: lanes assigned by previous work (k_lane_schedule); also writes each
 // sample's walked entries to S.lane_work_out for the next forward.
-template <bool STATS, bool FRAG, bool BAL, bool ONE>
-__global__ __launch_bounds__(kBlock) void k_raster_fwd(Batch B, WsPtrs W) {
-  __shared__ float4 s_r0[kBlock], s_r1[kBlock], s_r2[kBlock];
-  __shared__ unsigned s_m[kBlock];
-  __shared__ uint32_t s_key[BAL ? kBlock : 1];
-  __shared__ uint8_t s_pix[BAL ? kBlock : 1];
-  __shared__ int4 s_box[4];
-  const int tile = tile_of_block(B.t_total);
-  if (tile >= B.t_total) return;
-  int sidx = quadrant_sample((int)threadIdx.x >> 6, (int)threadIdx.x & 63);
-  if (BAL) {
-    const TileCtx c0 = tile_ctx<ONE>(B, tile, sidx);
-    sidx = lane_schedule(batch_session<ONE>(B, c0.s), W, tile, c0.tile_x0, c0.tile_y0, s_key,
-                         s_pix, s_box);
-  }
+template <bool STATS, bool FRAG, bool BAL, bool ONE, bool IRR>
+__global__ __launch_bounds__(64) void k_raster_fwd(Batch B, WsPtrs W) {
+  constexpr bool kPlain = !STATS && !FRAG && !BAL && !IRR;
+  __shared__ __align__(16) float s_tab[kFwdStage * kTabWords];
+  __shared__ float4 s_r0[kFwdQueue], s_k4[kFwdQueue], s_col[kFwdQueue];
+  __shared__ int s_pos[kFwdQueue];
+  int tile, wave;
+  if (!wave_of_block(B.t_total, tile, wave)) return;
+  const int lane = threadIdx.x;
+  const int sidx = BAL ? (int)W.lane_perm[(int64_t)tile * kBlock + wave * 64 + lane]
+                       : quadrant_sample(wave, lane);
   const TileCtx c = tile_ctx<ONE>(B, tile, sidx);
   const SessionDev& S = batch_session<ONE>(B, c.s);
-  const int tid = threadIdx.x;
+  const bool grid8 = !IRR || (!BAL && (S.sub_sx | S.sub_sy) == 0);   // samples are 8x8 pixels
   const bool active = c.has && (S.pmask == nullptr || S.pmask[c.pix] != 0);
   const float pxf = (float)c.px + 0.5f, pyf = (float)c.py + 0.5f;
+  // the box of samples the wave culls against
+  int x0 = (wave & 1) * 8, y0 = (wave >> 1) * 8, x1 = x0 + 7, y1 = y0 + 7;
+  if (BAL) {
+    x0 = x1 = sidx & 15;
+    y0 = y1 = sidx >> 4;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+      x0 = min(x0, __shfl_xor(x0, off));
+      x1 = max(x1, __shfl_xor(x1, off));
+      y0 = min(y0, __shfl_xor(y0, off));
+      y1 = max(y1, __shfl_xor(y1, off));
+    }
+  }
+  const float qx = (float)(c.tile_x0 + x0) + 0.5f, qy = (float)(c.tile_y0 + y0) + 0.5f;   // grid8
   // list positions fit in int32: the pair capacity is below 2^31
   const int start = (int)min((int64_t)W.tile_start[tile], W.cap);
   const int end = (int)min((int64_t)W.tile_start[tile + 1], W.cap);
   // T carries the pixel's stop in its sign: T > 0 while the pixel walks
-  // (T >= 1e-4 > 0 until the stop), -T once it has stopped (or never walks),
-  // so the per-entry test is one compare and no flag is carried across the loop
-  float T = active ? 1.f : -1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f, D = 0.f;
+  // (T >= 1e-4 > 0 until the stop), -T once it has stopped (or never walks)
+  float T = active ? 1.f : -1.f;
+  f32x4 C = {0.f, 0.f, 0.f, 0.f};           // colour, depth
   int last = -1;
   int stop = end;               // list position where the pixel stopped
   int nblend = 0;
-  const int fwave = tid >> 6, flane = tid & 63;
   uint32_t fcur = 0;            // saved fragments of this wave so far
-  const int64_t fbase = FRAG ? frag_base(start, end, fwave) : 0;
-  // the Gaussian id this thread stages next (loaded one batch ahead)
-  uint32_t nid = start + tid < end ? W.ids[start + tid] : 0u;
-  for (int b0 = start; b0 < end; b0 += kBlock) {
-    if (__syncthreads_and(!(T > 0.f))) break;
-    const int e = b0 + tid;
-    if (e < end) {
-      const GaussRec r = W.rec[nid];
-      s_r0[tid] = r.pos;
-      s_r1[tid] = conic_log2(r.conic);
-      s_r2[tid] = r.col;
-      const unsigned qm = BAL ? box_mask(r.pos, r.conic, r.ext, c.tile_x0, c.tile_y0, S.sub_sx,
-                                         S.sub_sy, s_box)
-                              : quad_mask(r.pos, r.conic, r.ext, c.tile_x0, c.tile_y0, S.sub_sx,
-                                          S.sub_sy);
-      s_m[tid] = qm;
-      W.qmask[e] = (uint8_t)qm;     // for the backward, which walks no entry unstaged here
+  const int64_t fbase = FRAG ? frag_base(start, end, wave) : 0;
+  const float* const t_x = s_tab + (lane & 7);
+  const float2* const t_y = reinterpret_cast<const float2*>(s_tab + 8) + (lane >> 3);
+  const float* const col_words = reinterpret_cast<const float*>(s_col) + (lane & 15);
+  int walked = 0, done = 0;     // entries walked up to the lane's last blended one; in all
+  int head = 0, queued = 0;     // head: a multiple of kFwdStage, so no batch wraps around
+  // the record this lane tests next, and the Gaussian after it: a list's test
+  // steps would otherwise wait for a dependent load each
+  uint32_t nid = start + lane < end ? W.ids[start + lane] : 0u;
+  GaussRec next;
+  if (start + lane < end) next = W.rec[nid];
+  nid = start + 64 + lane < end ? W.ids[start + 64 + lane] : 0u;
+  for (int b0 = start; b0 < end; b0 += 64) {
+    const GaussRec r = next;
+    bool hit = b0 + lane < end;
+    if (b0 + 64 + lane < end) next = W.rec[nid];
+    if (b0 + 128 + lane < end) nid = W.ids[b0 + 128 + lane];
+    if (hit) {
+      hit = box_hit(r.pos, r.conic, r.ext.z, c.tile_x0, c.tile_y0, S.sub_sx, S.sub_sy, x0, y0, x1,
+                    y1);
     }
-    if (e + kBlock < end) nid = W.ids[e + kBlock];
-    __syncthreads();
-    const int cnt = min(kBlock, end - b0);
-    // the lane's last blended entry of this batch, as its LDS byte offset
-    // (16 k, the address the step reads anyway)
-    int last16 = -1;
-    for (int q = 0; q < kBlock / 64; ++q) {
-      unsigned long long m = wave_entries(s_m, 64 * q, cnt, 1u << fwave);
+    const unsigned long long m = __ballot(hit);
+    if (lane == 0) W.hits[hits_at(start, tile, b0, wave)] = m;
+    if (hit) {
+      int at = head + queued + (int)lane_rank(m);
+      at -= at >= kFwdQueue ? kFwdQueue : 0;
+      s_r0[at] = r.pos;
+      s_k4[at] = conic_log2(r.conic);
+      s_col[at] = r.col;
+      s_pos[at] = b0 + lane;
+    }
+    queued += __popcll(m);
+    while (queued >= kFwdStage || (b0 + 64 >= end && queued > 0)) {
+      const int n = min(kFwdStage, queued);
+      // entries of opacity 0 fill the last group of four up
+      if (lane < (-n & 3)) {
+        const int at = head + n + lane;
+        s_r0[at] = s_k4[at] = s_col[at] = make_float4(0.f, 0.f, 0.f, 0.f);
+        s_pos[at] = 0;
+      }
+      wave_lds_order();
+      if (grid8) {
+        // kParts lanes an entry, each its share of the columns and rows
+        constexpr int kParts = 64 / kFwdStage, kShare = 8 / kParts;
+        const int e = lane % kFwdStage, h = (lane / kFwdStage) * kShare;
+        const float4 r0 = s_r0[head + e], k4 = s_k4[head + e];
+        float* t = s_tab + e * kTabWords;
+        if (e < ((n + 3) & ~3)) {
+#pragma unroll
+          for (int i = 0; i < kShare; i += 2) {
+            const float d0 = (r0.x - (qx + (float)(h + i))) + r0.z;
+            const float d1 = (r0.x - (qx + (float)(h + i + 1))) + r0.z;
+            *reinterpret_cast<float2*>(t + h + i) = make_float2(d0, d1);
+          }
+#pragma unroll
+          for (int i = 0; i < kShare; ++i) {
+            const float dy = (r0.y - (qy + (float)(h + i))) + r0.w;
+            *reinterpret_cast<float2*>(t + 8 + 2 * (h + i)) =
+                make_float2(k4.y * dy, (k4.z * dy) * dy);
+          }
+          if (h == 0) *reinterpret_cast<float2*>(t + 24) = make_float2(k4.x, k4.w);
+        }
+        wave_lds_order();
+      }
+      int lastk = -1;               // the lane's last blended entry of these
       // every lane evaluates each entry; the decisions are selects, not
       // branches: skip (alpha < 1/255), stop (T would fall below 1e-4; the
       // fragment is excluded) or blend
-      auto step = [&](int k) {
-        const Frag f = frag_alpha(s_r0[k], s_r1[k], pxf, pyf);
+      auto weight = [&](int k) -> float {
+        Frag f;
+        float raw;
+        if (grid8) {
+          const float dx = t_x[k * kTabWords];
+          const float2 y = t_y[k * (kTabWords / 2)];
+          const float2 ao = *reinterpret_cast<const float2*>(s_tab + k * kTabWords + 24);
+          const float p2 = __builtin_fmaf(dx, __builtin_fmaf(ao.x, dx, y.x), y.y);
+          f.e = __builtin_amdgcn_exp2f(p2);
+          raw = ao.y * f.e;
+          f.alpha = fminf(kAlphaMax, raw);
+          f.om = fmaxf(1.f - kAlphaMax, __builtin_fmaf(-ao.y, f.e, 1.f));
+        } else {
+          const float4 kk = s_k4[head + k];
+          f = frag_alpha(s_r0[head + k], kk, pxf, pyf);
+          raw = kk.w * f.e;
+        }
         const float tn = T * f.om;
-        const bool hit = T > 0.f && !(f.alpha < kAlphaMin);
-        const bool blend = hit && !(tn < kTMin);
-        const bool stop_here = hit != blend;              // hit and T would fall below 1e-4
-        if (STATS || BAL) stop = stop_here ? b0 + k : stop;
+        const bool seen = !(f.alpha < kAlphaMin);
+        const bool blend = seen && !(tn < kTMin);
+        if (STATS || BAL) stop = T > 0.f && seen && !blend ? s_pos[head + k] : stop;
         const float w = blend ? f.alpha * T : 0.f;       // adds exactly 0 otherwise
-        const float4 col = s_r2[k];
-        C0 = __builtin_fmaf(w, col.x, C0);
-        C1 = __builtin_fmaf(w, col.y, C1);
-        C2 = __builtin_fmaf(w, col.z, C2);
-        D = __builtin_fmaf(w, col.w, D);
-        T = blend ? tn : (stop_here ? -T : T);
-        last16 = blend ? (k << 4) : last16;
+        T = blend ? tn : (seen ? -fabsf(T) : T);
+        lastk = blend ? k : lastk;
         if (STATS) nblend += blend ? 1 : 0;
-        if (FRAG) {
+        if (FRAG && k < n) {
           const unsigned long long bm = __ballot(blend);
-          if (flane == 0) W.fmask[(int64_t)(b0 + k) * 4 + fwave] = bm;
-          if (blend) {
-            const float4 k4 = s_r1[k];
+          if (lane == 0) W.fmask[(int64_t)s_pos[head + k] * 4 + wave] = bm;
+          if (blend)
             W.fdata[fbase + fcur + lane_rank(bm)] =
-                make_float2(k4.w * f.e > kAlphaMax ? -f.alpha : f.alpha, f.om);
-          }
+                make_float2(raw > kAlphaMax ? -f.alpha : f.alpha, f.om);
           fcur += (uint32_t)__popcll(bm);
         }
+        return w;
       };
-      while (m) {
-        if (__ballot(T > 0.f) == 0) break;             // the whole wave has stopped
-        step(64 * q + __builtin_ctzll(m));
-        m &= m - 1;
-        if (m) {                                       // two entries per check
-          step(64 * q + __builtin_ctzll(m));
-          m &= m - 1;
-        }
+      // unrolled in the plain kernels, so that every position is an immediate
+#pragma unroll(kPlain ? kFwdStage / 4 : 1)
+      for (int k = 0; k < kFwdStage; k += 4) {
+        if (k >= n || __ballot(T > 0.f) == 0) break;     // or the whole wave has stopped
+        const float a = col_words[4 * (head + k)];
+        C = __builtin_amdgcn_mfma_f32_4x4x1f32(a, weight(k), C, 2, 0, 0);
+        C = __builtin_amdgcn_mfma_f32_4x4x1f32(a, weight(k + 1), C, 2, 1, 0);
+        C = __builtin_amdgcn_mfma_f32_4x4x1f32(a, weight(k + 2), C, 2, 2, 0);
+        C = __builtin_amdgcn_mfma_f32_4x4x1f32(a, weight(k + 3), C, 2, 3, 0);
       }
+      if (lastk >= 0) {
+        last = s_pos[head + lastk];
+        walked = done + lastk + 1;
+      }
+      done += n;
+      wave_lds_order();
+      queued -= n;
+      head = head == kFwdQueue - kFwdStage ? 0 : head + kFwdStage;
     }
-    last = last16 >= 0 ? b0 + (last16 >> 4) : last;
-    __syncthreads();
+    if (__ballot(T > 0.f) == 0) break;
   }
-  if (FRAG && flane == 0) W.fcount[(int64_t)tile * 4 + fwave] = fcur;
+  if (FRAG && lane == 0) W.fcount[(int64_t)tile * 4 + wave] = fcur;
+  if (W.order) {                // (not when the backward recomputes the state)
+    int w = walked;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) w = max(w, __shfl_xor(w, off));
+    if (lane == 0 && w > 0) file_work(W, B.t_total, tile, wave, w);
+  }
   T = fabsf(T);
   if (!c.inside) return;
   if (BAL && S.lane_work_out) {
-    const int walked = active ? min(stop + 1, end) - start : 0;
-    S.lane_work_out[c.by0 * S.width + c.bx0] = (uint16_t)min(walked, 65535);
+    const int visited = active ? min(stop + 1, end) - start : 0;
+    S.lane_work_out[c.by0 * S.width + c.bx0] = (uint16_t)min(visited, 65535);
   }
   const int64_t hw = (int64_t)S.width * S.height;
   // loss gradient (Eq. 6, L1 colour and depth, means over the active pixels):
@@ -338,26 +443,26 @@ __global__ __launch_bounds__(kBlock) void k_raster_fwd(Batch B, WsPtrs W) {
   }
   // every pixel of the lane's block: the sample gets its result, the others
   // (masked out) render as background
-  const int x1 = min(S.width, c.bx0 + (1 << S.sub_sx));
-  const int y1 = min(S.height, c.by0 + (1 << S.sub_sy));
-  for (int y = c.by0; y < y1; ++y)
-    for (int x = c.bx0; x < x1; ++x) {
+  const int ex = min(S.width, c.bx0 + (1 << S.sub_sx));
+  const int ey = min(S.height, c.by0 + (1 << S.sub_sy));
+  for (int y = c.by0; y < ey; ++y)
+    for (int x = c.bx0; x < ex; ++x) {
       const int p = y * S.width + x;
       const bool me = p == c.pix;
       if (S.color) {
-        S.color[p] = me ? C0 : 0.f;
-        S.color[hw + p] = me ? C1 : 0.f;
-        S.color[2 * hw + p] = me ? C2 : 0.f;
+        S.color[p] = me ? C[0] : 0.f;
+        S.color[hw + p] = me ? C[1] : 0.f;
+        S.color[2 * hw + p] = me ? C[2] : 0.f;
       }
       if (S.l1_dcolor) {
         const float m = S.pmask ? (S.pmask[p] ? 1.f : 0.f) : 1.f;
-        const float v[4] = {me ? C0 : 0.f, me ? C1 : 0.f, me ? C2 : 0.f, me ? D : 0.f};
+        const float v[4] = {me ? C[0] : 0.f, me ? C[1] : 0.f, me ? C[2] : 0.f, me ? C[3] : 0.f};
 #pragma unroll
         for (int k = 0; k < 3; ++k)
           S.l1_dcolor[k * hw + p] = m * l1_sc * sign_of(v[k] - S.l1_tcolor[k * hw + p]);
         S.l1_ddepth[p] = m * l1_sd * sign_of(v[3] - S.l1_tdepth[p]);
       }
-      if (S.depth) S.depth[p] = me ? D : 0.f;
+      if (S.depth) S.depth[p] = me ? C[3] : 0.f;
       if (S.alpha) S.alpha[p] = me ? 1.f - T : 0.f;
       if (S.final_T) S.final_T[p] = me ? T : 1.f;
       if (S.last_idx) S.last_idx[p] = me ? last : -1;
@@ -386,14 +491,6 @@ __device__ __forceinline__ unsigned pair_off(int r, int c) {
   return 128u * (unsigned)((c >> 1) ^ (r & 1)) + 16u * (unsigned)r + 8u * (unsigned)(c & 1);
 }
 __device__ __forceinline__ unsigned slot_bits(int slot) { return 528u * (unsigned)slot; }
-
-// LDS traffic between the lanes of one wave: a wave's LDS operations execute
-// in order, so only the compiler has to be held.
-__device__ __forceinline__ void wave_lds_order() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // NV = 10 (all parameters) or 6 (pose only) sums per list entry.  GA: some
 // session has an alpha-image gradient (without one, its term of dL/dalpha is
@@ -444,11 +541,8 @@ void k_raster_bwd(Batch B, WsPtrs W) {
   __shared__ unsigned long long s_fm[FRAG ? kBwdBatch : 1];
   __shared__ __align__(16) float2 s_pair[kGrp * 64];        // the group's (n, w)
   __shared__ float2 s_xy[IRR ? 64 : 1];                     // sample centres
-  // the XCD's band of tiles (as tile_of_block), its four waves in a row
-  const int per = (B.t_total + 7) >> 3;
-  const int tile = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 5);
-  const int wave = ((int)blockIdx.x >> 3) & 3;
-  if (tile >= B.t_total) return;
+  int tile, wave;
+  if (!wave_by_work(W, B.t_total, tile, wave)) return;
   const int lane = threadIdx.x;
   const int sidx = BAL ? (int)W.lane_perm[(int64_t)tile * kBlock + wave * 64 + lane]
                        : quadrant_sample(wave, lane);
@@ -518,20 +612,14 @@ void k_raster_bwd(Batch B, WsPtrs W) {
   // S_j . g: the colour and depth of the fragments behind j, normalised by
   // the transmittance T_{j+1} they start from, dotted with the upstream gradient
   float SG = 0.f;
-  // quadrant mask and Gaussian of the entry this lane stages next
-  int b0 = max(hi + 1 - kBwdBatch, start);
-  unsigned nq = 0;
-  uint32_t nid = 0;
-  if (lane < hi + 1 - b0) {
-    nq = W.qmask[b0 + lane];
-    nid = W.ids[b0 + lane];
-  }
-  for (int bend = hi + 1; bend > start; bend -= kBwdBatch) {
-    b0 = max(bend - kBwdBatch, start);
+  // the entries the quadrant can reach, of the 64 staged next (saved by the
+  // forward up to the wave's last blended one at least), and this lane's
+  int b0 = start + ((hi - start) & ~(kBwdBatch - 1));
+  unsigned long long nh = W.hits[hits_at(start, tile, b0, wave)];
+  uint32_t nid = b0 + lane <= hi ? W.ids[b0 + lane] : 0u;
+  for (; b0 >= start; b0 -= kBwdBatch) {
     const int lrel = last - b0;     // entries at or before lrel lie before the pixel's stop
-    // the forward staged every entry up to the last blended one of any pixel
-    // of the tile, and saved which quadrants it can reach
-    bool hit = lane < bend - b0 && ((nq >> wave) & 1u) != 0;
+    bool hit = b0 + lane <= hi && ((nh >> lane) & 1ull) != 0;
     unsigned long long fm = 0;
     if (FRAG && hit) {
       fm = W.fmask[(int64_t)(b0 + lane) * 4 + wave];
@@ -550,12 +638,9 @@ void k_raster_bwd(Batch B, WsPtrs W) {
                    __float_as_uint(r.ext.x);
       if (FRAG) s_fm[at] = fm;
     }
-    {
-      const int nb0 = max(b0 - kBwdBatch, start);
-      if (lane < b0 - nb0) {
-        nq = W.qmask[nb0 + lane];
-        nid = W.ids[nb0 + lane];
-      }
+    if (b0 > start) {
+      nh = W.hits[hits_at(start, tile, b0 - kBwdBatch, wave)];
+      nid = W.ids[b0 - kBwdBatch + lane];
     }
     wave_lds_order();
     int slot = 0;                   // entries in the group
@@ -701,26 +786,48 @@ void k_raster_bwd(Batch B, WsPtrs W) {
 template <bool STATS>
 static void raster_fwd_variant(const Batch& b, const WsPtrs& w, bool frags, bool bal, int grid,
                                hipStream_t st) {
+  const bool one = b.n_sessions == 1, irr = b.any_sub != 0;
   if (frags) {
     if (bal)
-      k_raster_fwd<STATS, true, true, false><<<grid, kBlock, 0, st>>>(b, w);
+      k_raster_fwd<STATS, true, true, false, true><<<grid, 64, 0, st>>>(b, w);
     else
-      k_raster_fwd<STATS, true, false, false><<<grid, kBlock, 0, st>>>(b, w);
+      k_raster_fwd<STATS, true, false, false, true><<<grid, 64, 0, st>>>(b, w);
+  } else if (bal) {
+    k_raster_fwd<STATS, false, true, false, true><<<grid, 64, 0, st>>>(b, w);
+  } else if (irr) {
+    if (one)
+      k_raster_fwd<STATS, false, false, true, true><<<grid, 64, 0, st>>>(b, w);
+    else
+      k_raster_fwd<STATS, false, false, false, true><<<grid, 64, 0, st>>>(b, w);
   } else {
-    if (bal)
-      k_raster_fwd<STATS, false, true, false><<<grid, kBlock, 0, st>>>(b, w);
-    else if (b.n_sessions == 1)
-      k_raster_fwd<STATS, false, false, true><<<grid, kBlock, 0, st>>>(b, w);
+    if (one)
+      k_raster_fwd<STATS, false, false, true, false><<<grid, 64, 0, st>>>(b, w);
     else
-      k_raster_fwd<STATS, false, false, false><<<grid, kBlock, 0, st>>>(b, w);
+      k_raster_fwd<STATS, false, false, false, false><<<grid, 64, 0, st>>>(b, w);
   }
 }
 
-hipError_t launch_raster_fwd(const Batch& b, const WsPtrs& w, bool stats, bool frags, bool bal,
+// Waves of both rasterizers: four per tile, in bands of tiles per XCD.
+static int raster_grid(const Batch& b) { return 32 * ((b.t_total + 7) / 8); }
+
+// The backward's order by work is for grids whose waves are not all on the chip
+// at once: up to four a SIMD (1024 tiles) they are, and neighbours then share
+// the L2 better in tile order.  Measured, backward in tile order and by work:
+// 836 tiles (1200x680 at 1 in 4, 500k) 136 and 141 us; 1200 tiles (640x480 /
+// 100k) 84 and 71 us; 3225 tiles (1200x680 / 300k) 165 and 146 us.
+static WsPtrs raster_order(const Batch& b, const WsPtrs& w) {
+  WsPtrs r = w;
+  if (b.t_total <= 1024) r.order = nullptr;
+  return r;
+}
+
+hipError_t launch_raster_fwd(const Batch& b, const WsPtrs& w0, bool stats, bool frags, bool bal,
                              hipStream_t st, StageTimer* tm) {
   if (b.t_total <= 0) return hipSuccess;
-  const int grid = 8 * ((b.t_total + 7) / 8);
+  const int grid = raster_grid(b);
+  const WsPtrs w = raster_order(b, w0);
   Scope sc(tm, kStRasterFwd, st);
+  if (bal) k_lane_schedule<<<b.t_total, kBlock, 0, st>>>(b, w);
   if (stats)
     raster_fwd_variant<true>(b, w, frags, bal, grid, st);
   else
@@ -734,28 +841,29 @@ static void raster_bwd_variant(const Batch& b, const WsPtrs& w, bool frags, bool
   const bool one = b.n_sessions == 1, irr = b.any_sub != 0;
   if (frags) {
     if (bal)
-      k_raster_bwd<NV, GA, true, true, false, true><<<4 * grid, 64, 0, st>>>(b, w);
+      k_raster_bwd<NV, GA, true, true, false, true><<<grid, 64, 0, st>>>(b, w);
     else
-      k_raster_bwd<NV, GA, true, false, false, true><<<4 * grid, 64, 0, st>>>(b, w);
+      k_raster_bwd<NV, GA, true, false, false, true><<<grid, 64, 0, st>>>(b, w);
   } else if (bal) {
-    k_raster_bwd<NV, GA, false, true, false, true><<<4 * grid, 64, 0, st>>>(b, w);
+    k_raster_bwd<NV, GA, false, true, false, true><<<grid, 64, 0, st>>>(b, w);
   } else if (irr) {
     if (one)
-      k_raster_bwd<NV, GA, false, false, true, true><<<4 * grid, 64, 0, st>>>(b, w);
+      k_raster_bwd<NV, GA, false, false, true, true><<<grid, 64, 0, st>>>(b, w);
     else
-      k_raster_bwd<NV, GA, false, false, false, true><<<4 * grid, 64, 0, st>>>(b, w);
+      k_raster_bwd<NV, GA, false, false, false, true><<<grid, 64, 0, st>>>(b, w);
   } else {
     if (one)
-      k_raster_bwd<NV, GA, false, false, true, false><<<4 * grid, 64, 0, st>>>(b, w);
+      k_raster_bwd<NV, GA, false, false, true, false><<<grid, 64, 0, st>>>(b, w);
     else
-      k_raster_bwd<NV, GA, false, false, false, false><<<4 * grid, 64, 0, st>>>(b, w);
+      k_raster_bwd<NV, GA, false, false, false, false><<<grid, 64, 0, st>>>(b, w);
   }
 }
 
-hipError_t launch_raster_bwd(const Batch& b, const WsPtrs& w, int pose_only, bool alpha_grad,
+hipError_t launch_raster_bwd(const Batch& b, const WsPtrs& w0, int pose_only, bool alpha_grad,
                              bool frags, bool bal, hipStream_t st, StageTimer* tm) {
   if (b.t_total <= 0) return hipGetLastError();
-  const int grid = 8 * ((b.t_total + 7) / 8);
+  const int grid = raster_grid(b);
+  const WsPtrs w = raster_order(b, w0);
   Scope sc(tm, kStRasterBwd, st);
   if (pose_only) {
     if (alpha_grad)

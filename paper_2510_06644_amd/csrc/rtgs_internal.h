@@ -20,6 +20,7 @@ constexpr double kDilation = 0.3;
 constexpr double kFovClamp = 1.3;
 constexpr int kChunk = 1024;              // Gaussians per binning chunk (1 per thread)
 constexpr int kWindow = 512;              // pairs per window of the tile -> Gaussian merge
+constexpr int kOrderClasses = 32;         // work classes of the raster backward's order
 constexpr int kMaxTilesPerSession = 12288; // LDS tile histogram of one session (48 KB)
 
 // Adam state of a session's map for an update fused into the backward
@@ -119,12 +120,14 @@ struct WsLayout {
   uint64_t keys;        // uint64[cap]: (depth bits << 32 | id), chunk-major; in partial's memory
   uint64_t keys_tm;     // uint64[cap]: the long lists gathered tile-major for their sort; likewise
   uint64_t ids;         // uint32[cap]
-  uint64_t qmask;       // uint8[cap]: quadrants of its tile each list entry can reach
+  uint64_t hits;        // uint64[cap / 64 + T][4]: masks of the list entries each quadrant can reach
   uint64_t partial;     // float[cap][4][10]: sums of each (tile, Gaussian) pair's quadrants
   uint64_t live;        // uint8[cap][4]: 1 where partial holds sums (zero between backwards)
   uint64_t state_t;     // float[pixels]: recomputed final T
   uint64_t state_last;  // int32[pixels]: recomputed last position
   uint64_t lane_perm;   // uint8[T][256]: sample of each lane (lanes assigned by previous work)
+  uint64_t order_n;     // uint32[8][kOrderClasses]: quadrants filed per XCD band and work class
+  uint64_t order;       // uint32[8][kOrderClasses][4 ceil(T / 8)]: 4 tile + quadrant
   // saved fragments (workspace sized with RTGS_FWD_SAVE_FRAGMENTS, else absent)
   uint64_t fmask;       // uint64[4 cap]: blend mask of each (list entry, wave)
   uint64_t fcount;      // uint32[4 T]: saved fragments of each (tile, wave)
@@ -188,12 +191,14 @@ struct WsPtrs {
   unsigned long long* keys;
   unsigned long long* keys_tm;
   uint32_t* ids;
-  uint8_t* qmask;
+  unsigned long long* hits;
   float* partial;
   uint8_t* live;
   float* state_t;
   int32_t* state_last;
   uint8_t* lane_perm;
+  uint32_t* order_n;
+  uint32_t* order;             // null: the forward files nothing
   unsigned long long* fmask;   // null without saved fragments
   uint32_t* fcount;
   float2* fdata;
