@@ -144,7 +144,7 @@ WsLayout make_layout(const Counts& c, int64_t cap, bool frags) {
   L.win_off = take(4 * (uint64_t)(c.c_total + 1));
   L.vlist = take(8 * (uint64_t)c.c_total * (kChunk + 1));
   L.window = take(16 * windows);
-  L.edge = take(80 * windows);
+  L.edge = take(160 * windows);
   L.hist = take(4 * (uint64_t)c.h_total);
   L.gsum = take(4 * 16 * t);
   L.tile_count = take(4 * (t + 1));
@@ -194,7 +194,7 @@ WsPtrs ws_ptrs(void* ws, const WsLayout& L) {
   w.win_off = reinterpret_cast<uint32_t*>(base + L.win_off);
   w.vlist = reinterpret_cast<uint2*>(base + L.vlist);
   w.window = reinterpret_cast<uint4*>(base + L.window);
-  w.edge = reinterpret_cast<float*>(base + L.edge);
+  w.edge = reinterpret_cast<double*>(base + L.edge);
   w.hist = reinterpret_cast<uint32_t*>(base + L.hist);
   w.gsum = reinterpret_cast<uint32_t*>(base + L.gsum);
   w.tile_count = reinterpret_cast<uint32_t*>(base + L.tile_count);

@@ -74,41 +74,50 @@ __device__ __forceinline__ uint32_t live_bits(uint32_t f) {
 }
 
 // acc += the sums of items lo + lane, lo + lane + LANES, ... below hi of the
-// list, U loads in flight; src: the window's first slot.
-template <int NV, int LANES, int U>
+// list, two in flight; src: the window's first slot.
+template <int NV, int LANES>
 __device__ __forceinline__ void add_items(const float2* src, const uint16_t* list, int lo, int hi,
                                           int lane, float (&acc)[NV]) {
-  for (int i0 = lo + lane; i0 < hi; i0 += U * LANES) {
-    float2 v[U][NV / 2];
+  for (int i0 = lo + lane; i0 < hi; i0 += 2 * LANES) {
+    const bool two = i0 + LANES < hi;
+    const int a = (int)list[i0], b = two ? (int)list[i0 + LANES] : a;
+    float2 v[NV / 2], w[NV / 2];
+    // NV floats at an 8-byte aligned offset: NV / 2 8-byte loads
 #pragma unroll
-    for (int j = 0; j < U; ++j) {
-      // NV floats at an 8-byte aligned offset: NV / 2 8-byte loads
-      const bool on = i0 + j * LANES < hi;
-      const int item = on ? (int)list[i0 + j * LANES] : 0;
-#pragma unroll
-      for (int i = 0; i < NV / 2; ++i)
-        v[j][i] = on ? src[item * (NV / 2) + i] : make_float2(0.f, 0.f);
+    for (int i = 0; i < NV / 2; ++i) {
+      v[i] = src[a * (NV / 2) + i];
+      w[i] = src[b * (NV / 2) + i];
     }
 #pragma unroll
-    for (int j = 0; j < U; ++j)
-#pragma unroll
-      for (int i = 0; i < NV / 2; ++i) {
-        acc[2 * i] += v[j][i].x;
-        acc[2 * i + 1] += v[j][i].y;
-      }
+    for (int i = 0; i < NV / 2; ++i) {
+      acc[2 * i] += v[i].x;
+      acc[2 * i + 1] += v[i].y;
+      acc[2 * i] += two ? w[i].x : 0.f;
+      acc[2 * i + 1] += two ? w[i].y : 0.f;
+    }
   }
 }
 
-// Where the sums over window w (pairs [p0, p1)) of the Gaussian with pairs
-// [first, last) go: grad2d, or the window's edge it crosses (see edge_sum).
-__device__ __forceinline__ float* merge_dst(const WsPtrs& W, int w, uint32_t p0, uint32_t p1,
-                                            uint32_t gid, uint32_t first, uint32_t last) {
-  if (first >= p0 && last <= p1) return W.grad2d + (int64_t)gid * 10;
-  return W.edge + ((int64_t)w * 2 + (first < p0 ? 0 : 1)) * 10;
+// Stores the sums over window w (pairs [p0, p1)) of the Gaussian with pairs
+// [first, last): to grad2d, or to the window's edge it crosses (see
+// merged_sums; in double, as what many windows' sums add up to may cancel).
+template <int NV>
+__device__ __forceinline__ void merge_store(const WsPtrs& W, int w, uint32_t p0, uint32_t p1,
+                                            uint32_t gid, uint32_t first, uint32_t last,
+                                            const float (&acc)[NV]) {
+  if (first >= p0 && last <= p1) {
+    float* o = W.grad2d + (int64_t)gid * 10;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) o[i] = acc[i];
+  } else {
+    double* o = W.edge + ((int64_t)w * 2 + (first < p0 ? 0 : 1)) * 10;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) o[i] = (double)acc[i];
+  }
 }
 
 template <int NV>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7)))
 void k_merge(Batch B, WsPtrs W) {
   static_assert(kWindow == 512, "two pairs a thread");
   __shared__ uint16_t s_item[4 * kWindow];            // 4 pair + quadrant, in order
@@ -176,13 +185,9 @@ void k_merge(Batch B, WsPtrs W) {
       float acc[NV];
 #pragma unroll
       for (int i = 0; i < NV; ++i) acc[i] = 0.f;
-      add_items<NV, 8, 2>(src, s_item, lo, hi, sub, acc);
+      add_items<NV, 8>(src, s_item, lo, hi, sub, acc);
       row_sums<8, NV>(acc);
-      if (mine && sub == 7) {
-        float* o = merge_dst(W, w, p0, p1, g.x, g.y, last);
-#pragma unroll
-        for (int i = 0; i < NV; ++i) o[i] = acc[i];
-      }
+      if (mine && sub == 7) merge_store<NV>(W, w, p0, p1, g.x, g.y, last, acc);
     }
     __syncthreads();
     // the list's order depends on timing; each Gaussian's sum does not
@@ -195,18 +200,14 @@ void k_merge(Batch B, WsPtrs W) {
       float acc[NV];
 #pragma unroll
       for (int i = 0; i < NV; ++i) acc[i] = 0.f;
-      add_items<NV, 64, 2>(src, s_item, lo, hi, lane, acc);
+      add_items<NV, 64>(src, s_item, lo, hi, lane, acc);
       row_sums<16, NV>(acc);
       // the four rows' totals in order
 #pragma unroll
       for (int i = 0; i < NV; ++i)
         acc[i] = ((__shfl(acc[i], 15) + __shfl(acc[i], 31)) + __shfl(acc[i], 47)) +
                  __shfl(acc[i], 63);
-      if (lane == 0) {
-        float* o = merge_dst(W, w, p0, p1, g.x, g.y, last);
-#pragma unroll
-        for (int i = 0; i < NV; ++i) o[i] = acc[i];
-      }
+      if (lane == 0) merge_store<NV>(W, w, p0, p1, g.x, g.y, last, acc);
     }
     __syncthreads();                                  // the LDS lists are reused
   }
@@ -217,18 +218,21 @@ void k_merge(Batch B, WsPtrs W) {
 // each following one).  c: its chunk; [first, last): its pairs.
 template <int NV>
 __device__ __forceinline__ void merged_sums(const WsPtrs& W, int c, int64_t gid, uint32_t first,
-                                            uint32_t n, float (&m)[NV]) {
+                                            uint32_t n, double (&m)[NV]) {
   const uint32_t c0 = W.chunk_off[c];
   const int w0 = (int)(W.win_off[c] + (first - c0) / kWindow);
   const int w1 = (int)(W.win_off[c] + (first + n - 1 - c0) / kWindow);
-  const float* p = w0 == w1 ? W.grad2d + gid * 10 : W.edge + ((int64_t)w0 * 2 + 1) * 10;
+  if (w0 == w1) {
+    const float* p = W.grad2d + gid * 10;
 #pragma unroll
-  for (int i = 0; i < NV; ++i) m[i] = p[i];
-  for (int w = w0 + 1; w <= w1; ++w) {
-    p = W.edge + (int64_t)w * 2 * 10;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) m[i] += p[i];
+    for (int i = 0; i < NV; ++i) m[i] = p[i];
+    return;
   }
+#pragma unroll
+  for (int i = 0; i < NV; ++i) m[i] = W.edge[((int64_t)w0 * 2 + 1) * 10 + i];
+  for (int w = w0 + 1; w <= w1; ++w)
+#pragma unroll
+    for (int i = 0; i < NV; ++i) m[i] += W.edge[(int64_t)w * 2 * 10 + i];
 }
 
 template <int NV, bool ADAM, bool ONE>
@@ -254,9 +258,9 @@ __global__ __launch_bounds__(kGaussPerBlock) void k_gauss_bwd(Batch B, WsPtrs W,
     if (rect.z >= rect.x) {
       // the Gaussian's sums of the raster backward; pose only: without those
       // of the opacity and the colours
-      float g2[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+      double g2[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
       if (W.counters[0] <= W.cap) {       // no pairs have sums after an overflow
-        float m[NV];
+        double m[NV];
         merged_sums<NV>(W, S.chunk_base + li0 / kChunk, gid, W.goff[gid],
                         (uint32_t)((rect.z - rect.x + 1) * (rect.w - rect.y + 1)), m);
         if (NV == 10) {
@@ -385,7 +389,7 @@ __global__ __launch_bounds__(kGaussPerBlock) void k_gauss_bwd(Batch B, WsPtrs W,
         gq[1] = (gx4 - a * dot) * iqn;
         gq[2] = (gy4 - b * dot) * iqn;
         gq[3] = (gz4 - c * dot) * iqn;
-        go_eta = -(double)g2[5] * (1.0 - o);       // dL/do = -(sum of n) / o
+        go_eta = -g2[5] * (1.0 - o);       // dL/do = -(sum of n) / o
         if (want_cov) {
           // dL/dSigma = T^T G' T
           double GT0[3], GT1[3];

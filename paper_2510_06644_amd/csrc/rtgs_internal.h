@@ -110,7 +110,7 @@ struct WsLayout {
   uint64_t vlist;       // uint2[C][kChunk + 1]: (Gaussian, first pair) of a chunk's Gaussians
                         // with pairs, in order; then (0, the chunk's end)
   uint64_t window;      // uint4[cap / kWindow + C]: a window's pairs [x, y), vlist entries [z, w]
-  uint64_t edge;        // float[windows][2][10]: sums of Gaussians crossing a window's ends
+  uint64_t edge;        // double[windows][2][10]: sums of Gaussians crossing a window's ends
   uint64_t hist;        // uint32[sum_s C_s T_s]: per (chunk, tile) counts, then each
                         // chunk's exclusive scan over its tiles (run offsets in the chunk)
   uint64_t gsum;        // uint32[16][T]: per (group of chunks, tile) sums
@@ -182,7 +182,7 @@ struct WsPtrs {
   uint32_t* win_off;
   uint2* vlist;
   uint4* window;
-  float* edge;
+  double* edge;
   uint32_t* hist;
   uint32_t* gsum;
   uint32_t* tile_count;
