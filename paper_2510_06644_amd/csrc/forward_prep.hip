@@ -15,9 +15,7 @@
 //    and writes them as one contiguous block (chunk-major: every store is
 //    coalesced, where scattering 8-byte keys into the tile ranges made the
 //    memory system merge millions of partial lines).  One workgroup per tile
-//    then gathers the tile's run from every chunk and sorts it in LDS (merge
-//    sort of 64-bit keys; long lists are gathered to global memory and go to
-//    a second kernel with 1024 threads, sorting in place beyond its LDS).
+//    then gathers the tile's run from every chunk and sorts it (tile_sort.hip).
 //    The same pass writes each Gaussian's first slot in Gaussian-major pair
 //    order, which the backward uses to merge gradients without atomics.  No
 //    host sync: the pair total stays on the device, and a capacity overflow
@@ -629,328 +627,6 @@ __global__ __launch_bounds__(kBinThreads) void k_emit(Batch B, WsPtrs W) {
   }
 }
 
-// Bitonic sorting network on a[0..n) (ascending), all merges in the "flip"
-// form so that virtual +inf padding up to the next power of two never moves:
-// each compare-exchange puts the minimum at the lower index, hence a pair
-// whose upper index is >= n is left alone.
-template <typename P>
-__device__ void bitonic_sort(P a, int n) {
-  int npow = 1;
-  while (npow < n) npow <<= 1;
-  const int half = npow >> 1;
-  for (int k = 2; k <= npow; k <<= 1) {
-    const int hk = k >> 1;
-    for (int p = threadIdx.x; p < half; p += blockDim.x) {
-      const int r = p & (hk - 1);
-      const int i = (p / hk) * k + r;
-      const int j = i + k - 1 - 2 * r;
-      if (j < n) {
-        const unsigned long long x = a[i], y = a[j];
-        if (y < x) { a[i] = y; a[j] = x; }
-      }
-    }
-    __threadfence_block();
-    __syncthreads();
-    for (int m = k >> 2; m >= 1; m >>= 1) {
-      for (int p = threadIdx.x; p < half; p += blockDim.x) {
-        const int i = (p / m) * 2 * m + (p & (m - 1));
-        const int j = i + m;
-        if (j < n) {
-          const unsigned long long x = a[i], y = a[j];
-          if (y < x) { a[i] = y; a[j] = x; }
-        }
-      }
-      __threadfence_block();
-      __syncthreads();
-    }
-  }
-}
-
-// Merge sort of one tile's 64-bit keys: the list is padded to N keys (a power
-// of two, n <= N <= K NT) with all-ones keys, which no real key equals since
-// depth bits of a finite float are below 0x7f800000.  The first N / K threads
-// each sort K keys in registers, then log2(N / K) merge levels run through two
-// LDS buffers: a thread finds where its K outputs start on the merge path of
-// its pair of runs by binary search and merges K keys.  One barrier per level
-// (all NT threads take it), instead of one per bitonic stage.
-constexpr unsigned long long kKeyPad = ~0ull;
-constexpr int kSortPerThread = 4;
-
-__device__ __forceinline__ void cas(unsigned long long& a, unsigned long long& b) {
-  const unsigned long long lo = a < b ? a : b, hi = a < b ? b : a;
-  a = lo;
-  b = hi;
-}
-
-// Sorting networks: 5 comparators for 4 keys, Batcher's 19 for 8.
-__device__ __forceinline__ void sort_network(unsigned long long (&k)[4]) {
-  cas(k[0], k[1]); cas(k[2], k[3]);
-  cas(k[0], k[2]); cas(k[1], k[3]);
-  cas(k[1], k[2]);
-}
-__device__ __forceinline__ void sort_network(unsigned long long (&k)[8]) {
-  cas(k[0], k[1]); cas(k[2], k[3]); cas(k[4], k[5]); cas(k[6], k[7]);
-  cas(k[0], k[2]); cas(k[1], k[3]); cas(k[4], k[6]); cas(k[5], k[7]);
-  cas(k[1], k[2]); cas(k[5], k[6]);
-  cas(k[0], k[4]); cas(k[1], k[5]); cas(k[2], k[6]); cas(k[3], k[7]);
-  cas(k[2], k[4]); cas(k[3], k[5]);
-  cas(k[1], k[2]); cas(k[3], k[4]); cas(k[5], k[6]);
-}
-
-// Smallest power of two >= max(n, lo).
-__device__ __forceinline__ int pow2_at_least(int n, int lo) {
-  int p = lo;
-  while (p < n) p <<= 1;
-  return p;
-}
-
-// LDS position of key e of a sort buffer: one spare key after every eight, so
-// that the threads' runs of K = 4 keys (32 bytes apart) fall on different
-// banks instead of the same few (at most 2-way conflicts for 64-bit accesses).
-__device__ __forceinline__ int sp(int e) { return e + (e >> 3); }
-
-// Keys a sort buffer of n keys holds with the spare ones.
-constexpr int sort_buf_keys(int n) { return n + n / 8; }
-
-// KEYS_OUT: write the sorted keys back to keys_out instead of their ids.
-// PAD_IN: `keys` is a sort buffer in LDS (positions by sp), else plain memory.
-template <int NT, int K, bool KEYS_OUT = false, bool PAD_IN = false>
-__device__ void merge_sort_tile(const unsigned long long* keys, uint32_t* ids, int n,
-                                unsigned long long* buf0, unsigned long long* buf1,
-                                unsigned long long* keys_out = nullptr) {
-  const int N = pow2_at_least(n, K);
-  const int t = threadIdx.x;
-  const bool act = K * t < N;
-  if (act) {
-    unsigned long long k[K];
-#pragma unroll
-    for (int s = 0; s < K; ++s) {
-      const int e = K * t + s;
-      k[s] = e < n ? keys[PAD_IN ? sp(e) : e] : kKeyPad;
-    }
-    sort_network(k);
-#pragma unroll
-    for (int s = 0; s < K; ++s) buf0[sp(K * t + s)] = k[s];
-  }
-  __syncthreads();
-  unsigned long long* src = buf0;
-  unsigned long long* dst = buf1;
-  for (int L = K; L < N; L <<= 1) {
-    if (act) {
-      const int pos = K * t;
-      const int base = pos & ~(2 * L - 1);
-      const int r = pos - base;
-      const int a0 = base, b0 = base + L;     // the two runs being merged
-      // number of A keys among the first r outputs (ties: A first)
-      int lo = r > L ? r - L : 0, hi = r < L ? r : L;
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (src[sp(a0 + mid)] <= src[sp(b0 + r - 1 - mid)]) lo = mid + 1;
-        else hi = mid;
-      }
-      int i = lo, j = r - lo;
-      unsigned long long x = i < L ? src[sp(a0 + i)] : kKeyPad;
-      unsigned long long y = j < L ? src[sp(b0 + j)] : kKeyPad;
-      // an exhausted run reads as all-ones keys, so one compare decides: past
-      // the end of B, x <= y holds; past the end of A, it holds only if y is
-      // padding too, and then either choice writes the same all-ones key
-#pragma unroll
-      for (int s = 0; s < K; ++s) {
-        const bool take_a = x <= y;
-        dst[sp(pos + s)] = take_a ? x : y;
-        if (take_a) {
-          ++i;
-          x = i < L ? src[sp(a0 + i)] : kKeyPad;
-        } else {
-          ++j;
-          y = j < L ? src[sp(b0 + j)] : kKeyPad;
-        }
-      }
-    }
-    __syncthreads();
-    unsigned long long* tmp = src;
-    src = dst;
-    dst = tmp;
-  }
-  for (int i = t; i < n; i += NT) {
-    if (KEYS_OUT)
-      keys_out[i] = src[sp(i)];
-    else
-      ids[i] = (uint32_t)src[sp(i)];
-  }
-}
-
-// The ids of the merge of two sorted key runs A[0..na) and B[0..nb) (global
-// memory), each thread writing a contiguous share of the outputs after a
-// merge-path search for its start (ties: A first).
-__device__ void merge_runs_to_ids(const unsigned long long* A, int na,
-                                  const unsigned long long* Bv, int nb, uint32_t* ids) {
-  const int n = na + nb;
-  const int per = (n + (int)blockDim.x - 1) / (int)blockDim.x;
-  const int r = min((int)threadIdx.x * per, n), r1 = min(r + per, n);
-  if (r >= r1) return;
-  int lo = max(0, r - nb), hi = min(r, na);       // A keys among the first r outputs
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (A[mid] <= Bv[r - 1 - mid]) lo = mid + 1;
-    else hi = mid;
-  }
-  int i = lo, j = r - lo;
-  for (int o = r; o < r1; ++o) {
-    const bool take_a = j >= nb || (i < na && A[i] <= Bv[j]);
-    ids[o] = (uint32_t)(take_a ? A[i++] : Bv[j++]);
-  }
-}
-
-// The tile's list is the concatenation of its run in every chunk of its
-// session (chunk-major keys, run offsets in the chunks' histogram rows).
-// First each run's source and place in the list (a thread per chunk, a block
-// scan of the run lengths, both kept in LDS for up to kGatherChunks chunks);
-// then the n keys dealt evenly over the threads, each finding the run of its
-// first key by binary search and issuing its loads together.  Sessions with
-// more chunks copy run by run.
-constexpr int kGatherChunks = 1020;    // s_at and s_src fit in one sort buffer
-
-template <bool PAD>
-__device__ void gather_tile(const WsPtrs& W, const SessionDev& S, int lt, int n,
-                            unsigned long long* dst, uint32_t* s_part, uint32_t* s_at,
-                            uint32_t* s_src) {
-  const int ts = S.tiles_x * S.tiles_y;
-  const int nc = (S.n + kChunk - 1) / kChunk;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const bool spread = nc <= kGatherChunks;
-  uint32_t carry = 0;
-  for (int c0 = 0; c0 < nc; c0 += kBlock) {
-    const int c = c0 + (int)threadIdx.x;
-    uint32_t cnt = 0, src = 0;
-    if (c < nc) {
-      const uint32_t* row = W.hist + S.hist_base + (int64_t)c * ts;
-      const uint32_t off = row[lt];
-      const uint32_t nxt = lt + 1 < ts ? row[lt + 1] : W.chunk_total[S.chunk_base + c];
-      cnt = nxt - off;
-      src = W.chunk_off[S.chunk_base + c] + off;
-    }
-    uint32_t x = cnt;
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t y = __shfl_up(x, o, 64);
-      if (lane >= o) x += y;
-    }
-    if (lane == 63) s_part[wave] = x;
-    __syncthreads();
-    uint32_t at = carry + x - cnt, tot = 0;
-    for (int q = 0; q < kBlock / 64; ++q) {
-      at += q < wave ? s_part[q] : 0u;
-      tot += s_part[q];
-    }
-    if (spread) {
-      if (c < nc) {
-        s_at[c] = at;
-        s_src[c] = src;
-      }
-    } else {
-      for (uint32_t j = 0; j < cnt; ++j) dst[PAD ? sp(at + j) : at + j] = W.keys[src + j];
-    }
-    carry += tot;
-    __syncthreads();                        // s_part is reused
-  }
-  if (!spread) return;
-  if (threadIdx.x == 0) s_at[nc] = (uint32_t)n;
-  __syncthreads();
-  const int per = (n + kBlock - 1) / kBlock;
-  const int p0 = min((int)threadIdx.x * per, n), p1 = min(p0 + per, n);
-  if (p0 >= p1) return;
-  int lo = 0, hi = nc - 1;                  // last run with s_at <= p0
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (s_at[mid] <= (uint32_t)p0) lo = mid; else hi = mid - 1;
-  }
-  int c = lo;
-  for (int q0 = p0; q0 < p1; q0 += 4) {
-    unsigned long long k[4];
-    int qn = min(4, p1 - q0);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (j < qn) {
-        const uint32_t p = (uint32_t)(q0 + j);
-        while (p >= s_at[c + 1]) ++c;       // runs are contiguous in the list
-        k[j] = W.keys[s_src[c] + (p - s_at[c])];
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (j < qn) dst[PAD ? sp(q0 + j) : q0 + j] = k[j];
-  }
-}
-
-// One workgroup per tile (neighbouring tiles on one XCD, whose L2 then holds
-// the chunk rows and runs they share): lists of up to 1024 keys are gathered
-// to LDS and sorted here; longer ones are gathered to the tile-major buffer
-// and queued for k_sort_big_tiles.
-template <bool ONE>
-__global__ __launch_bounds__(kBlock) void k_sort_tiles(Batch B, WsPtrs W) {
-  __shared__ unsigned long long b0[sort_buf_keys(kSortPerThread * kBlock)];
-  __shared__ unsigned long long b1[sort_buf_keys(kSortPerThread * kBlock)];
-  __shared__ uint32_t s_part[kBlock / 64];
-  // the gather's run table lives in b0, which the merge sort fills only after
-  // it has read the gathered keys from b1
-  static_assert(2 * kGatherChunks + 1 <= 2 * kSortPerThread * kBlock, "run table fits b0");
-  uint32_t* s_at = reinterpret_cast<uint32_t*>(b0);
-  uint32_t* s_src = s_at + kGatherChunks + 1;
-  const int per = (B.t_total + 7) >> 3;
-  const int t = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
-  if (t >= B.t_total) return;
-  const uint32_t st = W.tile_start[t];
-  const int n = (int)(W.tile_start[t + 1] - st);   // all empty after an overflow
-  if (n <= 0) return;
-  const int s = ONE ? 0 : find_session(session_table(B), B.n_sessions, t,
-                                         [](const SessionDev& x) { return x.tile_base; });
-  const SessionDev& S = batch_session<ONE>(B, s);
-  if (n > kSortPerThread * kBlock) {
-    gather_tile<false>(W, S, t - S.tile_base, n, W.keys_tm + st, s_part, s_at, s_src);
-    if (threadIdx.x == 0) {
-      const unsigned long long q = atomicAdd((unsigned long long*)&W.counters[2], 1ull);
-      W.big_tiles[q] = (uint32_t)t;
-    }
-    return;
-  }
-  gather_tile<true>(W, S, t - S.tile_base, n, b1, s_part, s_at, s_src);
-  __syncthreads();
-  merge_sort_tile<kBlock, kSortPerThread, false, true>(b1, W.ids + st, n, b0, b1);
-}
-
-// Queued long lists (gathered to the tile-major buffer): up to 4096 keys by
-// the LDS merge sort with 1024 threads; up to 8192 as two such sorts of
-// halves written back as keys, then one merge of the halves from global
-// memory; longer ones by the bitonic network in place in global memory.  One
-// launch whatever the lengths.
-constexpr int kBigThreads = 1024;
-constexpr int kBigKeys = kSortPerThread * kBigThreads;
-__global__ __launch_bounds__(kBigThreads) void k_sort_big_tiles(WsPtrs W) {
-  __shared__ unsigned long long b0[sort_buf_keys(kBigKeys)], b1[sort_buf_keys(kBigKeys)];
-  const long long count = W.counters[2];
-  for (long long q = blockIdx.x; q < count; q += gridDim.x) {
-    const int t = (int)W.big_tiles[q];
-    const int64_t st = W.tile_start[t];
-    const int n = (int)(W.tile_start[t + 1] - st);
-    unsigned long long* g = W.keys_tm + st;
-    if (n <= kBigKeys) {
-      merge_sort_tile<kBigThreads, kSortPerThread>(g, W.ids + st, n, b0, b1);
-    } else if (n <= 2 * kBigKeys) {
-      merge_sort_tile<kBigThreads, kSortPerThread, true>(g, nullptr, kBigKeys, b0, b1, g);
-      __syncthreads();
-      merge_sort_tile<kBigThreads, kSortPerThread, true>(g + kBigKeys, nullptr, n - kBigKeys, b0,
-                                                          b1, g + kBigKeys);
-      __threadfence_block();
-      __syncthreads();
-      merge_runs_to_ids(g, kBigKeys, g + kBigKeys, n - kBigKeys, W.ids + st);
-    } else {
-      bitonic_sort(g, n);
-      for (int i = threadIdx.x; i < n; i += blockDim.x) W.ids[st + i] = (uint32_t)g[i];
-    }
-    __syncthreads();
-  }
-}
-
 __global__ void k_debug_stage(Batch B, WsPtrs W, float* stage, int* rect, int* ranges, int* ids,
                               int64_t ids_cap) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1053,11 +729,7 @@ hipError_t launch_forward_prep(const Batch& b, const WsPtrs& w, unsigned long lo
   }
   if (b.t_total > 0) {
     Scope sc(tm, kStSort, st);
-    if (one)
-      k_sort_tiles<true><<<8 * ((b.t_total + 7) / 8), kBlock, 0, st>>>(b, w);
-    else
-      k_sort_tiles<false><<<8 * ((b.t_total + 7) / 8), kBlock, 0, st>>>(b, w);
-    k_sort_big_tiles<<<b.t_total < 512 ? b.t_total : 512, kBigThreads, 0, st>>>(w);
+    launch_tile_sort(b, w, st);
   }
   return hipGetLastError();
 }

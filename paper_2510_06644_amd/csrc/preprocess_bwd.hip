@@ -75,9 +75,9 @@ __device__ __forceinline__ uint32_t live_bits(uint32_t f) {
 
 // acc += the sums of items lo + lane, lo + lane + LANES, ... below hi of the
 // list, two in flight; src: the window's first slot.
-template <int NV, int LANES>
+template <int NV, int LANES, typename Acc>
 __device__ __forceinline__ void add_items(const float2* src, const uint16_t* list, int lo, int hi,
-                                          int lane, float (&acc)[NV]) {
+                                          int lane, Acc (&acc)[NV]) {
   for (int i0 = lo + lane; i0 < hi; i0 += 2 * LANES) {
     const bool two = i0 + LANES < hi;
     const int a = (int)list[i0], b = two ? (int)list[i0 + LANES] : a;
@@ -98,22 +98,66 @@ __device__ __forceinline__ void add_items(const float2* src, const uint16_t* lis
   }
 }
 
-// Stores the sums over window w (pairs [p0, p1)) of the Gaussian with pairs
+// a + b of a pair of doubles after swapping halves (32) or rows (16) of lanes,
+// as swap32_add and swap16_add do for floats.
+template <int LANES>
+__device__ __forceinline__ double swap_add(double a, double b) {
+  const unsigned long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+  const unsigned xl = (unsigned)x, xh = (unsigned)(x >> 32);
+  const unsigned yl = (unsigned)y, yh = (unsigned)(y >> 32);
+  unsigned l0, l1, h0, h1;
+  if (LANES == 32) {
+    const auto l = __builtin_amdgcn_permlane32_swap(xl, yl, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(xh, yh, false, false);
+    l0 = l[0]; l1 = l[1]; h0 = h[0]; h1 = h[1];
+  } else {
+    const auto l = __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
+    l0 = l[0]; l1 = l[1]; h0 = h[0]; h1 = h[1];
+  }
+  return __longlong_as_double(((unsigned long long)h0 << 32) | l0) +
+         __longlong_as_double(((unsigned long long)h1 << 32) | l1);
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+  const unsigned long long x = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)x, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(x >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+
+// Wavefront reduce-scatter of NV doubles (NV / 2 odd): halves, then rows, then
+// along the rows.  Lane 16 (2 h + p) + 15 ends with the totals of values
+// h NV / 2 + p + 2 j in x[j] for j < NV / 4, of h NV / 2 + NV / 2 - 1 in x[NV / 4].
+template <int NV>
+__device__ __forceinline__ void wave_sums(const double (&v)[NV], double (&x)[(NV / 2 + 1) / 2]) {
+  constexpr int H = NV / 2;
+  double w[H];
+#pragma unroll
+  for (int i = 0; i < H; ++i) w[i] = swap_add<32>(v[i], v[i + H]);
+#pragma unroll
+  for (int j = 0; j < (H + 1) / 2; ++j) {
+    double s = swap_add<16>(w[2 * j], w[2 * j + 1 < H ? 2 * j + 1 : 2 * j]);
+    s += dpp_d<kDppRowShr1>(s);
+    s += dpp_d<kDppRowShr2>(s);
+    s += dpp_d<kDppRowShr4>(s);
+    s += dpp_d<kDppRowShr8>(s);
+    x[j] = s;
+  }
+}
+
+// Stores sum i over window w (pairs [p0, p1)) of the Gaussian with pairs
 // [first, last): to grad2d, or to the window's edge it crosses (see
 // merged_sums; in double, as what many windows' sums add up to may cancel).
-template <int NV>
+template <typename Acc>
 __device__ __forceinline__ void merge_store(const WsPtrs& W, int w, uint32_t p0, uint32_t p1,
-                                            uint32_t gid, uint32_t first, uint32_t last,
-                                            const float (&acc)[NV]) {
-  if (first >= p0 && last <= p1) {
-    float* o = W.grad2d + (int64_t)gid * 10;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) o[i] = acc[i];
-  } else {
-    double* o = W.edge + ((int64_t)w * 2 + (first < p0 ? 0 : 1)) * 10;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) o[i] = (double)acc[i];
-  }
+                                            uint32_t gid, uint32_t first, uint32_t last, int i,
+                                            Acc v) {
+  if (first >= p0 && last <= p1)
+    W.grad2d[(int64_t)gid * 10 + i] = (float)v;
+  else
+    W.edge[((int64_t)w * 2 + (first < p0 ? 0 : 1)) * 10 + i] = (double)v;
 }
 
 template <int NV>
@@ -187,7 +231,9 @@ void k_merge(Batch B, WsPtrs W) {
       for (int i = 0; i < NV; ++i) acc[i] = 0.f;
       add_items<NV, 8>(src, s_item, lo, hi, sub, acc);
       row_sums<8, NV>(acc);
-      if (mine && sub == 7) merge_store<NV>(W, w, p0, p1, g.x, g.y, last, acc);
+      if (mine && sub == 7)
+#pragma unroll
+        for (int i = 0; i < NV; ++i) merge_store(W, w, p0, p1, g.x, g.y, last, i, acc[i]);
     }
     __syncthreads();
     // the list's order depends on timing; each Gaussian's sum does not
@@ -197,17 +243,19 @@ void k_merge(Batch B, WsPtrs W) {
       const uint2 g = W.vlist[e];
       const uint32_t last = W.vlist[e + 1].y;
       const int lo = s_cum[g.y > p0 ? g.y - p0 : 0u], hi = s_cum[min(last - p0, (uint32_t)kWindow)];
-      float acc[NV];
+      // (in double: a float's error would grow with the number of items)
+      double acc[NV], x[(NV / 2 + 1) / 2];
 #pragma unroll
-      for (int i = 0; i < NV; ++i) acc[i] = 0.f;
+      for (int i = 0; i < NV; ++i) acc[i] = 0.0;
       add_items<NV, 64>(src, s_item, lo, hi, lane, acc);
-      row_sums<16, NV>(acc);
-      // the four rows' totals in order
+      wave_sums<NV>(acc, x);
+      if ((lane & 15) == 15) {
+        const int odd = (lane >> 4) & 1, v0 = (lane >> 5) * (NV / 2);
 #pragma unroll
-      for (int i = 0; i < NV; ++i)
-        acc[i] = ((__shfl(acc[i], 15) + __shfl(acc[i], 31)) + __shfl(acc[i], 47)) +
-                 __shfl(acc[i], 63);
-      if (lane == 0) merge_store<NV>(W, w, p0, p1, g.x, g.y, last, acc);
+        for (int j = 0; j < NV / 4; ++j)
+          merge_store(W, w, p0, p1, g.x, g.y, last, v0 + odd + 2 * j, x[j]);
+        if (!odd) merge_store(W, w, p0, p1, g.x, g.y, last, v0 + NV / 2 - 1, x[NV / 4]);
+      }
     }
     __syncthreads();                                  // the LDS lists are reused
   }

@@ -249,6 +249,7 @@ struct Scope {
 // ---- launch wrappers (defined in the .hip files) ----
 hipError_t launch_forward_prep(const Batch& b, const WsPtrs& w, unsigned long long* max_pairs,
                                bool reuse_lists, hipStream_t st, StageTimer* tm);
+void launch_tile_sort(const Batch& b, const WsPtrs& w, hipStream_t st);
 hipError_t launch_raster_fwd(const Batch& b, const WsPtrs& w, bool stats, bool frags, bool bal,
                              hipStream_t st, StageTimer* tm);
 hipError_t launch_raster_bwd(const Batch& b, const WsPtrs& w, int pose_only, bool alpha_grad,
