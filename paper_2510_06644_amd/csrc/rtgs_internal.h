@@ -332,7 +332,7 @@ struct PoseArgs {
 hipError_t launch_pose_update(const PoseArgs& a, hipStream_t st);
 constexpr int kAdamPerThread = 4;
 
-constexpr int kPruneScratchWords = 4096;
+constexpr int kPruneScratchWords = 16384;
 
 // Stable compaction of per-Gaussian arrays by a drop mask (the permanent
 // removal of the mask-prune schedule).

@@ -3,10 +3,21 @@
 // prune_by_grad (Sec. 4.1, Eq. 7): importance = ||dL/dmu|| + lambda ||dL/dSigma||_F
 // per Gaussian (float64, rounded to float32), then the floor(ratio V) lowest
 // (score, index) among visible, unmasked Gaussians join the mask.  The k-th
-// smallest score is found by a 4-pass 8-bit radix select over the float bits
-// (scores are >= 0, so bit order is value order), ties at the threshold go to
-// the lowest indices through a block scan.  Everything stays on the device;
-// a 16 KB scratch owned by the handle holds histograms and block counts.
+// smallest score is found by a radix select over the float bits (scores are
+// >= 0, so bit order is value order) in three passes of 11, 11 and 10 bits,
+// ties at the threshold go to the lowest indices through per-block counts.
+// Everything stays on the device; a 64 KB scratch owned by the handle holds
+// histograms and block counts.
+//
+// Five streaming passes over 36 bytes per Gaussian, each a launch of its own
+// (every pass needs the totals of the one before); what a pass derives from
+// those totals (digit, rank, offsets) each of its blocks works out for itself,
+// so no single-block launches stand between them.  Most scores of a tracking
+// iteration are exactly zero: a wave adds the count of its first lane's bin
+// at once instead of lane by lane; 256 histogram blocks rather than 1024, whose
+// additions to the same bins queue up (23 us a pass instead of 8.8).  500k
+// Gaussians: four 8-bit passes with a single-block pick after each and a serial
+// scan of the block counts, 14 launches, 150 us -> 6 launches, 50 us.
 //
 // downsample_mask (Sec. 4.2): one thread per block of 2^ceil(j/2) x
 // 2^floor(j/2) pixels keeps the pixel with the lowest previous final T.
@@ -15,11 +26,17 @@
 namespace rtgs {
 namespace {
 
-constexpr int kHist = 0;          // 256 bins
-constexpr int kState = 256;       // [0] V, [1] k, [2] prefix, [3] rank, [4] done flag
-constexpr int kBlockCnt = 512;    // per-block equal counts (exclusive prefix after scan)
-constexpr int kSelBlocks = 2048;  // max blocks of the final passes
+constexpr int kBins = 2048;            // bins of a pass
+constexpr int kHist = 0;               // three histograms
+constexpr int kBlockCnt = 3 * kBins;   // per-block counts of threshold keys
+constexpr int kSelBlocks = 2048;       // max blocks of the final passes
 constexpr int kSelThreads = 1024;
+constexpr int kHistThreads = 1024;
+static_assert(kBlockCnt + kSelBlocks <= kPruneScratchWords, "scratch holds the counts");
+
+// Digit of pass p (0: the top 11 bits, 1: the next 11, 2: the last 10).
+constexpr int pass_shift(int p) { return p == 0 ? 21 : p == 1 ? 10 : 0; }
+constexpr uint32_t pass_mask(int p) { return p == 2 ? 1023u : 2047u; }
 
 __device__ __forceinline__ bool candidate(const uint8_t* vis, const uint8_t* mask, int i) {
   return (vis == nullptr || vis[i] != 0) && (mask == nullptr || mask[i] == 0);
@@ -34,70 +51,116 @@ __device__ __forceinline__ uint32_t score_bits(const float* gm, const float* gc,
   return __float_as_uint(s);
 }
 
-__global__ void k_prune_init(uint32_t* scr) {
-  const int i = threadIdx.x;
-  if (i < 256) scr[kHist + i] = 0;
-  if (i < 8) scr[kState + i] = 0;
+__global__ __launch_bounds__(kHistThreads) void k_prune_init(uint32_t* scr, int* n_masked) {
+  const int i = blockIdx.x * kHistThreads + threadIdx.x;
+  if (i < 3 * kBins) scr[kHist + i] = 0;
+  if (i == 0 && n_masked) *n_masked = 0;
 }
 
-__global__ void k_prune_count(const uint8_t* vis, const uint8_t* mask, int n, uint32_t* scr) {
-  __shared__ uint32_t c;
-  if (threadIdx.x == 0) c = 0;
+// The digit of a pass's histogram that holds rank `rank` (1-based, at most the
+// total), and the rank inside it, by the block's NT threads.  s: NT / 64 + 2
+// words of LDS.  Returns the total in `total`.
+template <int NT>
+__device__ __forceinline__ void pick_digit(const uint32_t* hist, uint32_t rank, uint32_t* s,
+                                           uint32_t& digit, uint32_t& inside, uint32_t& total) {
+  constexpr int kPer = kBins / NT;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  uint32_t h[kPer], sum = 0;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    h[i] = hist[tid * kPer + i];
+    sum += h[i];
+  }
+  uint32_t x = sum;
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t y = __shfl_up(x, off, 64);
+    if (lane >= off) x += y;
+  }
+  if (lane == 63) s[wave] = x;
   __syncthreads();
-  uint32_t mine = 0;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-    mine += candidate(vis, mask, i) ? 1u : 0u;
-  atomicAdd(&c, mine);
-  __syncthreads();
-  if (threadIdx.x == 0) atomicAdd(&scr[kState + 0], c);
-}
-
-__global__ void k_prune_setup(uint32_t* scr, float ratio, int* n_masked) {
-  const uint32_t v = scr[kState + 0];
-  const uint32_t k = (uint32_t)floor((double)ratio * (double)v);
-  scr[kState + 1] = k;
-  scr[kState + 2] = 0;     // prefix
-  scr[kState + 3] = k;     // rank still to place (1-based while searching)
-  if (n_masked) *n_masked = (int)k;
-}
-
-// Histogram of the 8-bit digit at `shift` among candidates whose higher bits
-// equal the current prefix.
-__global__ void k_prune_hist(const float* gm, const float* gc, float lam, const uint8_t* vis,
-                             const uint8_t* mask, int n, int shift, uint32_t* scr) {
-  __shared__ uint32_t h[256];
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  const uint32_t prefix = scr[kState + 2];
-  const bool active = scr[kState + 3] > 0;
-  if (active) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-      if (!candidate(vis, mask, i)) continue;
-      const uint32_t key = score_bits(gm, gc, lam, i);
-      const uint32_t hiBits = shift == 24 ? 0u : (key >> (shift + 8));
-      if (hiBits != (shift == 24 ? 0u : prefix)) continue;
-      atomicAdd(&h[(key >> shift) & 255u], 1u);
+  uint32_t before = x - sum;
+  total = 0;
+  for (int q = 0; q < NT / 64; ++q) {
+    before += q < wave ? s[q] : 0u;
+    total += s[q];
+  }
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    if (before < rank && rank <= before + h[i]) {
+      s[NT / 64] = (uint32_t)(tid * kPer + i);
+      s[NT / 64 + 1] = rank - before;
     }
+    before += h[i];
   }
   __syncthreads();
-  if (h[threadIdx.x]) atomicAdd(&scr[kHist + threadIdx.x], h[threadIdx.x]);
+  digit = s[NT / 64];
+  inside = s[NT / 64 + 1];
+  __syncthreads();
 }
 
-// Pick the digit holding the remaining rank; extend the prefix; clear bins.
-__global__ void k_prune_pick(uint32_t* scr) {
-  __shared__ uint32_t h[256];
-  h[threadIdx.x] = scr[kHist + threadIdx.x];
-  scr[kHist + threadIdx.x] = 0;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t r = scr[kState + 3];
-    if (r > 0) {
-      uint32_t d = 0;
-      while (d < 255 && h[d] < r) { r -= h[d]; ++d; }
-      scr[kState + 2] = (scr[kState + 2] << 8) | d;
-      scr[kState + 3] = r;     // rank among keys equal to the final prefix
-    }
+// What `passes` passes have settled: k = floor(ratio V) of the V candidates,
+// the threshold's leading digits, and the rank among the keys that share them.
+struct Select {
+  uint32_t k, prefix, rank;
+};
+
+template <int NT>
+__device__ __forceinline__ Select selected(const uint32_t* scr, float ratio, int passes,
+                                           uint32_t* s) {
+  Select r{0, 0, 0};
+  uint32_t total = 0, d = 0, in = 0;
+  pick_digit<NT>(scr + kHist, 0, s, d, in, total);            // V
+  r.k = (uint32_t)floor((double)ratio * (double)total);
+  r.rank = r.k;
+  if (r.k == 0) return r;
+  for (int p = 0; p < passes; ++p) {
+    pick_digit<NT>(scr + kHist + p * kBins, r.rank, s, d, in, total);
+    r.prefix = (r.prefix << (p == 2 ? 10 : 11)) | d;
+    r.rank = in;
   }
+  return r;
+}
+
+// Histogram of pass PASS's digit among candidates whose higher digits are the
+// threshold's.
+template <int PASS>
+__global__ __launch_bounds__(kHistThreads) void k_prune_hist(const float* gm, const float* gc,
+                                                             float lam, const uint8_t* vis,
+                                                             const uint8_t* mask, int n,
+                                                             float ratio, uint32_t* scr) {
+  __shared__ uint32_t h[kBins];
+  __shared__ uint32_t s[kHistThreads / 64 + 2];
+  for (int i = threadIdx.x; i < kBins; i += kHistThreads) h[i] = 0;
+  Select sel{0, 0, 0};
+  if (PASS > 0) {
+    sel = selected<kHistThreads>(scr, ratio, PASS, s);
+    if (sel.k == 0) return;
+  }
+  __syncthreads();
+  const int stride = gridDim.x * kHistThreads;
+  for (int i0 = blockIdx.x * kHistThreads; i0 < n; i0 += stride) {
+    const int i = i0 + threadIdx.x;
+    bool in = i < n && candidate(vis, mask, i);
+    uint32_t key = 0;
+    if (in) {
+      key = score_bits(gm, gc, lam, i);
+      in = PASS == 0 || (key >> pass_shift(PASS > 0 ? PASS - 1 : 0)) == sel.prefix;
+    }
+    const uint32_t d = (key >> pass_shift(PASS)) & pass_mask(PASS);
+    // the bin of the first lane in one addition, the others one by one
+    const unsigned long long m = __ballot(in);
+    if (m == 0) continue;
+    const int first = __builtin_ctzll(m);
+    const uint32_t d0 = (uint32_t)__shfl((int)d, first);
+    const unsigned long long same = __ballot(in && d == d0);
+    if ((int)(threadIdx.x & 63) == first)
+      atomicAdd(&h[d0], (uint32_t)__popcll(same));
+    else if (in && d != d0)
+      atomicAdd(&h[d], 1u);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < kBins; i += kHistThreads)
+    if (h[i]) atomicAdd(&scr[kHist + PASS * kBins + i], h[i]);
 }
 
 __device__ __forceinline__ int sel_chunk(int n, int nb) {
@@ -109,47 +172,52 @@ __device__ __forceinline__ int sel_chunk(int n, int nb) {
 __global__ __launch_bounds__(kSelThreads) void k_prune_eqcount(const float* gm, const float* gc,
                                                               float lam, const uint8_t* vis,
                                                               const uint8_t* mask, int n, int nb,
-                                                              uint32_t* scr) {
-  __shared__ uint32_t c;
-  if (threadIdx.x == 0) c = 0;
-  __syncthreads();
-  const uint32_t tau = scr[kState + 2];
-  const bool any = scr[kState + 1] > 0;
+                                                              float ratio, uint32_t* scr) {
+  __shared__ uint32_t s[kSelThreads / 64 + 2];
+  const Select sel = selected<kSelThreads>(scr, ratio, 3, s);
   const int chunk = sel_chunk(n, nb);
   const int beg = blockIdx.x * chunk, end = min(n, beg + chunk);
-  uint32_t mine = 0;
-  if (any)
-    for (int i = beg + threadIdx.x; i < end; i += kSelThreads)
-      mine += (candidate(vis, mask, i) && score_bits(gm, gc, lam, i) == tau) ? 1u : 0u;
-  atomicAdd(&c, mine);
-  __syncthreads();
-  if (threadIdx.x == 0) scr[kBlockCnt + blockIdx.x] = c;
-}
-
-__global__ void k_prune_scan(uint32_t* scr, int nb) {
-  if (threadIdx.x == 0) {
-    uint32_t run = 0;
-    for (int b = 0; b < nb; ++b) {
-      const uint32_t c = scr[kBlockCnt + b];
-      scr[kBlockCnt + b] = run;
-      run += c;
+  uint32_t mine = 0;                       // of the wave, in every lane
+  if (sel.k > 0)
+    for (int i0 = beg; i0 < end; i0 += kSelThreads) {
+      const int i = i0 + threadIdx.x;
+      const bool eq = i < end && candidate(vis, mask, i) &&
+                      score_bits(gm, gc, lam, i) == sel.prefix;
+      mine += (uint32_t)__popcll(__ballot(eq));
     }
+  if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = mine;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t t = 0;
+    for (int q = 0; q < kSelThreads / 64; ++q) t += s[q];
+    scr[kBlockCnt + blockIdx.x] = t;
   }
 }
 
 __global__ __launch_bounds__(kSelThreads) void k_prune_final(const float* gm, const float* gc,
                                                             float lam, const uint8_t* vis,
                                                             const uint8_t* mask_in, int n, int nb,
-                                                            uint32_t* scr, uint8_t* mask_out,
+                                                            float ratio, const uint32_t* scr,
+                                                            uint8_t* mask_out, int* n_masked,
                                                             float* score_out) {
+  __shared__ uint32_t s[kSelThreads / 64 + 2];
   __shared__ uint32_t wsum[kSelThreads / 64];
-  const uint32_t tau = scr[kState + 2];
-  const uint32_t take = scr[kState + 3];
-  const bool any = scr[kState + 1] > 0;
+  const Select sel = selected<kSelThreads>(scr, ratio, 3, s);
+  const uint32_t tau = sel.prefix, take = sel.rank;
+  const bool any = sel.k > 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0 && n_masked) *n_masked = (int)sel.k;
   const int chunk = sel_chunk(n, nb);
   const int beg = blockIdx.x * chunk, end = min(n, beg + chunk);
-  uint32_t run = scr[kBlockCnt + blockIdx.x];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // threshold keys in the blocks before this one
+  uint32_t run = 0;
+  for (int b = threadIdx.x; b < (int)blockIdx.x; b += kSelThreads) run += scr[kBlockCnt + b];
+  for (int off = 32; off >= 1; off >>= 1) run += __shfl_xor(run, off);
+  if (lane == 0) wsum[wave] = run;
+  __syncthreads();
+  run = 0;
+  for (int q = 0; q < kSelThreads / 64; ++q) run += wsum[q];
+  __syncthreads();
   for (int base = beg; base < end; base += kSelThreads) {
     const int i = base + threadIdx.x;
     bool cand = false, eq = false, lt = false;
@@ -171,22 +239,20 @@ __global__ __launch_bounds__(kSelThreads) void k_prune_final(const float* gm, co
     for (int q = 0; q < kSelThreads / 64; ++q) tot += wsum[q];
     __syncthreads();
     if (i < end) {
-      const bool sel = any && (lt || (eq && before < take));
+      const bool sel_i = any && (lt || (eq && before < take));
       const bool was = mask_in != nullptr && mask_in[i] != 0;
-      mask_out[i] = (was || sel) ? 1 : 0;
+      mask_out[i] = (was || sel_i) ? 1 : 0;
     }
     run += tot;
   }
 }
 
-__global__ void k_ds_init(int* n_active) {
-  if (threadIdx.x == 0 && n_active) *n_active = 0;
-}
-
+// (every block keeps one pixel, so the count is the number of blocks)
 __global__ void k_downsample(const float* T, int w, int h, int bw, int bh, uint8_t* mask,
                              int* n_active) {
   const int nbx = (w + bw - 1) / bw, nby = (h + bh - 1) / bh;
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b == 0 && n_active) *n_active = nbx * nby;
   if (b >= nbx * nby) return;
   const int x0 = (b % nbx) * bw, y0 = (b / nbx) * bh;
   const int x1 = min(w, x0 + bw), y1 = min(h, y0 + bh);
@@ -200,7 +266,6 @@ __global__ void k_downsample(const float* T, int w, int h, int bw, int bh, uint8
     }
   for (int y = y0; y < y1; ++y)
     for (int x = x0; x < x1; ++x) mask[y * w + x] = (y * w + x == best) ? 1 : 0;
-  if (n_active) atomicAdd(n_active, 1);
 }
 
 }  // namespace
@@ -209,24 +274,20 @@ hipError_t launch_prune(const float* g_means, const float* g_cov3d, const uint8_
                         const uint8_t* mask_in, int n, float lambda, float ratio,
                         uint8_t* mask_out, int* n_masked, float* score_out, uint32_t* scr,
                         hipStream_t st) {
-  k_prune_init<<<1, 256, 0, st>>>(scr);
-  if (n <= 0) {
-    k_prune_setup<<<1, 1, 0, st>>>(scr, ratio, n_masked);
-    return hipGetLastError();
-  }
-  const int grid = min(1024, (n + 255) / 256);
-  k_prune_count<<<grid, 256, 0, st>>>(visible, mask_in, n, scr);
-  k_prune_setup<<<1, 1, 0, st>>>(scr, ratio, n_masked);
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    k_prune_hist<<<grid, 256, 0, st>>>(g_means, g_cov3d, lambda, visible, mask_in, n, shift, scr);
-    k_prune_pick<<<1, 256, 0, st>>>(scr);
-  }
+  k_prune_init<<<3 * kBins / kHistThreads, kHistThreads, 0, st>>>(scr, n_masked);
+  if (n <= 0) return hipGetLastError();
+  const int grid = min(256, (n + kHistThreads - 1) / kHistThreads);
+  k_prune_hist<0><<<grid, kHistThreads, 0, st>>>(g_means, g_cov3d, lambda, visible, mask_in, n,
+                                                 ratio, scr);
+  k_prune_hist<1><<<grid, kHistThreads, 0, st>>>(g_means, g_cov3d, lambda, visible, mask_in, n,
+                                                 ratio, scr);
+  k_prune_hist<2><<<grid, kHistThreads, 0, st>>>(g_means, g_cov3d, lambda, visible, mask_in, n,
+                                                 ratio, scr);
   const int nb = min(kSelBlocks, (n + kSelThreads - 1) / kSelThreads);
   k_prune_eqcount<<<nb, kSelThreads, 0, st>>>(g_means, g_cov3d, lambda, visible, mask_in, n, nb,
-                                               scr);
-  k_prune_scan<<<1, 64, 0, st>>>(scr, nb);
+                                               ratio, scr);
   k_prune_final<<<nb, kSelThreads, 0, st>>>(g_means, g_cov3d, lambda, visible, mask_in, n, nb,
-                                             scr, mask_out, score_out);
+                                             ratio, scr, mask_out, n_masked, score_out);
   return hipGetLastError();
 }
 
@@ -234,8 +295,7 @@ hipError_t launch_downsample(const float* final_T, int w, int h, int j, uint8_t*
                              int* n_active, hipStream_t st) {
   const int bw = 1 << ((j + 1) / 2), bh = 1 << (j / 2);
   const int nb = ((w + bw - 1) / bw) * ((h + bh - 1) / bh);
-  k_ds_init<<<1, 64, 0, st>>>(n_active);
-  if (nb > 0) k_downsample<<<(nb + 255) / 256, 256, 0, st>>>(final_T, w, h, bw, bh, mask_out,
+  k_downsample<<<(nb + 255) / 256, 256, 0, st>>>(final_T, w, h, bw, bh, mask_out,
                                                             n_active);
   return hipGetLastError();
 }
