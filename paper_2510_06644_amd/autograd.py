@@ -22,6 +22,8 @@ per-fragment results for the backward, Sec. 5.2):
 * ``"auto"``: save unless 8 B/pixel would exceed ``auto_budget`` of the free
   device memory.
 """
+import dataclasses
+
 import torch
 
 from . import rtgs
@@ -50,7 +52,11 @@ class RenderFn(torch.autograd.Function):
         ctx.vm = vm
         ctx.cam = cam
         ctx.renderer = renderer
-        ctx.st = st
+        # without the images: an output that its own graph node holds is a
+        # reference cycle, and the workspace then waits for the garbage
+        # collector while every call allocates device memory anew (2000 Gaussians
+        # at 128x128, forward and backward: 440 us instead of 260)
+        ctx.st = dataclasses.replace(st, color=None, depth=None, alpha=None, visible=None)
         ctx.gauss_mask = gauss_mask
         ctx.pixel_mask = pixel_mask
         ctx.need_cov3d = need_cov3d
@@ -62,8 +68,8 @@ class RenderFn(torch.autograd.Function):
     def backward(ctx, g_color, g_depth, g_alpha, _g_visible):
         need_map, need_pose = ctx.needs
         st = ctx.st
-        h, w = st.depth.shape
-        dev = st.depth.device
+        h, w = ctx.cam.height, ctx.cam.width
+        dev = st.ws.device
         g_color = torch.zeros(3, h, w, device=dev) if g_color is None else g_color.contiguous()
         g_depth = torch.zeros(h, w, device=dev) if g_depth is None else g_depth.contiguous()
         if not (need_map or need_pose):
