@@ -32,6 +32,14 @@ __global__ void k_init(WsPtrs W) {
   W.order_n[threadIdx.x] = 0u;
 }
 
+// Two counts to host memory, and zero in their place.
+__global__ void k_take_counts(unsigned long long* d, unsigned long long* host) {
+  if (threadIdx.x < 2) {
+    host[threadIdx.x] = d[threadIdx.x];
+    d[threadIdx.x] = 0;
+  }
+}
+
 struct Proj {
   double u, v, z, sxx, sxy, syy;
   bool ok;
@@ -676,6 +684,11 @@ __global__ void k_wave_sum_test(const float* in, float* out, int n_waves) {
 }
 
 }  // namespace
+
+hipError_t launch_take_counts(unsigned long long* d, unsigned long long* host, hipStream_t st) {
+  k_take_counts<<<1, 64, 0, st>>>(d, host);
+  return hipGetLastError();
+}
 
 hipError_t launch_forward_prep(const Batch& b, const WsPtrs& w, unsigned long long* max_pairs,
                                bool reuse_lists, hipStream_t st, StageTimer* tm) {

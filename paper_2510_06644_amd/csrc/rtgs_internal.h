@@ -247,6 +247,8 @@ struct Scope {
 };
 
 // ---- launch wrappers (defined in the .hip files) ----
+// Moves d[0], d[1] to host memory (pinned) and zeroes them.
+hipError_t launch_take_counts(unsigned long long* d, unsigned long long* host, hipStream_t st);
 hipError_t launch_forward_prep(const Batch& b, const WsPtrs& w, unsigned long long* max_pairs,
                                bool reuse_lists, hipStream_t st, StageTimer* tm);
 void launch_tile_sort(const Batch& b, const WsPtrs& w, hipStream_t st);
