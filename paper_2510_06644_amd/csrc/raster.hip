@@ -24,6 +24,8 @@
 // (Sec. 5.3).  The tile -> Gaussian merge (its Stage Buffer) adds a Gaussian's
 // slots in the preprocessing backward; no float atomics anywhere, so gradients
 // are bitwise reproducible.
+#include <type_traits>
+
 #include "rtgs_internal.h"
 
 namespace rtgs {
@@ -70,7 +72,7 @@ __device__ __forceinline__ bool wave_by_work(const WsPtrs& W, int t_total, int& 
     const uint32_t y = __shfl_up(x, off, kOrderClasses);
     if ((lane & (kOrderClasses - 1)) >= off) x += y;
   }
-  const unsigned long long past = __ballot(x > i);
+  const unsigned long long past = __builtin_amdgcn_ballot_w64(x > i);
   if (past == 0) return false;
   const int c = __builtin_ctzll(past);     // lane of the class
   const uint32_t before = (uint32_t)__shfl(x - n, c);
@@ -224,7 +226,9 @@ __device__ __forceinline__ void wave_lds_order() {
 
 constexpr int kFwdStage = 16;             // entries walked at a time (16, 32, 8: 87, 90, 100 us)
 constexpr int kFwdQueue = kFwdStage + 64; // < kFwdStage left over + 64 new ones
-constexpr int kTabWords = 26;             // words of an entry's table (even; spreads the banks)
+// Words of an entry's table for COLS columns and rows of samples: dx of the
+// columns, the two terms of the rows, (A, opacity).  Even; spreads the banks.
+constexpr int tab_words(int cols) { return 3 * cols + 2; }
 
 // One wave per workgroup, for one 8x8 quadrant of a tile (as the backward).
 // It tests 64 list entries at a time, one a lane, against its quadrant (the
@@ -236,8 +240,8 @@ constexpr int kTabWords = 26;             // words of an entry's table (even; sp
 //    exponent that depend on the row alone are formed once per entry, by four
 //    lanes an entry, so that a pixel's exponent is two FMAs on three LDS
 //    values instead of nine operations; the values are frag_alpha's, bit for
-//    bit.  Samples that are not on the pixel grid (IRR: downsampled frames,
-//    BAL) use frag_alpha itself.
+//    bit.  One sample a block of 2x2 pixels takes 16 columns and rows; other
+//    samples off the pixel grid (larger blocks, BAL) use frag_alpha itself.
 //  * C += w (r, g, b, z) is one 4x4x1 MFMA: block i of four lanes multiplies
 //    the entry's four values (row j: value j) with its lanes' four weights,
 //    an exact FMA per element; the A operand of four entries is one LDS read,
@@ -245,7 +249,8 @@ constexpr int kTabWords = 26;             // words of an entry's table (even; sp
 //  * A stopped pixel's T is negative, so `T' < 1e-4` also keeps it stopped.
 // Measured at 1200x680 / 300k: 92 -> 88 us (51.8M -> 36M wave VALU
 // instructions; 71 us of issue, exp at quarter rate included, the rest the
-// last waves draining); 640x480 / 100k 55 -> 49 us, 320x240 / 20k 21.6 -> 18 us.
+// last waves draining); 640x480 / 100k 55 -> 49 us, 320x240 / 20k 21.6 -> 18 us;
+// 1200x680 at 1 in 4 / 500k 109 -> 78 us by the tables of 16 columns.
 // Before, four waves of a tile shared batches of 256 entries, 29 VALU
 // instructions a walked entry.
 //
@@ -256,8 +261,9 @@ constexpr int kTabWords = 26;             // words of an entry's table (even; sp
 // sample's walked entries to S.lane_work_out for the next forward.
 template <bool STATS, bool FRAG, bool BAL, bool ONE, bool IRR>
 __global__ __launch_bounds__(64) void k_raster_fwd(Batch B, WsPtrs W) {
-  constexpr bool kPlain = !STATS && !FRAG && !BAL && !IRR;
-  __shared__ __align__(16) float s_tab[kFwdStage * kTabWords];
+  constexpr bool kPlain = !STATS && !FRAG && !BAL;
+  constexpr int kMaxCols = IRR && !BAL ? 16 : 8;
+  __shared__ __align__(16) float s_tab[kFwdStage * tab_words(kMaxCols)];
   __shared__ float4 s_r0[kFwdQueue], s_k4[kFwdQueue], s_col[kFwdQueue];
   __shared__ int s_pos[kFwdQueue];
   int tile, wave;
@@ -267,7 +273,6 @@ __global__ __launch_bounds__(64) void k_raster_fwd(Batch B, WsPtrs W) {
                        : quadrant_sample(wave, lane);
   const TileCtx c = tile_ctx<ONE>(B, tile, sidx);
   const SessionDev& S = batch_session<ONE>(B, c.s);
-  const bool grid8 = !IRR || (!BAL && (S.sub_sx | S.sub_sy) == 0);   // samples are 8x8 pixels
   const bool active = c.has && (S.pmask == nullptr || S.pmask[c.pix] != 0);
   const float pxf = (float)c.px + 0.5f, pyf = (float)c.py + 0.5f;
   // the box of samples the wave culls against
@@ -283,7 +288,9 @@ __global__ __launch_bounds__(64) void k_raster_fwd(Batch B, WsPtrs W) {
       y1 = max(y1, __shfl_xor(y1, off));
     }
   }
-  const float qx = (float)(c.tile_x0 + x0) + 0.5f, qy = (float)(c.tile_y0 + y0) + 0.5f;   // grid8
+  // the quadrant's first pixel, and the lane's sample from there
+  const int ox = c.tile_x0 + (x0 << S.sub_sx), oy = c.tile_y0 + (y0 << S.sub_sy);
+  const float qx = (float)ox + 0.5f, qy = (float)oy + 0.5f;
   // list positions fit in int32: the pair capacity is below 2^31
   const int start = (int)min((int64_t)W.tile_start[tile], W.cap);
   const int end = (int)min((int64_t)W.tile_start[tile + 1], W.cap);
@@ -296,129 +303,140 @@ __global__ __launch_bounds__(64) void k_raster_fwd(Batch B, WsPtrs W) {
   int nblend = 0;
   uint32_t fcur = 0;            // saved fragments of this wave so far
   const int64_t fbase = FRAG ? frag_base(start, end, wave) : 0;
-  const float* const t_x = s_tab + (lane & 7);
-  const float2* const t_y = reinterpret_cast<const float2*>(s_tab + 8) + (lane >> 3);
   const float* const col_words = reinterpret_cast<const float*>(s_col) + (lane & 15);
   int walked = 0, done = 0;     // entries walked up to the lane's last blended one; in all
-  int head = 0, queued = 0;     // head: a multiple of kFwdStage, so no batch wraps around
-  // the record this lane tests next, and the Gaussian after it: a list's test
-  // steps would otherwise wait for a dependent load each
-  uint32_t nid = start + lane < end ? W.ids[start + lane] : 0u;
-  GaussRec next;
-  if (start + lane < end) next = W.rec[nid];
-  nid = start + 64 + lane < end ? W.ids[start + 64 + lane] : 0u;
-  for (int b0 = start; b0 < end; b0 += 64) {
-    const GaussRec r = next;
-    bool hit = b0 + lane < end;
-    if (b0 + 64 + lane < end) next = W.rec[nid];
-    if (b0 + 128 + lane < end) nid = W.ids[b0 + 128 + lane];
-    if (hit) {
-      hit = box_hit(r.pos, r.conic, r.ext.z, c.tile_x0, c.tile_y0, S.sub_sx, S.sub_sy, x0, y0, x1,
-                    y1);
-    }
-    const unsigned long long m = __ballot(hit);
-    if (lane == 0) W.hits[hits_at(start, tile, b0, wave)] = m;
-    if (hit) {
-      int at = head + queued + (int)lane_rank(m);
-      at -= at >= kFwdQueue ? kFwdQueue : 0;
-      s_r0[at] = r.pos;
-      s_k4[at] = conic_log2(r.conic);
-      s_col[at] = r.col;
-      s_pos[at] = b0 + lane;
-    }
-    queued += __popcll(m);
-    while (queued >= kFwdStage || (b0 + 64 >= end && queued > 0)) {
-      const int n = min(kFwdStage, queued);
-      // entries of opacity 0 fill the last group of four up
-      if (lane < (-n & 3)) {
-        const int at = head + n + lane;
-        s_r0[at] = s_k4[at] = s_col[at] = make_float4(0.f, 0.f, 0.f, 0.f);
-        s_pos[at] = 0;
+  // COLS: the columns and rows that the samples lie in (0: any number)
+  auto walk = [&](auto cols) {
+    constexpr int COLS = decltype(cols)::value, kTab = tab_words(COLS);
+    const float* const t_x = s_tab + (COLS == 8 ? lane & 7 : c.px - ox);
+    const float2* const t_y =
+        reinterpret_cast<const float2*>(s_tab + COLS) + (COLS == 8 ? lane >> 3 : c.py - oy);
+    int head = 0, queued = 0;     // head: a multiple of kFwdStage, so no batch wraps around
+    // the record this lane tests next, and the Gaussian after it: a list's test
+    // steps would otherwise wait for a dependent load each
+    uint32_t nid = start + lane < end ? W.ids[start + lane] : 0u;
+    GaussRec next;
+    if (start + lane < end) next = W.rec[nid];
+    nid = start + 64 + lane < end ? W.ids[start + 64 + lane] : 0u;
+    for (int b0 = start; b0 < end; b0 += 64) {
+      const GaussRec r = next;
+      bool hit = b0 + lane < end;
+      if (b0 + 64 + lane < end) next = W.rec[nid];
+      if (b0 + 128 + lane < end) nid = W.ids[b0 + 128 + lane];
+      if (hit) {
+        hit = box_hit(r.pos, r.conic, r.ext.z, c.tile_x0, c.tile_y0, S.sub_sx, S.sub_sy, x0, y0, x1,
+                      y1);
       }
-      wave_lds_order();
-      if (grid8) {
-        // kParts lanes an entry, each its share of the columns and rows
-        constexpr int kParts = 64 / kFwdStage, kShare = 8 / kParts;
-        const int e = lane % kFwdStage, h = (lane / kFwdStage) * kShare;
-        const float4 r0 = s_r0[head + e], k4 = s_k4[head + e];
-        float* t = s_tab + e * kTabWords;
-        if (e < ((n + 3) & ~3)) {
-#pragma unroll
-          for (int i = 0; i < kShare; i += 2) {
-            const float d0 = (r0.x - (qx + (float)(h + i))) + r0.z;
-            const float d1 = (r0.x - (qx + (float)(h + i + 1))) + r0.z;
-            *reinterpret_cast<float2*>(t + h + i) = make_float2(d0, d1);
-          }
-#pragma unroll
-          for (int i = 0; i < kShare; ++i) {
-            const float dy = (r0.y - (qy + (float)(h + i))) + r0.w;
-            *reinterpret_cast<float2*>(t + 8 + 2 * (h + i)) =
-                make_float2(k4.y * dy, (k4.z * dy) * dy);
-          }
-          if (h == 0) *reinterpret_cast<float2*>(t + 24) = make_float2(k4.x, k4.w);
+      const unsigned long long m = __builtin_amdgcn_ballot_w64(hit);
+      if (lane == 0) W.hits[hits_at(start, tile, b0, wave)] = m;
+      if (hit) {
+        int at = head + queued + (int)lane_rank(m);
+        at -= at >= kFwdQueue ? kFwdQueue : 0;
+        s_r0[at] = r.pos;
+        s_k4[at] = conic_log2(r.conic);
+        s_col[at] = r.col;
+        s_pos[at] = b0 + lane;
+      }
+      queued += __popcll(m);
+      while (queued >= kFwdStage || (b0 + 64 >= end && queued > 0)) {
+        const int n = min(kFwdStage, queued);
+        // entries of opacity 0 fill the last group of four up
+        if (lane < (-n & 3)) {
+          const int at = head + n + lane;
+          s_r0[at] = s_k4[at] = s_col[at] = make_float4(0.f, 0.f, 0.f, 0.f);
+          s_pos[at] = 0;
         }
         wave_lds_order();
-      }
-      int lastk = -1;               // the lane's last blended entry of these
-      // every lane evaluates each entry; the decisions are selects, not
-      // branches: skip (alpha < 1/255), stop (T would fall below 1e-4; the
-      // fragment is excluded) or blend
-      auto weight = [&](int k) -> float {
-        Frag f;
-        float raw;
-        if (grid8) {
-          const float dx = t_x[k * kTabWords];
-          const float2 y = t_y[k * (kTabWords / 2)];
-          const float2 ao = *reinterpret_cast<const float2*>(s_tab + k * kTabWords + 24);
-          const float p2 = __builtin_fmaf(dx, __builtin_fmaf(ao.x, dx, y.x), y.y);
-          f.e = __builtin_amdgcn_exp2f(p2);
-          raw = ao.y * f.e;
-          f.alpha = fminf(kAlphaMax, raw);
-          f.om = fmaxf(1.f - kAlphaMax, __builtin_fmaf(-ao.y, f.e, 1.f));
-        } else {
-          const float4 kk = s_k4[head + k];
-          f = frag_alpha(s_r0[head + k], kk, pxf, pyf);
-          raw = kk.w * f.e;
+        if (COLS > 0) {
+          // kParts lanes an entry, each its share of the columns and rows
+          constexpr int kParts = 64 / kFwdStage, kShare = COLS / kParts;
+          const int e = lane % kFwdStage, h = (lane / kFwdStage) * kShare;
+          const float4 r0 = s_r0[head + e], k4 = s_k4[head + e];
+          float* t = s_tab + e * kTab;
+          if (e < ((n + 3) & ~3)) {
+#pragma unroll
+            for (int i = 0; i < kShare; i += 2) {
+              const float d0 = (r0.x - (qx + (float)(h + i))) + r0.z;
+              const float d1 = (r0.x - (qx + (float)(h + i + 1))) + r0.z;
+              *reinterpret_cast<float2*>(t + h + i) = make_float2(d0, d1);
+            }
+#pragma unroll
+            for (int i = 0; i < kShare; ++i) {
+              const float dy = (r0.y - (qy + (float)(h + i))) + r0.w;
+              *reinterpret_cast<float2*>(t + COLS + 2 * (h + i)) =
+                  make_float2(k4.y * dy, (k4.z * dy) * dy);
+            }
+            if (h == 0) *reinterpret_cast<float2*>(t + 3 * COLS) = make_float2(k4.x, k4.w);
+          }
+          wave_lds_order();
         }
-        const float tn = T * f.om;
-        const bool seen = !(f.alpha < kAlphaMin);
-        const bool blend = seen && !(tn < kTMin);
-        if (STATS || BAL) stop = T > 0.f && seen && !blend ? s_pos[head + k] : stop;
-        const float w = blend ? f.alpha * T : 0.f;       // adds exactly 0 otherwise
-        T = blend ? tn : (seen ? -fabsf(T) : T);
-        lastk = blend ? k : lastk;
-        if (STATS) nblend += blend ? 1 : 0;
-        if (FRAG && k < n) {
-          const unsigned long long bm = __ballot(blend);
-          if (lane == 0) W.fmask[(int64_t)s_pos[head + k] * 4 + wave] = bm;
-          if (blend)
-            W.fdata[fbase + fcur + lane_rank(bm)] =
-                make_float2(raw > kAlphaMax ? -f.alpha : f.alpha, f.om);
-          fcur += (uint32_t)__popcll(bm);
-        }
-        return w;
-      };
-      // unrolled in the plain kernels, so that every position is an immediate
+        int lastk = -1;               // the lane's last blended entry of these
+        // every lane evaluates each entry; the decisions are selects, not
+        // branches: skip (alpha < 1/255), stop (T would fall below 1e-4; the
+        // fragment is excluded) or blend
+        auto weight = [&](int k) -> float {
+          Frag f;
+          float raw;
+          if (COLS > 0) {
+            const float dx = t_x[k * kTab];
+            const float2 y = t_y[k * (kTab / 2)];
+            const float2 ao = *reinterpret_cast<const float2*>(s_tab + k * kTab + 3 * COLS);
+            const float p2 = __builtin_fmaf(dx, __builtin_fmaf(ao.x, dx, y.x), y.y);
+            f.e = __builtin_amdgcn_exp2f(p2);
+            raw = ao.y * f.e;
+            f.alpha = fminf(kAlphaMax, raw);
+            f.om = fmaxf(1.f - kAlphaMax, __builtin_fmaf(-ao.y, f.e, 1.f));
+          } else {
+            const float4 kk = s_k4[head + k];
+            f = frag_alpha(s_r0[head + k], kk, pxf, pyf);
+            raw = kk.w * f.e;
+          }
+          const float tn = T * f.om;
+          const bool seen = !(f.alpha < kAlphaMin);
+          const bool blend = seen && !(tn < kTMin);
+          if (STATS || BAL) stop = T > 0.f && seen && !blend ? s_pos[head + k] : stop;
+          const float w = blend ? f.alpha * T : 0.f;       // adds exactly 0 otherwise
+          T = blend ? tn : (seen ? -fabsf(T) : T);
+          lastk = blend ? k : lastk;
+          if (STATS) nblend += blend ? 1 : 0;
+          if (FRAG && k < n) {
+            const unsigned long long bm = __builtin_amdgcn_ballot_w64(blend);
+            if (lane == 0) W.fmask[(int64_t)s_pos[head + k] * 4 + wave] = bm;
+            if (blend)
+              W.fdata[fbase + fcur + lane_rank(bm)] =
+                  make_float2(raw > kAlphaMax ? -f.alpha : f.alpha, f.om);
+            fcur += (uint32_t)__popcll(bm);
+          }
+          return w;
+        };
+        // unrolled in the plain kernels, so that every position is an immediate
 #pragma unroll(kPlain ? kFwdStage / 4 : 1)
-      for (int k = 0; k < kFwdStage; k += 4) {
-        if (k >= n || __ballot(T > 0.f) == 0) break;     // or the whole wave has stopped
-        const float a = col_words[4 * (head + k)];
-        C = __builtin_amdgcn_mfma_f32_4x4x1f32(a, weight(k), C, 2, 0, 0);
-        C = __builtin_amdgcn_mfma_f32_4x4x1f32(a, weight(k + 1), C, 2, 1, 0);
-        C = __builtin_amdgcn_mfma_f32_4x4x1f32(a, weight(k + 2), C, 2, 2, 0);
-        C = __builtin_amdgcn_mfma_f32_4x4x1f32(a, weight(k + 3), C, 2, 3, 0);
+        for (int k = 0; k < kFwdStage; k += 4) {
+          if (k >= n || __builtin_amdgcn_ballot_w64(T > 0.f) == 0) break;     // or the whole wave has stopped
+          const float a = col_words[4 * (head + k)];
+          C = __builtin_amdgcn_mfma_f32_4x4x1f32(a, weight(k), C, 2, 0, 0);
+          C = __builtin_amdgcn_mfma_f32_4x4x1f32(a, weight(k + 1), C, 2, 1, 0);
+          C = __builtin_amdgcn_mfma_f32_4x4x1f32(a, weight(k + 2), C, 2, 2, 0);
+          C = __builtin_amdgcn_mfma_f32_4x4x1f32(a, weight(k + 3), C, 2, 3, 0);
+        }
+        if (lastk >= 0) {
+          last = s_pos[head + lastk];
+          walked = done + lastk + 1;
+        }
+        done += n;
+        wave_lds_order();
+        queued -= n;
+        head = head == kFwdQueue - kFwdStage ? 0 : head + kFwdStage;
       }
-      if (lastk >= 0) {
-        last = s_pos[head + lastk];
-        walked = done + lastk + 1;
-      }
-      done += n;
-      wave_lds_order();
-      queued -= n;
-      head = head == kFwdQueue - kFwdStage ? 0 : head + kFwdStage;
+      if (__builtin_amdgcn_ballot_w64(T > 0.f) == 0) break;
     }
-    if (__ballot(T > 0.f) == 0) break;
-  }
+  };
+  if (!IRR || (!BAL && (S.sub_sx | S.sub_sy) == 0))
+    walk(std::integral_constant<int, 8>{});
+  else if (!BAL && S.sub_sx <= 1 && S.sub_sy <= 1)
+    walk(std::integral_constant<int, 16>{});
+  else
+    walk(std::integral_constant<int, 0>{});
   if (FRAG && lane == 0) W.fcount[(int64_t)tile * 4 + wave] = fcur;
   if (W.order) {                // (not when the backward recomputes the state)
     int w = walked;
@@ -476,21 +494,16 @@ __global__ __launch_bounds__(64) void k_raster_fwd(Batch B, WsPtrs W) {
     }
 }
 
-constexpr int kBwdBatch = 64;            // list entries per staging step (one per lane)
-
-// Entries per group of the backward's two passes, and the LDS swizzle of a
-// group's (-dL/dpower, w) pairs.  Pass 1 writes entry `slot`, sample (row r,
-// column c) of the wave's 8x8 samples; pass 2's lane (entry e, row r) reads
-// two columns at a time (16 bytes).  XOR by the slot and by the row's parity
-// spreads a quarter wave's 16-byte reads over all banks.
+// Entries per group of the backward's two passes, and the LDS layout of a
+// group: -dL/dpower of entry k at the wave's 64 pixels in row k, the blend
+// weights in row kGrp + k.  Rows are 17 units of 16 bytes long, and pass 2's
+// lanes are dealt to (entry, row of pixels) and (entry, 4 pixels) so that a
+// quarter wave's reads touch every bank once (see prow and pblock there).
 constexpr int kGrp = 8;
-
-// Byte offset in a group's 64 pairs of sample (r, c), slot bits excluded: the
-// slot enters by XOR with slot_bits(slot).
-__device__ __forceinline__ unsigned pair_off(int r, int c) {
-  return 128u * (unsigned)((c >> 1) ^ (r & 1)) + 16u * (unsigned)r + 8u * (unsigned)(c & 1);
-}
-__device__ __forceinline__ unsigned slot_bits(int slot) { return 528u * (unsigned)slot; }
+constexpr int kRowWords = 68;
+constexpr int kBwdQueue = 2 * kGrp + 64; // < 2 kGrp left over + 64 new ones
+// Words of an entry's table: as the forward's, then list position and pair.
+constexpr int bwd_tab_words(int cols) { return 3 * cols + 4; }
 
 // NV = 10 (all parameters) or 6 (pose only) sums per list entry.  GA: some
 // session has an alpha-image gradient (without one, its term of dL/dalpha is
@@ -503,25 +516,37 @@ __device__ __forceinline__ unsigned slot_bits(int slot) { return 528u * (unsigne
 // a flag byte; everything else is neither written nor read.
 //
 // Bound by VALU issue, so the design minimises instructions per (list entry,
-// wave).  Two passes over groups of kGrp entries:
-//  1. lane = pixel: alpha again, T and the suffix recovered, giving two values
-//     per (entry, pixel), n = -dL/dpower and the blend weight w, stored to LDS;
-//  2. lane = (entry, row of 8 pixels): the NV sums over the row's pixels as
-//     plain FMAs, the offsets to the Gaussian's centre shared along rows and
-//     columns; then one reduce-scatter over the 8 rows for all 8 entries.
+// wave).  The entries that reach the quadrant go through a queue, in falling
+// list order, and are worked on in groups of kGrp without branches, so that the
+// latencies of one entry hide behind the others; half a wave fetches the next
+// group's records meanwhile (64 bytes, a lane a quarter).  Two passes a group:
+//  1. lane = pixel: alpha again (with the forward's tables of offsets and row
+//     terms), T and the suffix recovered, giving two values per (entry, pixel),
+//     n = -dL/dpower and the blend weight w, stored to LDS.  The products of an
+//     entry's (r, g, b, z) with the pixels' upstream gradients are 4x4x1 MFMAs,
+//     four entries at a time;
+//  2. lane = (entry, row of 8 pixels): the sums of n over the row's pixels, the
+//     offsets to the Gaussian's centre from the tables; one reduce-scatter over
+//     the 8 rows for all 8 entries.  The sums of w times the upstream gradients
+//     are 4x4x1 MFMAs again (entry by value, over the pixels) and a sum over the
+//     16 groups of pixels; pose only, the one value goes with the sums of n.
 // The sums, d = centre - pixel: n dx, n dy, n dx^2, n dx dy, n dy^2, n (NV = 10
 // only), w g_r, w g_g, w g_b (NV = 10 only), w g_z; the conic and the opacity
 // are applied once per Gaussian by the preprocessing backward:
 //   d power / d(u, v) = -(a dx + b dy, b dx + c dy), d power / d(a, b, c) =
 //   -(dx^2 / 2, dx dy, dy^2 / 2), dL/do = sum alpha dL/dalpha / o.
 // All sums are formed in a fixed order: bitwise reproducible, no float atomics.
+// (Moments of n about the quadrant's middle, one 16x16x4 MFMA chain a group and
+// shifted to the centre in double, cost digits: narrow Gaussians cancel.)
 //
-// Measured at 1200x680 / 300k, NV = 10: 241 -> 165 us (109M -> 79M wave VALU
-// instructions, 438 -> 141 MB moved); pose only at 640x480 / 100k: 109 -> 84 us.
+// Measured at 1200x680 / 300k, NV = 10: 241 -> 136 us (109M -> 62M wave VALU
+// instructions, 121 us of issue; the rest the last waves draining); pose only at
+// 640x480 / 100k 109 -> 62 us, 1200x680 at 1 in 4 / 500k 135 -> 120 us.
 // Before, four waves of a tile met at two barriers per 64 entries, summed ten
 // values over the wave per entry (lane swaps and DPP, 29 instructions), and
-// every pair without a gradient was written as zeros.  The two passes alone,
-// still with the barriers: 239 us.
+// every pair without a gradient was written as zeros.  One wave a quadrant with
+// pass 2 on the VALU and entries one by one: 147, 72 and 138 us; the same with
+// the MFMAs but a branch an entry: 179 us.
 //
 // FRAG: the forward saved its fragments (frag_base): each entry's blending
 // lanes and their (alpha, 1 - alpha) are read instead of re-evaluating alpha,
@@ -531,15 +556,19 @@ __device__ __forceinline__ unsigned slot_bits(int slot) { return 528u * (unsigne
 // BAL: the forward assigned lanes by previous work (lane_schedule); the same
 // samples go to the same lanes here (the saved quadrant bits are per wave).
 // IRR: some tile's samples may not form the 8x8 pixel grid of its quadrants
-// (downsampled frames, BAL); pass 2 then takes each sample's own centre.
-template <int NV, bool GA, bool FRAG, bool BAL, bool ONE, bool IRR>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5)))
+// (downsampled frames, BAL).  A uniform branch outside the loops takes the grid's
+// code, that of tables of 16 columns and rows (blocks of up to 2x2 pixels) or
+// frag_alpha; off the grid pass 2 takes each sample's own centre.
+// EU: waves a SIMD the registers are kept to (raster_bwd_variant).
+template <int NV, bool GA, bool FRAG, bool BAL, bool ONE, bool IRR, int EU>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(EU)))
 void k_raster_bwd(Batch B, WsPtrs W) {
-  constexpr int NG = NV == 10 ? 4 : 1;     // upstream values pass 2 needs of a pixel
-  __shared__ float4 s_r0[kBwdBatch], s_r1[kBwdBatch], s_r2[kBwdBatch];
-  __shared__ uint32_t s_slot[kBwdBatch];
-  __shared__ unsigned long long s_fm[FRAG ? kBwdBatch : 1];
-  __shared__ __align__(16) float2 s_pair[kGrp * 64];        // the group's (n, w)
+  __shared__ uint2 s_queue[kBwdQueue];                      // (Gaussian, list position)
+  __shared__ float4 s_rec[4 * kGrp];                        // the group's records
+  __shared__ unsigned long long s_fm[FRAG ? kBwdQueue : 1];
+  __shared__ __align__(16) float s_rows[2 * kGrp * kRowWords];   // see kGrp
+  constexpr int kMaxCols = IRR && !BAL ? 16 : 8;
+  __shared__ __align__(16) float s_tab[kGrp * bwd_tab_words(kMaxCols)];
   __shared__ float2 s_xy[IRR ? 64 : 1];                     // sample centres
   int tile, wave;
   if (!wave_by_work(W, B.t_total, tile, wave)) return;
@@ -550,7 +579,6 @@ void k_raster_bwd(Batch B, WsPtrs W) {
   const SessionDev& S = batch_session<ONE>(B, c.s);
   const int ltx = c.lt % S.tiles_x, lty = c.lt / S.tiles_x;
   const bool active = c.has && (S.pmask == nullptr || S.pmask[c.pix] != 0);
-  const bool grid8 = !IRR || (!BAL && (S.sub_sx | S.sub_sy) == 0);   // samples are 8x8 pixels
   const int64_t hw = (int64_t)S.width * S.height;
   const int start = (int)min((int64_t)W.tile_start[tile], W.cap);
   const int end = (int)min((int64_t)W.tile_start[tile + 1], W.cap);
@@ -581,204 +609,322 @@ void k_raster_bwd(Batch B, WsPtrs W) {
     fcur = W.fcount[(int64_t)tile * 4 + wave];
     fbase = frag_base(start, end, wave);
   }
-  // pass 2: this lane's entry of a group, its row of samples, and the row's
-  // upstream gradients (exchanged through LDS once, then kept)
-  const int ge = lane & 7, gr = lane >> 3;
-  float G[8][NG];
+  // pass 2: this lane's entry of a group and its row of samples; the upstream
+  // gradients it takes: of z along the row (pose only), or r, g, b, z (lane & 3)
+  // at four pixels
+  const int ge = lane & 7, prow = (lane >> 4) | ((lane >> 1) & 4);
+  const int pblock = 4 * (((lane >> 2) & 3) * 4 + (lane >> 4));
+  float G[NV == 10 ? 4 : 8];
   {
-    float4* sg = reinterpret_cast<float4*>(s_pair);
-    sg[lane] = make_float4(g0, g1, g2, gD);
+    s_rows[lane] = NV == 10 ? g0 : gD;
+    if (NV == 10) {
+      s_rows[64 + lane] = g1;
+      s_rows[128 + lane] = g2;
+      s_rows[192 + lane] = gD;
+    }
     if (IRR) s_xy[lane] = make_float2(pxf, pyf);
     wave_lds_order();
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const float4 v = sg[8 * gr + q];
-      if (NV == 10) {
-        G[q][0] = v.x;
-        G[q][1 % NG] = v.y;
-        G[q][2 % NG] = v.z;
-        G[q][3 % NG] = v.w;
-      } else {
-        G[q][0] = v.w;
-      }
+    for (int u = 0; u < (NV == 10 ? 1 : 2); ++u) {
+      const float4 q = *reinterpret_cast<const float4*>(
+          s_rows + (NV == 10 ? 64 * (lane & 3) + pblock : 8 * prow + 4 * u));
+      G[4 * u] = q.x; G[4 * u + 1] = q.y; G[4 * u + 2] = q.z; G[4 * u + 3] = q.w;
     }
     wave_lds_order();
   }
-  const float qx0 = (float)(c.tile_x0 + (wave & 1) * 8) + 0.5f;      // grid8: first column
-  const float qyr = (float)(c.tile_y0 + (wave >> 1) * 8 + gr) + 0.5f;   // grid8: this row
-  char* const pair_base = reinterpret_cast<char*>(s_pair);
-  const unsigned w_off = pair_off(lane >> 3, lane & 7);
-  const unsigned r_off0 = pair_off(gr, 0) ^ slot_bits(ge), r_off1 = pair_off(gr, 2) ^ slot_bits(ge);
+  // the quadrant's first pixel
+  const int ox = c.tile_x0 + (((wave & 1) * 8) << S.sub_sx);
+  const int oy = c.tile_y0 + (((wave >> 1) * 8) << S.sub_sy);
+  const float qx = (float)ox + 0.5f, qy = (float)oy + 0.5f;
+  // what the lane stores of a group's sums, and where in a pair's slots: lane
+  // (h, p, bit 3, entry) sum 3 h + p, with bit 3 sum 3 h + 2 (p = 0) or the flag
+  // (p = 1); lane (h, p, bit 3, bit 2, value) the w sum of entry 4 h + 2 bit 3 + p
+  const uint32_t cap = (uint32_t)W.cap;          // below 2^31
+  const int lh = lane >> 5, lp = (lane >> 4) & 1, sum = 3 * lh + (lane & 8 ? 2 : lp);
+  const int we = 4 * lh + (lane & 8 ? 2 : 0) + lp;
+  const bool sum_lane = !((lane & 8) && lp);
+  const bool flag_lane = (lane & 8) && lp && lh == 0;
+  const bool w_lane = NV == 10 && !(lane & 4);
+  float* const sum_dst = W.partial + wave * NV + sum;
+  float* const w_dst = W.partial + wave * NV + 6 + (lane & 3);
+  float* const wr = s_rows + lane;
+  const float* const rn = s_rows + ge * kRowWords + 8 * prow;
+  const float* const rw = NV == 10 ? s_rows + (kGrp + (lane & 3)) * kRowWords + pblock
+                                   : rn + kGrp * kRowWords;
   // S_j . g: the colour and depth of the fragments behind j, normalised by
   // the transmittance T_{j+1} they start from, dotted with the upstream gradient
   float SG = 0.f;
-  // the entries the quadrant can reach, of the 64 staged next (saved by the
-  // forward up to the wave's last blended one at least), and this lane's
-  int b0 = start + ((hi - start) & ~(kBwdBatch - 1));
-  unsigned long long nh = W.hits[hits_at(start, tile, b0, wave)];
-  uint32_t nid = b0 + lane <= hi ? W.ids[b0 + lane] : 0u;
-  for (; b0 >= start; b0 -= kBwdBatch) {
-    const int lrel = last - b0;     // entries at or before lrel lie before the pixel's stop
-    bool hit = b0 + lane <= hi && ((nh >> lane) & 1ull) != 0;
-    unsigned long long fm = 0;
-    if (FRAG && hit) {
-      fm = W.fmask[(int64_t)(b0 + lane) * 4 + wave];
-      hit = fm != 0;                // no lane of the wave blended it
-    }
-    unsigned long long m = __ballot(hit);
-    int k = __popcll(m);            // staged entries, in list order
-    if (hit) {
-      const int at = (int)lane_rank(m);
-      const GaussRec r = W.rec[nid];
-      s_r0[at] = r.pos;
-      s_r1[at] = conic_log2(r.conic);
-      s_r2[at] = r.col;
-      // the pair's slot: Gaussian-major, then row-major in its tile rectangle
-      s_slot[at] = W.goff[nid] + (uint32_t)(lty * __float_as_int(r.ext.y) + ltx) -
-                   __float_as_uint(r.ext.x);
-      if (FRAG) s_fm[at] = fm;
-    }
-    if (b0 > start) {
-      nh = W.hits[hits_at(start, tile, b0 - kBwdBatch, wave)];
-      nid = W.ids[b0 - kBwdBatch + lane];
-    }
-    wave_lds_order();
-    int slot = 0;                   // entries in the group
-    unsigned long long kpack = 0;   // their staged positions, 8 bits each
-    while (m) {
-      // descending list order: entry b0 + pos, staged at k
-      const int pos = 63 - __builtin_clzll(m);
-      m &= ~(1ull << pos);
-      --k;
-      // ---- pass 1
-      const float4 k4 = s_r1[k];
-      Frag f;
-      bool contrib, clamped, some = true;
-      if (FRAG) {
-        const unsigned long long bm = s_fm[k];
-        fcur -= (uint32_t)__popcll(bm);
-        contrib = ((bm >> lane) & 1ull) != 0;
-        float2 rec = make_float2(0.f, 1.f);
-        if (contrib) rec = W.fdata[fbase + fcur + lane_rank(bm)];
-        f.alpha = fabsf(rec.x);
-        f.om = rec.y;
-        clamped = rec.x < 0.f;
-      } else {
-        f = frag_alpha(s_r0[k], k4, pxf, pyf);
-        contrib = pos <= lrel && !(f.alpha < kAlphaMin);
-        some = __ballot(contrib) != 0;
-        clamped = k4.w * f.e > kAlphaMax;
-      }
-      if (some) {                   // some lane blended this entry
-        // lanes that did not blend it take alpha = 0 and 1 - alpha = 1, so
-        // every update below leaves their state unchanged and their
-        // gradients exactly zero (selects, not branches)
-        const float4 col = s_r2[k];
-        const float al = contrib ? f.alpha : 0.f;
-        const float om = contrib ? f.om : 1.f;
-        const float rom = __builtin_amdgcn_rcpf(om);
-        const float Tj = Tc * rom;                     // T before this fragment (rcp(1) = 1)
-        const float w = al * Tj;
-        // (colour, depth) of the fragment dotted with the upstream gradient
-        float cg = col.x * g0;
-        cg = __builtin_fmaf(col.y, g1, cg);
-        cg = __builtin_fmaf(col.z, g2, cg);
-        cg = __builtin_fmaf(col.w, gD, cg);
-        // dL/dalpha_j = T_j (c_j - S_j) . g + T_final gA / (1 - alpha_j)
-        const float dla = GA ? __builtin_fmaf(Tj, cg - SG, gAT * rom) : Tj * (cg - SG);
-        SG = __builtin_fmaf(al, cg, om * SG);
-        Tc = Tj;
-        // the clamp alpha = 0.99 has no gradient to o or to the power
-        const bool live = contrib && !clamped;
-        const float n = live ? -(f.alpha * dla) : 0.f;   // -dL/dpower
-        *reinterpret_cast<float2*>(pair_base + (w_off ^ slot_bits(slot))) = make_float2(n, w);
-        kpack |= (unsigned long long)k << (8 * slot);
-        ++slot;
-      }
-      if (slot != kGrp && (m || slot == 0)) continue;
-      // ---- pass 2: the group's entries (fewer than kGrp at the end of a step)
-      wave_lds_order();
-      const int ke = (int)(kpack >> (8 * ge)) & (kBwdBatch - 1);
-      const float4 r0 = s_r0[ke];
-      float v[NV];
-#pragma unroll
-      for (int i = 0; i < NV; ++i) v[i] = 0.f;
-      if (grid8) {
-        // sums of n, n dx, n dx^2 along the row
-        float a0 = 0.f, a1 = 0.f, a2 = 0.f;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float4 p = *reinterpret_cast<const float4*>(
-              pair_base + ((q & 1) ? r_off1 : r_off0) + 256 * (q >> 1));
-#pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            const int col = 2 * q + j;
-            const float n = j ? p.z : p.x, w = j ? p.w : p.y;
-            const float dx = (r0.x - (qx0 + (float)col)) + r0.z;
-            const float nd = n * dx;
-            a0 += n;
-            a1 += nd;
-            a2 = __builtin_fmaf(nd, dx, a2);
-            if (NV == 10) {
-#pragma unroll
-              for (int t = 0; t < 3; ++t) v[6 + t] = __builtin_fmaf(w, G[col][t % NG], v[6 + t]);
-            }
-            v[NV - 1] = __builtin_fmaf(w, G[col][NG - 1], v[NV - 1]);
-          }
+  // COLS: the columns and rows that the samples lie in (0: any number); 8: they
+  // are the 8x8 pixel grid
+  auto walk = [&](auto cols) {
+    constexpr int COLS = decltype(cols)::value, kTab = bwd_tab_words(COLS);
+    constexpr bool G8 = COLS == 8;
+    const float* const t_x = s_tab + (G8 ? lane & 7 : c.px - ox);
+    const float2* const t_y =
+        reinterpret_cast<const float2*>(s_tab + COLS) + (G8 ? lane >> 3 : c.py - oy);
+    int head = 0, queued = 0;     // head: a multiple of kGrp, so no group wraps around
+    // the entries the quadrant can reach, of the 64 queued next (saved by the
+    // forward up to the wave's last blended one at least), and this lane's
+    int b0 = start + ((hi - start) & ~63);
+    unsigned long long nh = W.hits[hits_at(start, tile, b0, wave)];
+    uint32_t nid = b0 + lane <= hi ? W.ids[b0 + lane] : 0u;
+    // lane (entry l >> 2, quarter l & 3) of half a wave fetches the next group's
+    // records while the group before is worked on; quarter 3 becomes the pair's slot
+    float4 rec = make_float4(0.f, 0.f, 0.f, 0.f);
+    uint32_t goff = 0;
+    int pos_next = 0;
+    auto fetch = [&](int at, int n) {
+      at = at >= kBwdQueue ? at - kBwdQueue : at;
+      if (lane < 4 * kGrp) {
+        if (n < kGrp) {           // entries past the last: opacity 0
+          rec = make_float4(0.f, 0.f, 0.f, 0.f);
+          pos_next = 0;
         }
-        const float dy = (r0.y - qyr) + r0.w;
-        v[0] = a1;
-        v[1] = dy * a0;
-        v[2] = a2;
-        v[3] = dy * a1;
-        v[4] = dy * v[1];
-        if (NV == 10) v[5] = a0;
-      } else {
+        if ((lane >> 2) < n) {
+          const uint2 q = s_queue[at + (lane >> 2)];
+          rec = reinterpret_cast<const float4*>(W.rec + q.x)[lane & 3];
+          if ((lane & 3) == 3) goff = W.goff[q.x];
+          pos_next = (int)q.y;
+        }
+      }
+    };
+    bool first = true;
+    for (;;) {
+      // two groups ahead, so that the next one's records can be fetched
+      while (queued < 2 * kGrp && b0 >= start) {
+        bool hit = b0 + lane <= hi && ((nh >> lane) & 1ull) != 0;
+        unsigned long long fm = 0;
+        if (FRAG && hit) {
+          fm = W.fmask[(int64_t)(b0 + lane) * 4 + wave];
+          hit = fm != 0;              // no lane of the wave blended it
+        }
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(hit);
+        const int found = __popcll(m);
+        if (hit) {                    // in falling list order
+          int at = head + queued + found - 1 - (int)lane_rank(m);
+          at -= at >= kBwdQueue ? kBwdQueue : 0;
+          s_queue[at] = make_uint2(nid, (uint32_t)(b0 + lane));
+          if (FRAG) s_fm[at] = fm;
+        }
+        queued += found;
+        b0 -= 64;
+        if (b0 >= start) {
+          nh = W.hits[hits_at(start, tile, b0, wave)];
+          nid = W.ids[b0 + lane];
+        }
+      }
+      if (queued == 0) break;
+      const int n = min(kGrp, queued);
+      wave_lds_order();
+      if (first) fetch(head, n);
+      first = false;
+      if (lane < 4 * kGrp) {
+        const int part = lane & 3;
+        s_rec[lane] = COLS == 0 && part == 1 ? conic_log2(rec) : rec;
+        // the pair's slot: Gaussian-major, then row-major in its tile rectangle
+        if (part == 3)
+          *reinterpret_cast<int2*>(s_tab + (lane >> 2) * kTab + 3 * COLS + 2) =
+              make_int2(pos_next, (int)(goff - __float_as_uint(rec.x)) +
+                                      lty * __float_as_int(rec.y) + ltx);
+      }
+      if (queued > n) fetch(head + kGrp, min(kGrp, queued - n));
+      wave_lds_order();
+      const float4 re = s_rec[4 * ge];         // this lane's entry in the table and in pass 2
+      if (COLS > 0) {
+        // an entry's columns and rows prow, prow + 8 (see k_raster_fwd)
+        float* t = s_tab + ge * kTab;
+        const float4 k4 = conic_log2(s_rec[4 * ge + 1]);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float4 p = *reinterpret_cast<const float4*>(
-              pair_base + ((q & 1) ? r_off1 : r_off0) + 256 * (q >> 1));
+        for (int i = 0; i < COLS; i += 8) {
+          t[prow + i] = (re.x - (qx + (float)(prow + i))) + re.z;
+          const float dy = (re.y - (qy + (float)(prow + i))) + re.w;
+          *reinterpret_cast<float2*>(t + COLS + 2 * (prow + i)) =
+              make_float2(k4.y * dy, (k4.z * dy) * dy);
+        }
+        if (prow == 0) *reinterpret_cast<float2*>(t + 3 * COLS) = make_float2(k4.x, k4.w);
+        wave_lds_order();
+      }
+      // ---- pass 1
+      unsigned some = 0;            // the entries some pixel blended
 #pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            const int col = 2 * q + j;
-            const float n = j ? p.z : p.x, w = j ? p.w : p.y;
-            const float2 xy = s_xy[(8 * gr + col) % (IRR ? 64 : 1)];
-            const float dx = (r0.x - xy.x) + r0.z, dy = (r0.y - xy.y) + r0.w;
-            const float nx = n * dx, ny = n * dy;
+      for (int j = 0; j < kGrp; j += 4) {
+        // (colour, depth) of four entries dotted with the upstream gradient
+        f32x4 cg4 = {0.f, 0.f, 0.f, 0.f};
+        const float4 col = s_rec[4 * (j + (lane & 3)) + 2];
+        cg4 = __builtin_amdgcn_mfma_f32_4x4x1f32(col.x, g0, cg4, 0, 0, 0);
+        cg4 = __builtin_amdgcn_mfma_f32_4x4x1f32(col.y, g1, cg4, 0, 0, 0);
+        cg4 = __builtin_amdgcn_mfma_f32_4x4x1f32(col.z, g2, cg4, 0, 0, 0);
+        cg4 = __builtin_amdgcn_mfma_f32_4x4x1f32(col.w, gD, cg4, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int k = j + i;
+          Frag f;
+          bool contrib, clamped;
+          if (FRAG) {
+            const unsigned long long bm = k < n ? s_fm[head + k] : 0ull;
+            fcur -= (uint32_t)__popcll(bm);
+            contrib = ((bm >> lane) & 1ull) != 0;
+            float2 rec = make_float2(0.f, 1.f);
+            if (contrib) rec = W.fdata[fbase + fcur + lane_rank(bm)];
+            f.alpha = fabsf(rec.x);
+            f.om = rec.y;
+            clamped = rec.x < 0.f;
+          } else {
+            float raw;
+            int pos;
+            if (COLS > 0) {
+              const float dx = t_x[k * kTab];
+              const float2 y = t_y[k * (kTab / 2)];
+              const float4 ao = *reinterpret_cast<const float4*>(s_tab + k * kTab + 3 * COLS);
+              const float p2 = __builtin_fmaf(dx, __builtin_fmaf(ao.x, dx, y.x), y.y);
+              f.e = __builtin_amdgcn_exp2f(p2);
+              raw = ao.y * f.e;
+              pos = __float_as_int(ao.z);
+              f.alpha = fminf(kAlphaMax, raw);
+              f.om = fmaxf(1.f - kAlphaMax, __builtin_fmaf(-ao.y, f.e, 1.f));
+            } else {
+              const float4 k4 = s_rec[4 * k + 1];
+              f = frag_alpha(s_rec[4 * k], k4, pxf, pyf);
+              raw = k4.w * f.e;
+              pos = __float_as_int(s_tab[k * kTab + 3 * COLS + 2]);
+            }
+            // entries at or before `last` lie before the pixel's stop
+            contrib = pos <= last && !(f.alpha < kAlphaMin);
+            clamped = raw > kAlphaMax;
+          }
+          some |= __builtin_amdgcn_ballot_w64(contrib) != 0 ? 1u << k : 0u;
+          // lanes that did not blend it take alpha = 0 and 1 - alpha = 1, so
+          // every update below leaves their state unchanged and their
+          // gradients exactly zero (selects, not branches)
+          const float al = contrib ? f.alpha : 0.f;
+          const float om = contrib ? f.om : 1.f;
+          const float rom = __builtin_amdgcn_rcpf(om);
+          const float Tj = Tc * rom;                     // T before this fragment (rcp(1) = 1)
+          const float w = al * Tj;
+          const float cg = cg4[i];
+          // dL/dalpha_j = T_j (c_j - S_j) . g + T_final gA / (1 - alpha_j)
+          const float dla = GA ? __builtin_fmaf(Tj, cg - SG, gAT * rom) : Tj * (cg - SG);
+          SG = __builtin_fmaf(al, cg, om * SG);
+          Tc = Tj;
+          // the clamp alpha = 0.99 has no gradient to o or to the power
+          const bool live = contrib && !clamped;
+          const float nk = live ? -(f.alpha * dla) : 0.f;   // -dL/dpower
+          wr[k * kRowWords] = nk;
+          wr[(kGrp + k) * kRowWords] = w;
+        }
+      }
+      wave_lds_order();
+      if (some) {
+        // ---- pass 2
+        // w g over four pixels, of entries 0 to 3 and 4 to 7: lane = (pixels, value);
+        // pose only: over the row instead, in place of the sum of n
+        f32x4 wa = {0.f, 0.f, 0.f, 0.f}, wb = {0.f, 0.f, 0.f, 0.f};
+        if (NV == 10) {
+          const float4 p = *reinterpret_cast<const float4*>(rw);
+          const float4 q = *reinterpret_cast<const float4*>(rw + 4 * kRowWords);
+          wa = __builtin_amdgcn_mfma_f32_4x4x1f32(p.x, G[0], wa, 0, 0, 0);
+          wb = __builtin_amdgcn_mfma_f32_4x4x1f32(q.x, G[0], wb, 0, 0, 0);
+          wa = __builtin_amdgcn_mfma_f32_4x4x1f32(p.y, G[1], wa, 0, 0, 0);
+          wb = __builtin_amdgcn_mfma_f32_4x4x1f32(q.y, G[1], wb, 0, 0, 0);
+          wa = __builtin_amdgcn_mfma_f32_4x4x1f32(p.z, G[2], wa, 0, 0, 0);
+          wb = __builtin_amdgcn_mfma_f32_4x4x1f32(q.z, G[2], wb, 0, 0, 0);
+          wa = __builtin_amdgcn_mfma_f32_4x4x1f32(p.w, G[3], wa, 0, 0, 0);
+          wb = __builtin_amdgcn_mfma_f32_4x4x1f32(q.w, G[3], wb, 0, 0, 0);
+        }
+        // n times the offsets from the Gaussian's centre: lane = (entry, row)
+        float v[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        float nn[8];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const float4 q = *reinterpret_cast<const float4*>(rn + 4 * u);
+          nn[4 * u] = q.x; nn[4 * u + 1] = q.y; nn[4 * u + 2] = q.z; nn[4 * u + 3] = q.w;
+        }
+        float a0 = 0.f, a1 = 0.f, a2 = 0.f;      // sums of n, n dx, n dx^2 along the row
+        if (G8) {
+          float dxs[8];
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            const float4 q = *reinterpret_cast<const float4*>(s_tab + ge * kTab + 4 * u);
+            dxs[4 * u] = q.x; dxs[4 * u + 1] = q.y; dxs[4 * u + 2] = q.z; dxs[4 * u + 3] = q.w;
+          }
+          a0 = nn[0];
+          a1 = nn[0] * dxs[0];
+          a2 = a1 * dxs[0];
+#pragma unroll
+          for (int i = 1; i < 8; ++i) {
+            const float nd = nn[i] * dxs[i];
+            a0 += nn[i];
+            a1 += nd;
+            a2 = __builtin_fmaf(nd, dxs[i], a2);
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const float2 xy = s_xy[(8 * prow + i) % (IRR ? 64 : 1)];
+            const float dx = (re.x - xy.x) + re.z, dy = (re.y - xy.y) + re.w;
+            const float nx = nn[i] * dx, ny = nn[i] * dy;
             v[0] += nx;
             v[1] += ny;
             v[2] = __builtin_fmaf(nx, dx, v[2]);
             v[3] = __builtin_fmaf(nx, dy, v[3]);
             v[4] = __builtin_fmaf(ny, dy, v[4]);
-            if (NV == 10) {
-              v[5] += n;
-#pragma unroll
-              for (int t = 0; t < 3; ++t) v[6 + t] = __builtin_fmaf(w, G[col][t % NG], v[6 + t]);
-            }
-            v[NV - 1] = __builtin_fmaf(w, G[col][NG - 1], v[NV - 1]);
+            v[5] += nn[i];
           }
         }
+        if (G8) {
+          const float dy = (re.y - (qy + (float)prow)) + re.w;
+          v[0] = a1;
+          v[1] = dy * a0;
+          v[2] = a2;
+          v[3] = dy * a1;
+          v[4] = dy * v[1];
+          v[5] = a0;
+        }
+        if (NV == 6) {
+          const float4 p = *reinterpret_cast<const float4*>(rw);
+          const float4 q = *reinterpret_cast<const float4*>(rw + 4);
+          const float ww[8] = {p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w};
+          v[5] = ww[0] * G[0];
+#pragma unroll
+          for (int i = 1; i < 8; ++i) v[5] = __builtin_fmaf(ww[i], G[i % (NV == 10 ? 4 : 8)], v[5]);
+        }
+        float x[3];
+        rows8_reduce_scatter<6>(v, x);
+        // the w sums over the 16 groups of pixels (NV = 10): lane bits 5 to 2
+        float r[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] = swap32_add(wa[i], wb[i]);
+        float y0 = swap16_add(r[0], r[1]), y1 = swap16_add(r[2], r[3]);
+        y0 += dpp_f<kDppRowRor8, 0xf, true>(y0);
+        y1 += dpp_f<kDppRowRor8, 0xf, true>(y1);
+        y0 += dpp_f<kDppRowRor4, 0xf, true>(y0);
+        y1 += dpp_f<kDppRowRor4, 0xf, true>(y1);
+        const float y = lane & 8 ? y1 : y0;
+        {
+          // lane (h, p, bit 3, entry ge): sum 3 h + p; with bit 3: 3 h + 2, and the flag
+          const uint32_t pair = __float_as_uint(s_tab[ge * kTab + 3 * COLS + 3]);
+          const bool has = ((some >> ge) & 1u) && pair < cap;
+          const float z = lane & 8 ? x[1] : x[0];
+          if (has && sum_lane) sum_dst[(int64_t)pair * (4 * NV)] = z;
+          if (has && flag_lane) W.live[(int64_t)pair * 4 + wave] = 1;
+        }
+        if (NV == 10) {
+          // lane (h, p, bit 3, bit 2, value) of the w sums
+          const uint32_t pair = __float_as_uint(s_tab[we * kTab + 3 * COLS + 3]);
+          if (((some >> we) & 1u) && pair < cap && w_lane) w_dst[(int64_t)pair * (4 * NV)] = y;
+        }
+        wave_lds_order();
       }
-      float x[3];
-      rows8_reduce_scatter<NV>(v, x);
-      if (!(lane & 8) && ge < slot && (int64_t)s_slot[ke] < W.cap) {
-        // slot layout: quarter h = lane / 16 holds its two (one) paired totals
-        // together, the unpaired totals of the two halves follow (sum_at)
-        const int64_t at = ((int64_t)s_slot[ke] * 4 + wave) * NV;
-        float* dst = W.partial + at;
-        const int h = lane >> 4;
-        if (NV == 10)
-          *reinterpret_cast<float2*>(dst + 2 * h) = make_float2(x[0], x[1]);
-        else
-          dst[h] = x[0];
-        if (!(h & 1)) dst[NV - 2 + (h >> 1)] = NV == 10 ? x[2] : x[1];
-        if (h == 0) W.live[(int64_t)s_slot[ke] * 4 + wave] = 1;
-      }
-      wave_lds_order();
-      slot = 0;
-      kpack = 0;
+      queued -= n;
+      head = head == kBwdQueue - kGrp ? 0 : head + kGrp;
     }
-  }
+  };
+  if (!IRR || (!BAL && (S.sub_sx | S.sub_sy) == 0))
+    walk(std::integral_constant<int, 8>{});
+  else if (!BAL && S.sub_sx <= 1 && S.sub_sy <= 1)
+    walk(std::integral_constant<int, 16>{});
+  else
+    walk(std::integral_constant<int, 0>{});
 }
 
 }  // namespace
@@ -815,9 +961,11 @@ static int raster_grid(const Batch& b) { return 32 * ((b.t_total + 7) / 8); }
 // the L2 better in tile order.  Measured, backward in tile order and by work:
 // 836 tiles (1200x680 at 1 in 4, 500k) 136 and 141 us; 1200 tiles (640x480 /
 // 100k) 84 and 71 us; 3225 tiles (1200x680 / 300k) 165 and 146 us.
+constexpr int kFewTiles = 1024;
+
 static WsPtrs raster_order(const Batch& b, const WsPtrs& w) {
   WsPtrs r = w;
-  if (b.t_total <= 1024) r.order = nullptr;
+  if (b.t_total <= kFewTiles) r.order = nullptr;
   return r;
 }
 
@@ -835,27 +983,38 @@ hipError_t launch_raster_fwd(const Batch& b, const WsPtrs& w0, bool stats, bool 
   return hipGetLastError();
 }
 
+// Waves a SIMD that the backward's registers are kept to: four where all waves
+// are on the chip at once then (up to 1024 tiles; a fifth would not be used),
+// otherwise five, at the price of a few spilled registers.  Measured with four
+// and five: 836 tiles (1200x680 at 1 in 4, 500k) 120 and 128 us; six frames with
+// downsampled ones among them (10.5k tiles) 297 and 284 us.  All gradients of
+// downsampled frames need 124 registers and stay at four.
 template <int NV, bool GA>
 static void raster_bwd_variant(const Batch& b, const WsPtrs& w, bool frags, bool bal, int grid,
                                hipStream_t st) {
-  const bool one = b.n_sessions == 1, irr = b.any_sub != 0;
+  const bool one = b.n_sessions == 1, irr = b.any_sub != 0, few = b.t_total <= kFewTiles;
   if (frags) {
     if (bal)
-      k_raster_bwd<NV, GA, true, true, false, true><<<grid, 64, 0, st>>>(b, w);
+      k_raster_bwd<NV, GA, true, true, false, true, 4><<<grid, 64, 0, st>>>(b, w);
     else
-      k_raster_bwd<NV, GA, true, false, false, true><<<grid, 64, 0, st>>>(b, w);
+      k_raster_bwd<NV, GA, true, false, false, true, 4><<<grid, 64, 0, st>>>(b, w);
   } else if (bal) {
-    k_raster_bwd<NV, GA, false, true, false, true><<<grid, 64, 0, st>>>(b, w);
+    k_raster_bwd<NV, GA, false, true, false, true, 4><<<grid, 64, 0, st>>>(b, w);
   } else if (irr) {
-    if (one)
-      k_raster_bwd<NV, GA, false, false, true, true><<<grid, 64, 0, st>>>(b, w);
+    constexpr int EU = NV == 10 ? 4 : 5;
+    if (one && few)
+      k_raster_bwd<NV, GA, false, false, true, true, 4><<<grid, 64, 0, st>>>(b, w);
+    else if (one)
+      k_raster_bwd<NV, GA, false, false, true, true, EU><<<grid, 64, 0, st>>>(b, w);
     else
-      k_raster_bwd<NV, GA, false, false, false, true><<<grid, 64, 0, st>>>(b, w);
+      k_raster_bwd<NV, GA, false, false, false, true, EU><<<grid, 64, 0, st>>>(b, w);
   } else {
-    if (one)
-      k_raster_bwd<NV, GA, false, false, true, false><<<grid, 64, 0, st>>>(b, w);
+    if (one && few)
+      k_raster_bwd<NV, GA, false, false, true, false, 4><<<grid, 64, 0, st>>>(b, w);
+    else if (one)
+      k_raster_bwd<NV, GA, false, false, true, false, 5><<<grid, 64, 0, st>>>(b, w);
     else
-      k_raster_bwd<NV, GA, false, false, false, false><<<grid, 64, 0, st>>>(b, w);
+      k_raster_bwd<NV, GA, false, false, false, false, 5><<<grid, 64, 0, st>>>(b, w);
   }
 }
 

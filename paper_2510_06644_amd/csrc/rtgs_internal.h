@@ -102,7 +102,7 @@ struct WsLayout {
   uint64_t cnt;         // uint32[N]: tiles touched
   uint64_t goff;        // uint32[N]: first slot of the Gaussian's pairs, Gaussian-major
   uint64_t zkey;        // uint32[N]: depth bits of the Gaussian's sort key (projection)
-  uint64_t grad2d;      // float[N][10]: the pair sums of each Gaussian added up (order: sum_at)
+  uint64_t grad2d;      // float[N][10]: the pair sums of each Gaussian added up
   uint64_t pose_part;   // double[B][16]: per-block view-matrix gradient partial sums
   uint64_t chunk_total; // uint32[C + 1]: pairs per chunk
   uint64_t chunk_off;   // uint32[C + 1]: exclusive scan of chunk_total
@@ -155,15 +155,6 @@ struct alignas(64) GaussRec {
   float4 ext;     // tile rectangle as bits: y0 * width + x0, width (int); t = 2 ln(255 o); 0
 };
 static_assert(sizeof(GaussRec) == 64, "one line per record");
-
-// Place in a slot of partial (and in grad2d) of sum v of the raster backward
-// (k_raster_bwd; NV sums, H = NV / 2): what rows8_reduce_scatter leaves in a
-// quarter wave is stored together, the last sum of each half at the end.
-constexpr int sum_at(int nv, int v) {
-  const int h = nv / 2, half = v / h, i = v % h;
-  if (i == h - 1) return nv - 2 + half;
-  return (h / 2) * (2 * half + (i & 1)) + (i >> 1);
-}
 
 // Pointers derived from a workspace.
 struct WsPtrs {
@@ -412,6 +403,7 @@ constexpr int kDppRowShr1 = 0x111;
 constexpr int kDppRowShr2 = 0x112;
 constexpr int kDppRowShr4 = 0x114;
 constexpr int kDppRowShr8 = 0x118;
+constexpr int kDppRowRor4 = 0x124;
 constexpr int kDppRowRor8 = 0x128;
 
 template <int CTRL, int ROW_MASK, bool BOUND_ZERO>
