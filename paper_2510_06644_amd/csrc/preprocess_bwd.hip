@@ -285,8 +285,15 @@ __device__ __forceinline__ void merged_sums(const WsPtrs& W, int c, int64_t gid,
     for (int i = 0; i < NV; ++i) m[i] += W.edge[(int64_t)w * 2 * 10 + i];
 }
 
-template <int NV, bool ADAM, bool ONE>
-__global__ __launch_bounds__(kGaussPerBlock) void k_gauss_bwd(Batch B, WsPtrs W, int flags) {
+// Bound by memory latency behind few waves (float64 registers), so what a call
+// does not write is not compiled into its kernel (pose only 162 -> 114
+// registers), and the pose's partials are summed by lane swaps instead of
+// shuffles through LDS: pose only 1200x680 / 500k 25 -> 16 us, six served frames
+// 74 -> 34 us; all gradients and the pose 34 -> 32 us (kept to three waves a
+// SIMD, which spills, 36); Adam fused, 300k: 32 us, the rate of a copy.
+template <int NV, bool ADAM, bool ONE, bool SCORE, bool POSE>
+__global__ __launch_bounds__(kGaussPerBlock) __attribute__((amdgpu_waves_per_eu(NV == 6 ? 4 : POSE ? 2 : 3)))
+void k_gauss_bwd(Batch B, WsPtrs W, int flags) {
   __shared__ double s_red[kGaussPerBlock / 64][12];
   const int s = ONE ? 0 : find_session(session_table(B), B.n_sessions, (int)blockIdx.x,
                                        [](const SessionDev& x) { return x.block_base; });
@@ -294,11 +301,10 @@ __global__ __launch_bounds__(kGaussPerBlock) void k_gauss_bwd(Batch B, WsPtrs W,
   const int li0 = ((int)blockIdx.x - S.block_base) * kGaussPerBlock;
   // ---- projection backward, one thread per Gaussian
   const int li = li0 + (int)threadIdx.x;
-  const bool want_map = (flags & RTGS_GRAD_MAP) != 0;
+  constexpr bool want_map = NV == 10;
   const bool want_cov = (flags & RTGS_GRAD_COV3D) != 0 && S.g_cov3d != nullptr;
   // score inputs only (dL/dmu, dL/dSigma) on the pose-only raster path
-  const bool want_score = !want_map && (flags & RTGS_GRAD_SCORE) != 0 && S.g_means != nullptr &&
-                          S.g_cov3d != nullptr;
+  const bool want_score = SCORE && S.g_means != nullptr && S.g_cov3d != nullptr;
   double pose[12] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};   // dL/dW (9), dL/dt (3)
   if (li < S.n) {
     const int gid = S.gauss_base + li;
@@ -531,13 +537,19 @@ __global__ __launch_bounds__(kGaussPerBlock) void k_gauss_bwd(Batch B, WsPtrs W,
     }
   }
   // block partial of the pose gradient: wave shuffles, then the 4 waves in LDS
-  // (the flag is the launch's, so the whole workgroup leaves together)
-  if (!(flags & RTGS_GRAD_POSE)) return;
+  if (!POSE) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int k = 0; k < 12; ++k) {
-    double v = pose[k];
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    if (lane == 0) s_red[wave][k] = v;
+#pragma unroll
+  for (int k = 0; k < 12; k += 6) {
+    const double v[6] = {pose[k],     pose[k + 1], pose[k + 2],
+                         pose[k + 3], pose[k + 4], pose[k + 5]};
+    double x[2];
+    wave_sums<6>(v, x);
+    if ((lane & 15) == 15) {
+      const int h = lane >> 5, p = (lane >> 4) & 1;
+      s_red[wave][k + 3 * h + p] = x[0];
+      if (p == 0) s_red[wave][k + 3 * h + 2] = x[1];
+    }
   }
   __syncthreads();
   if (threadIdx.x < 12) {
@@ -549,23 +561,47 @@ __global__ __launch_bounds__(kGaussPerBlock) void k_gauss_bwd(Batch B, WsPtrs W,
 
 // One workgroup per session: fixed-order sum of its block partials into the
 // view-matrix gradient, and the pose (left-perturbation) gradient from it.
-__global__ __launch_bounds__(256) void k_pose_reduce(Batch B, WsPtrs W) {
-  __shared__ double s_acc[256][12];
+// One workgroup a session: 1024 threads so that the blocks' partials are in
+// flight together, then lane swaps and one pass through LDS (500k Gaussians:
+// 256 threads and a tree in LDS 10.5 -> 9 us; 100k 5.8 -> 4.7).
+constexpr int kReduceThreads = 1024;
+
+__global__ __launch_bounds__(kReduceThreads) void k_pose_reduce(Batch B, WsPtrs W) {
+  __shared__ double s_acc[kReduceThreads / 64][12];
   const SessionDev& S = session_of(B, blockIdx.x);
   const int b0 = S.block_base;
   const int b1 = (blockIdx.x + 1 < (unsigned)B.n_sessions)
                      ? session_of(B, blockIdx.x + 1).block_base
                      : B.b_total;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   double acc[12] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  for (int b = b0 + (int)threadIdx.x; b < b1; b += 256)
-    for (int k = 0; k < 12; ++k) acc[k] += W.pose_part[(int64_t)b * 16 + k];
-  for (int k = 0; k < 12; ++k) s_acc[threadIdx.x][k] = acc[k];
-  __syncthreads();
-  for (int off = 128; off >= 1; off >>= 1) {
-    if ((int)threadIdx.x < off)
-      for (int k = 0; k < 12; ++k) s_acc[threadIdx.x][k] += s_acc[threadIdx.x + off][k];
-    __syncthreads();
+  for (int b = b0 + (int)threadIdx.x; b < b1; b += kReduceThreads) {
+    const double2* p = reinterpret_cast<const double2*>(W.pose_part + (int64_t)b * 16);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      const double2 v = p[k];
+      acc[2 * k] += v.x;
+      acc[2 * k + 1] += v.y;
+    }
   }
+#pragma unroll
+  for (int k = 0; k < 12; k += 6) {
+    const double v[6] = {acc[k], acc[k + 1], acc[k + 2], acc[k + 3], acc[k + 4], acc[k + 5]};
+    double x[2];
+    wave_sums<6>(v, x);
+    if ((lane & 15) == 15) {
+      const int h = lane >> 5, p = (lane >> 4) & 1;
+      s_acc[wave][k + 3 * h + p] = x[0];
+      if (p == 0) s_acc[wave][k + 3 * h + 2] = x[1];
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < 12) {
+    double t = 0;
+    for (int q = 0; q < kReduceThreads / 64; ++q) t += s_acc[q][threadIdx.x];
+    s_acc[0][threadIdx.x] = t;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
     const double* g = s_acc[0];        // dL/dW row-major (9), dL/dt (3)
     if (S.g_viewmat)
@@ -593,12 +629,22 @@ __global__ __launch_bounds__(256) void k_pose_reduce(Batch B, WsPtrs W) {
 
 }  // namespace
 
-template <int NV, bool ADAM>
+template <int NV, bool ADAM, bool SCORE, bool POSE>
 static void gauss_bwd(const Batch& b, const WsPtrs& w, int grad_flags, hipStream_t st) {
   if (b.n_sessions == 1)
-    k_gauss_bwd<NV, ADAM, true><<<b.b_total, kGaussPerBlock, 0, st>>>(b, w, grad_flags);
+    k_gauss_bwd<NV, ADAM, true, SCORE, POSE>
+        <<<b.b_total, kGaussPerBlock, 0, st>>>(b, w, grad_flags);
   else
-    k_gauss_bwd<NV, ADAM, false><<<b.b_total, kGaussPerBlock, 0, st>>>(b, w, grad_flags);
+    k_gauss_bwd<NV, ADAM, false, SCORE, POSE>
+        <<<b.b_total, kGaussPerBlock, 0, st>>>(b, w, grad_flags);
+}
+
+template <int NV, bool ADAM, bool SCORE>
+static void gauss_bwd(const Batch& b, const WsPtrs& w, int grad_flags, hipStream_t st) {
+  if (grad_flags & RTGS_GRAD_POSE)
+    gauss_bwd<NV, ADAM, SCORE, true>(b, w, grad_flags, st);
+  else
+    gauss_bwd<NV, ADAM, SCORE, false>(b, w, grad_flags, st);
 }
 
 hipError_t launch_preprocess_bwd(const Batch& b, const WsPtrs& w, int grad_flags, hipStream_t st,
@@ -618,15 +664,17 @@ hipError_t launch_preprocess_bwd(const Batch& b, const WsPtrs& w, int grad_flags
   if (b.b_total > 0) {
     Scope sc(tm, kStPreprocessBwd, st);
     if (grad_flags & RTGS_GRAD_ADAM)
-      gauss_bwd<10, true>(b, w, grad_flags, st);
+      gauss_bwd<10, true, false>(b, w, grad_flags, st);
     else if (grad_flags & RTGS_GRAD_MAP)
-      gauss_bwd<10, false>(b, w, grad_flags, st);
+      gauss_bwd<10, false, false>(b, w, grad_flags, st);
+    else if (grad_flags & RTGS_GRAD_SCORE)
+      gauss_bwd<6, false, true>(b, w, grad_flags, st);
     else
-      gauss_bwd<6, false>(b, w, grad_flags, st);
+      gauss_bwd<6, false, false>(b, w, grad_flags, st);
   }
   if ((grad_flags & RTGS_GRAD_POSE) && b.n_sessions > 0) {
     Scope sc(tm, kStPoseReduce, st);
-    k_pose_reduce<<<b.n_sessions, 256, 0, st>>>(b, w);
+    k_pose_reduce<<<b.n_sessions, kReduceThreads, 0, st>>>(b, w);
   }
   return hipGetLastError();
 }
