@@ -439,7 +439,8 @@ void launch_tile_sort(const Batch& b, const WsPtrs& w, hipStream_t st) {
     k_sort_tiles<true><<<grid, kSortThreads, 0, st>>>(b, w);
   else
     k_sort_tiles<false><<<grid, kSortThreads, 0, st>>>(b, w);
-  k_sort_big_tiles<<<b.t_total < 512 ? b.t_total : 512, kBigThreads, 0, st>>>(w);
+  if (b.n_total > kSmallKeys)            // no list is longer than that
+    k_sort_big_tiles<<<b.t_total < 512 ? b.t_total : 512, kBigThreads, 0, st>>>(w);
 }
 
 }  // namespace rtgs
