@@ -45,11 +45,7 @@ __global__ __launch_bounds__(kCompactBlock) void k_compact_scan(CompactArgs a, i
   const int b0 = min((int)threadIdx.x * per, nb), b1 = min(b0 + per, nb);
   uint32_t sum = 0;
   for (int b = b0; b < b1; ++b) sum += a.block_keep[b];
-  uint32_t x = sum;
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = __shfl_up(x, off, 64);
-    if (lane >= off) x += y;
-  }
+  const uint32_t x = wave_scan(sum);
   if (lane == 63) s_w[wave] = x;
   __syncthreads();
   uint32_t run = x - sum, total = 0;

@@ -226,11 +226,7 @@ __device__ uint32_t chunk_offsets(const ChunkIn& in, uint32_t* s_off, uint32_t* 
   for (int j = 0; j < kChunkRounds; ++j) {
     const int i = j * kBinThreads + (int)threadIdx.x;
     const uint32_t n = in.cnt[j];
-    uint32_t x = n;
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t y = __shfl_up(x, off, 64);
-      if (lane >= off) x += y;
-    }
+    const uint32_t x = wave_scan(n);
     if (lane == 63) s_wave[wave] = x;
     __syncthreads();
     uint32_t before = 0, tot = 0;
@@ -353,11 +349,7 @@ __device__ uint32_t block_scan_1024(const uint32_t* in, uint32_t* out, int n, ui
   const int beg = min(tid * per, n), end = min(beg + per, n);
   uint32_t sum = 0;
   for (int i = beg; i < end; ++i) sum += in[i];
-  uint32_t x = sum;                       // inclusive scan of the run sums in the wave
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = __shfl_up(x, off, 64);
-    if (lane >= off) x += y;
-  }
+  const uint32_t x = wave_scan(sum);
   if (lane == 63) part[wave] = x;
   __syncthreads();
   uint32_t before = 0, total = 0;
@@ -387,11 +379,7 @@ __device__ uint32_t block_scan_regs(uint32_t (&v)[P], uint32_t* part) {
   uint32_t sum = 0;
 #pragma unroll
   for (int i = 0; i < P; ++i) sum += v[i];
-  uint32_t x = sum;
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = __shfl_up(x, off, 64);
-    if (lane >= off) x += y;
-  }
+  const uint32_t x = wave_scan(sum);
   if (lane == 63) part[wave] = x;
   __syncthreads();
   uint32_t before = 0, total = 0;
@@ -595,11 +583,7 @@ __global__ __launch_bounds__(kBinThreads) void k_emit(Batch B, WsPtrs W) {
     uint32_t sum = 0;
 #pragma unroll
     for (int k = 0; k < kRunMax; ++k) sum += hv[k];
-    uint32_t x = sum;
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t y = __shfl_up(x, off, 64);
-      if (lane >= off) x += y;
-    }
+    const uint32_t x = wave_scan(sum);
     if (lane == 63) s_wave[wave] = x;
     __syncthreads();
     uint32_t run = x - sum;

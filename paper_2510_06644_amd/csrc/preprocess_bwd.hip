@@ -65,9 +65,11 @@ __device__ __forceinline__ void row_sums(float (&acc)[NV]) {
 // more than kItemsWave items, add its items.  A Gaussian that crosses a
 // window's end leaves a partial sum per window in `edge`, added up in window
 // order by the preprocessing backward.  Every sum is in a fixed order:
-// deterministic.  1200x680 / 300k: 42 us (8 lanes per Gaussian following its own
-// flags 72, all items staged in LDS first 47 to 57; kItemsWave 64 as 32, 128 three
-// more; the wave's sums in float 38, with a larger error than a slot by slot sum).
+// deterministic.  1200x680 / 300k: 38 us (42 with a store a value and the scan by
+// shuffles, and, of that form: 8 lanes per Gaussian following its own
+// flags 72, all items staged in LDS first 47 to 57, kItemsWave 64 no change, 128
+// three more, the next window's flags prefetched no change; the wave's sums in
+// float four less, with a larger error than a slot by slot sum).
 constexpr int kItemsWave = 32;
 
 // A pair's flag bytes (0 or 1) as four bits.
@@ -94,8 +96,13 @@ __device__ __forceinline__ void add_items(const float2* src, const uint16_t* lis
     for (int i = 0; i < NV / 2; ++i) {
       acc[2 * i] += v[i].x;
       acc[2 * i + 1] += v[i].y;
-      acc[2 * i] += two ? w[i].x : 0.f;
-      acc[2 * i + 1] += two ? w[i].y : 0.f;
+    }
+    if (two) {
+#pragma unroll
+      for (int i = 0; i < NV / 2; ++i) {
+        acc[2 * i] += w[i].x;
+        acc[2 * i + 1] += w[i].y;
+      }
     }
   }
 }
@@ -182,12 +189,7 @@ void k_merge(Batch B, WsPtrs W) {
     if (tid == 0) s_nbig = 0;
     // items before each pair: one scan for the two halves of the pairs
     const uint32_t have = (uint32_t)__popc(fa) | ((uint32_t)__popc(fb) << 16);
-    uint32_t x = have;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t y = __shfl_up(x, off, 64);
-      if (lane >= off) x += y;
-    }
+    const uint32_t x = wave_scan(have);
     if (lane == 63) s_w[wave] = x;
     __syncthreads();
     uint32_t before = 0, all = 0;
@@ -233,9 +235,18 @@ void k_merge(Batch B, WsPtrs W) {
       for (int i = 0; i < NV; ++i) acc[i] = 0.f;
       add_items<NV, 8>(src, s_item, lo, hi, sub, acc);
       row_sums<8, NV>(acc);
-      if (mine && sub == 7)
+      if (mine && sub == 7) {
+        if (g.y >= p0 && last <= p1) {
+          float2* dst = reinterpret_cast<float2*>(W.grad2d + (int64_t)g.x * 10);
 #pragma unroll
-        for (int i = 0; i < NV; ++i) merge_store(W, w, p0, p1, g.x, g.y, last, i, acc[i]);
+          for (int i = 0; i < NV / 2; ++i) dst[i] = make_float2(acc[2 * i], acc[2 * i + 1]);
+        } else {
+          double2* dst = reinterpret_cast<double2*>(W.edge + ((int64_t)w * 2 + (g.y < p0 ? 0 : 1)) * 10);
+#pragma unroll
+          for (int i = 0; i < NV / 2; ++i)
+            dst[i] = make_double2((double)acc[2 * i], (double)acc[2 * i + 1]);
+        }
+      }
     }
     __syncthreads();
     // the list's order depends on timing; each Gaussian's sum does not

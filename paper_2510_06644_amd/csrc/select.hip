@@ -71,11 +71,7 @@ __device__ __forceinline__ void pick_digit(const uint32_t* hist, uint32_t rank, 
     h[i] = hist[tid * kPer + i];
     sum += h[i];
   }
-  uint32_t x = sum;
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = __shfl_up(x, off, 64);
-    if (lane >= off) x += y;
-  }
+  const uint32_t x = wave_scan(sum);
   if (lane == 63) s[wave] = x;
   __syncthreads();
   uint32_t before = x - sum;

@@ -250,11 +250,7 @@ __device__ __forceinline__ void list_runs(const WsPtrs& W, const SessionDev& S, 
       cnt = nxt - off;
       src = W.chunk_off[S.chunk_base + c] + off;
     }
-    uint32_t x = cnt;
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t y = __shfl_up(x, o, 64);
-      if (lane >= o) x += y;
-    }
+    const uint32_t x = wave_scan(cnt);
     if (lane == 63) s_part[wave] = x;
     __syncthreads();
     uint32_t at = carry + x - cnt, tot = 0;
