@@ -93,8 +93,9 @@ def counter_record():
 # per-unit figures of the method (n Gaussians, p pairs): projection 56 B of
 # parameters in, the 64 B raster record, tile rectangle and count out (152 B);
 # the per-chunk histogram reads rectangle and count (20 B); emit 12 B and sort
-# 12 B per pair (key written and read, id written); merge 40 B per pair slot
-# read and 40 B per Gaussian written; the preprocessing backward with the map's
+# 12 B per pair (key written and read, id written); merge 40 B per pair and 40 B
+# per Gaussian written (the method's count: the kernel reads 40 B per quadrant of
+# a pair that has sums, and a 4-byte flag word per pair); the preprocessing backward with the map's
 # Adam update fused 392 B per Gaussian (rectangle 16 and merged 2D gradient 40
 # read, 14 parameters read and written with both Adam moments, 24 B each);
 # a separate Adam 28 B for each of 14 parameters per Gaussian.  Kernel names
@@ -105,13 +106,13 @@ HBM_STAGES = {
     "emit": (lambda n, p: 12 * p, ("k_emit<true>",)),
     "sort": (lambda n, p: 12 * p, ("k_sort_tiles<true>", "k_sort_big_tiles")),
     "merge": (lambda n, p: 40 * p + 40 * n, ("k_merge",)),
-    "preprocess_bwd": (lambda n, p: 392 * n, ("k_gauss_bwd<10, true, true>",)),
+    "preprocess_bwd": (lambda n, p: 392 * n, ("k_gauss_bwd<10, true, true, false, false>",)),
     "adam": (lambda n, p: 392 * n, ("k_adam",)),
 }
 # the raster variants the headline step launches (the statistics forward of
 # the work counts is another)
-VALU_STAGES = {"raster_fwd": ("k_raster_fwd<false, false, false, true>",),
-               "raster_bwd": ("k_raster_bwd<10, false, false, false, true>",)}
+VALU_STAGES = {"raster_fwd": ("k_raster_fwd<false, false, false, true, false>",),
+               "raster_bwd": ("k_raster_bwd<10, false, false, false, true, false, 5>",)}
 
 
 def _kernel_sum(rec, prefixes, field):
