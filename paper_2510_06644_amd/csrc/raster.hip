@@ -2,11 +2,10 @@
 // Step 4 (rendering backpropagation, the exact derivative of Eq. 3 that
 // Eqs. 4-5 sketch) for a batch of sessions sharing one tile space.
 //
-// One workgroup per 16x16 tile, 256 lanes = 4 wave64; each wave owns an 8x8
-// quadrant, so a Gaussian whose padded bounding box misses a quadrant is
-// skipped by that whole wave (a wave-uniform branch; the GPU counterpart of
-// the paper's 4x4 subtiles).  Gaussian records of the tile's depth-sorted
-// list are staged through LDS in batches of 256.
+// Lists are per 16x16 tile; a workgroup is one wave64 with an 8x8 quadrant of a
+// tile of its own, so a Gaussian whose ellipse misses a quadrant is skipped by
+// that whole wave (the GPU counterpart of the paper's 4x4 subtiles) and no wave
+// waits for another.
 //
 // Forward: per lane, alpha = min(0.99, o exp(power)); skip alpha < 1/255;
 // stop before T would fall below 1e-4; saves final T and the position of the
