@@ -112,7 +112,7 @@ HBM_STAGES = {
 # the raster variants the headline step launches (the statistics forward of
 # the work counts is another)
 VALU_STAGES = {"raster_fwd": ("k_raster_fwd<false, false, false, true, false>",),
-               "raster_bwd": ("k_raster_bwd<10, false, false, false, true, false, 5>",)}
+               "raster_bwd": ("k_raster_bwd<10, false, false, false, true, false, 6>",)}
 
 
 def _kernel_sum(rec, prefixes, field):

@@ -538,7 +538,7 @@ constexpr int bwd_tab_words(int cols) { return 3 * cols + 4; }
 // (Moments of n about the quadrant's middle, one 16x16x4 MFMA chain a group and
 // shifted to the centre in double, cost digits: narrow Gaussians cancel.)
 //
-// Measured at 1200x680 / 300k, NV = 10: 241 -> 136 us (109M -> 62M wave VALU
+// Measured at 1200x680 / 300k, NV = 10: 241 -> 133 us (109M -> 62M wave VALU
 // instructions, 121 us of issue; the rest the last waves draining); pose only at
 // 640x480 / 100k 109 -> 62 us, 1200x680 at 1 in 4 / 500k 135 -> 120 us.
 // Before, four waves of a tile met at two barriers per 64 entries, summed ten
@@ -984,10 +984,13 @@ hipError_t launch_raster_fwd(const Batch& b, const WsPtrs& w0, bool stats, bool 
 
 // Waves a SIMD that the backward's registers are kept to: four where all waves
 // are on the chip at once then (up to 1024 tiles; a fifth would not be used),
-// otherwise five, at the price of a few spilled registers.  Measured with four
-// and five: 836 tiles (1200x680 at 1 in 4, 500k) 120 and 128 us; six frames with
-// downsampled ones among them (10.5k tiles) 297 and 284 us.  All gradients of
-// downsampled frames need 124 registers and stay at four.
+// otherwise five, or six for all gradients, at the price of a few spilled
+// registers.  Measured with four and five: 836 tiles (1200x680 at 1 in 4, 500k)
+// 120 and 128 us; six frames with downsampled ones among them (10.5k tiles) 297
+// and 284 us.  All gradients with four, five and six: 1200x680 / 300k 145, 138 and
+// 133 us, / 500k 128 and 123, three mapped frames 213 and 202 (the latter two five
+// and six); pose only at 640x480 / 100k with five and six 62 and 63.  All
+// gradients of downsampled frames need 124 registers and stay at four.
 template <int NV, bool GA>
 static void raster_bwd_variant(const Batch& b, const WsPtrs& w, bool frags, bool bal, int grid,
                                hipStream_t st) {
@@ -1011,9 +1014,9 @@ static void raster_bwd_variant(const Batch& b, const WsPtrs& w, bool frags, bool
     if (one && few)
       k_raster_bwd<NV, GA, false, false, true, false, 4><<<grid, 64, 0, st>>>(b, w);
     else if (one)
-      k_raster_bwd<NV, GA, false, false, true, false, 5><<<grid, 64, 0, st>>>(b, w);
+      k_raster_bwd<NV, GA, false, false, true, false, NV == 10 ? 6 : 5><<<grid, 64, 0, st>>>(b, w);
     else
-      k_raster_bwd<NV, GA, false, false, false, false, 5><<<grid, 64, 0, st>>>(b, w);
+      k_raster_bwd<NV, GA, false, false, false, false, NV == 10 ? 6 : 5><<<grid, 64, 0, st>>>(b, w);
   }
 }
 
