@@ -109,7 +109,7 @@ struct rtgs_context {
   EventTimer timer;
   unsigned long long* d_scalars = nullptr;   // [0] largest pair count since last query,
                                              // [1] largest count that overflowed (or 0)
-  unsigned long long* h_scalars = nullptr;   // pinned: what rtgs_query took from d_scalars
+  unsigned long long* h_scalars = nullptr;   // after the ring: what rtgs_query took from d_scalars
   uint32_t* d_prune = nullptr;               // prune scratch
   SessionDev* h_ring = nullptr;              // pinned [kRing][RTGS_MAX_SESSIONS]
   hipEvent_t ring_ev[kRing] = {};
@@ -509,11 +509,12 @@ int32_t rtgs_create(rtgs_handle_t* out, int32_t device) {
   h->device = device;
   e = hipMalloc(&h->d_scalars, 64);
   if (e == hipSuccess) e = hipMemset(h->d_scalars, 0, 64);
-  if (e == hipSuccess) e = hipHostMalloc(&h->h_scalars, 64, hipHostMallocDefault);
   if (e == hipSuccess) e = hipMalloc(&h->d_prune, sizeof(uint32_t) * kPruneScratchWords);
   if (e == hipSuccess)
-    e = hipHostMalloc(&h->h_ring, sizeof(SessionDev) * RTGS_MAX_SESSIONS * kRing,
+    e = hipHostMalloc(&h->h_ring, sizeof(SessionDev) * RTGS_MAX_SESSIONS * kRing + 64,
                       hipHostMallocDefault);
+  if (e == hipSuccess)
+    h->h_scalars = reinterpret_cast<unsigned long long*>(h->h_ring + RTGS_MAX_SESSIONS * kRing);
   for (int i = 0; i < kRing && e == hipSuccess; ++i)
     e = hipEventCreateWithFlags(&h->ring_ev[i], hipEventDisableTiming);
   if (e != hipSuccess) {
@@ -531,7 +532,6 @@ int32_t rtgs_destroy(rtgs_handle_t h) {
     if (h->ring_ev[i]) (void)hipEventDestroy(h->ring_ev[i]);
   if (h->h_ring) (void)hipHostFree(h->h_ring);
   if (h->d_prune) (void)hipFree(h->d_prune);
-  if (h->h_scalars) (void)hipHostFree(h->h_scalars);
   if (h->d_scalars) (void)hipFree(h->d_scalars);
   delete h;
   return RTGS_OK;
