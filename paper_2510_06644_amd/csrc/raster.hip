@@ -800,7 +800,9 @@ void k_raster_bwd(Batch B, WsPtrs W) {
           const float rom = __builtin_amdgcn_rcpf(om);
           const float Tj = Tc * rom;                     // T before this fragment (rcp(1) = 1)
           const float w = al * Tj;
-          const float cg = cg4[i];
+          // (0 where the lane did not blend it: a colour or depth that is not finite
+          // reaches the pixels that blended it alone)
+          const float cg = contrib ? cg4[i] : 0.f;
           // dL/dalpha_j = T_j (c_j - S_j) . g + T_final gA / (1 - alpha_j)
           const float dla = GA ? __builtin_fmaf(Tj, cg - SG, gAT * rom) : Tj * (cg - SG);
           SG = __builtin_fmaf(al, cg, om * SG);
