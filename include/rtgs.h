@@ -80,6 +80,15 @@ extern "C" {
                                      writes this forward's walked entries to
                                      lane_work_out; render_fwd_batched only   */
 
+#define RTGS_FWD_COMPACT_SUMS 64  /* workspace sizes only: room for a quarter of
+                                     the pairs' gradient sums at a time (40
+                                     bytes a pair of capacity instead of 160).
+                                     A backward whose ws_bytes has not room for
+                                     all of them takes the pairs in four
+                                     passes: the same gradients bit for bit,
+                                     slower.  Without effect together with
+                                     RTGS_FWD_SAVE_FRAGMENTS                  */
+
 /* ---- render_bwd flags ---- */
 #define RTGS_GRAD_POSE        1   /* write g_pose6 and/or g_viewmat            */
 #define RTGS_GRAD_MAP         2   /* write the five per-Gaussian gradients     */

@@ -120,8 +120,15 @@ struct rtgs_context {
 
 namespace rtgs {
 
-WsLayout make_layout(const Counts& c, int64_t cap, bool frags) {
+// The backward of a compact workspace takes the pairs in this many passes, each
+// with room for the sums of a window past its end.
+constexpr int kPasses = 4;
+
+WsLayout make_layout(const Counts& c, int64_t cap, bool frags, bool compact) {
   WsLayout L{};
+  L.sum_span = (cap + kPasses - 1) / kPasses;
+  if (L.sum_span + kWindow >= cap) compact = false;      // nothing to save
+  if (!compact) L.sum_span = cap;
   uint64_t off = 0;
   auto take = [&](uint64_t bytes) {
     const uint64_t at = off;
@@ -153,17 +160,20 @@ WsLayout make_layout(const Counts& c, int64_t cap, bool frags) {
   L.big_tiles = take(4 * (t + 1));
   L.ids = take(4 * (uint64_t)cap);
   L.hits = take(32 * ((uint64_t)cap / 64 + t + 1));
-  L.partial = take(4 * 4 * 10 * (uint64_t)cap + 2 * kAlign);
-  // the keys are dead once the lists are sorted, the sums live from the raster
-  // backward to the merge: they share memory
-  L.keys = L.partial;
-  L.keys_tm = L.partial + align_up(8 * (uint64_t)cap);
   L.live = take(4 * (uint64_t)cap);
   L.state_t = take(4 * (uint64_t)c.px_total);
   L.state_last = take(4 * (uint64_t)c.px_total);
   L.lane_perm = take(256 * t);
   L.order_n = take(4 * 8 * kOrderClasses);
   L.order = take(4 * 8 * kOrderClasses * 4 * ((t + 7) / 8));
+  // after what a forward leaves for its backward, so that all of that lies at the
+  // same place in a full and in a compact workspace
+  const uint64_t room = (uint64_t)(compact ? L.sum_span + kWindow : cap);
+  L.partial = take(4 * 4 * 10 * room + 2 * kAlign);
+  // the keys are dead once the lists are sorted, the sums live from the raster
+  // backward to the merge: they share memory
+  L.keys = L.partial;
+  L.keys_tm = L.partial + align_up(8 * (uint64_t)cap);
   if (frags) {
     L.fmask = take(8 * 4 * (uint64_t)cap);
     L.fcount = take(4 * 4 * t);
@@ -218,6 +228,7 @@ WsPtrs ws_ptrs(void* ws, const WsLayout& L) {
     w.fdata = reinterpret_cast<float2*>(base + L.fdata);
   }
   w.cap = L.cap;
+  w.sum_n = w.sum_span = (uint32_t)L.cap;
   return w;
 }
 
@@ -471,7 +482,9 @@ int32_t prepare(rtgs_handle_t h, const rtgs_session* ss, int32_t ns, void* ws, u
   r = geometry(n.data(), wd.data(), ht.data(), ns, g, js.data());
   if (r) return r;
   if (!ws) return fail(RTGS_ERR_INVALID_ARG, "null workspace");
+  // the sums of all pairs at once where the workspace has room for them
   L = make_layout(g, cap, frags);
+  if (ws_bytes < L.total && !frags) L = make_layout(g, cap, false, true);
   if (ws_bytes < L.total)
     return fail(RTGS_ERR_WORKSPACE, "workspace %llu bytes < required %llu",
                 (unsigned long long)ws_bytes, (unsigned long long)L.total);
@@ -479,6 +492,11 @@ int32_t prepare(rtgs_handle_t h, const rtgs_session* ss, int32_t ns, void* ws, u
     return fail(RTGS_ERR_INVALID_ARG, "workspace not 256-byte aligned");
   w = ws_ptrs(ws, L);
   return RTGS_OK;
+}
+
+WsLayout layout_for(const Counts& g, int64_t cap, int32_t flags) {
+  const bool frags = (flags & RTGS_FWD_SAVE_FRAGMENTS) != 0;
+  return make_layout(g, cap, frags, (flags & RTGS_FWD_COMPACT_SUMS) && !frags);
 }
 
 rtgs_session single(const rtgs_gaussians* g, const rtgs_camera* cam, const uint8_t* pmask) {
@@ -546,7 +564,7 @@ int32_t rtgs_workspace_size_batched(const int32_t* n, const int32_t* width, cons
   Counts g;
   r = geometry(n, width, height, n_sessions, g);
   if (r) return r;
-  *bytes = make_layout(g, pair_capacity, (flags & RTGS_FWD_SAVE_FRAGMENTS) != 0).total;
+  *bytes = layout_for(g, pair_capacity, flags).total;
   return RTGS_OK;
 }
 
@@ -559,7 +577,7 @@ int32_t rtgs_workspace_size(int32_t n, int32_t width, int32_t height, int64_t pa
   Counts g;
   r = geometry(&n, &width, &height, 1, g, &j);
   if (r) return r;
-  *bytes = make_layout(g, pair_capacity, (flags & RTGS_FWD_SAVE_FRAGMENTS) != 0).total;
+  *bytes = layout_for(g, pair_capacity, flags).total;
   return RTGS_OK;
 }
 
@@ -632,9 +650,21 @@ int32_t render_bwd_batched(rtgs_handle_t h, const rtgs_session* ss, int32_t ns, 
   }
   bool alpha_grad = false;            // some session passes dL/dA
   for (int i = 0; i < ns; ++i) alpha_grad = alpha_grad || ss[i].dL_dalpha != nullptr;
-  if (e == hipSuccess)
-    e = launch_raster_bwd(B, w, (flags & RTGS_GRAD_MAP) ? 0 : 1, alpha_grad, frags, bal, st,
-                          tm);
+  if (e != hipSuccess) return hip_fail(e, "render_bwd launch");
+  const bool map = (flags & RTGS_GRAD_MAP) != 0;
+  // all pairs at once, or in a compact workspace in passes: each walks every
+  // list again and keeps the sums of its share of the pairs, with the same bits
+  int64_t lo = 0;
+  do {
+    if (L.sum_span < cap) {
+      w.sum_lo = (uint32_t)lo;
+      w.sum_span = (uint32_t)L.sum_span;
+      w.sum_n = (uint32_t)std::min<int64_t>(L.sum_span + kWindow, cap - lo);
+    }
+    e = launch_raster_bwd(B, w, map ? 0 : 1, alpha_grad, frags, bal, st, tm);
+    if (e == hipSuccess) e = launch_merge(B, w, map, st, tm);
+    lo += L.sum_span;
+  } while (e == hipSuccess && lo < cap);
   if (e == hipSuccess) e = launch_preprocess_bwd(B, w, flags, st, tm);
   if (e != hipSuccess) return hip_fail(e, "render_bwd launch");
   h->last_stream = st;
@@ -968,7 +998,7 @@ int32_t rtgs_tile_rects(int32_t n, int32_t width, int32_t height, int32_t sample
   Counts g;
   r = geometry(&n, &width, &height, 1, g, &sample_log2);
   if (r) return r;
-  const WsLayout L = make_layout(g, pair_capacity);
+  const WsLayout L = make_layout(g, pair_capacity, false, true);   // (what it reads lies the same)
   if (ws_bytes < L.total) return fail(RTGS_ERR_WORKSPACE, "workspace too small");
   if (n == 0) return RTGS_OK;
   const WsPtrs w = ws_ptrs(const_cast<void*>(ws), L);
@@ -1046,7 +1076,7 @@ int32_t rtgs_debug_stage(const int32_t* n, const int32_t* width, const int32_t* 
   Counts g;
   r = geometry(n, width, height, n_sessions, g, sample_log2);
   if (r) return r;
-  const WsLayout L = make_layout(g, pair_capacity);
+  const WsLayout L = make_layout(g, pair_capacity, false, true);   // (what it reads lies the same)
   if (ws_bytes < L.total) return fail(RTGS_ERR_WORKSPACE, "workspace too small");
   const WsPtrs w = ws_ptrs(const_cast<void*>(ws), L);
   Batch B{};

@@ -184,6 +184,11 @@ void k_merge(Batch B, WsPtrs W) {
   for (int w = blockIdx.x; w < n_win; w += gridDim.x) {
     const uint4 d = W.window[w];                      // pairs [x, y), list entries [z, w]
     const uint32_t p0 = d.x, p1 = d.y;
+    if (p0 < W.sum_lo) {                              // of the pass before; its last pairs
+      for (uint32_t p = W.sum_lo + tid; p < p1; p += 256) live[p] = 0u;   // are set again in this one
+      continue;
+    }
+    if (p0 - W.sum_lo >= W.sum_span) continue;        // of a later pass
     const uint32_t a = p0 + tid, b = a + 256;
     const uint32_t fa = a < p1 ? live[a] : 0u, fb = b < p1 ? live[b] : 0u;
     if (tid == 0) s_nbig = 0;
@@ -212,7 +217,7 @@ void k_merge(Batch B, WsPtrs W) {
     __syncthreads();
     if (fa) live[a] = 0u;
     if (fb) live[b] = 0u;
-    const float2* const src = reinterpret_cast<const float2*>(W.partial + (int64_t)p0 * 4 * NV);
+    const float2* const src = reinterpret_cast<const float2*>(W.partial + (int64_t)(p0 - W.sum_lo) * 4 * NV);
     for (uint32_t e0 = d.z; e0 <= d.w; e0 += 256 / 8) {
       const uint32_t e = e0 + tid / 8;
       uint2 g = make_uint2(0, 0);
@@ -658,8 +663,7 @@ static void gauss_bwd(const Batch& b, const WsPtrs& w, int grad_flags, hipStream
     gauss_bwd<NV, ADAM, SCORE, false>(b, w, grad_flags, st);
 }
 
-hipError_t launch_preprocess_bwd(const Batch& b, const WsPtrs& w, int grad_flags, hipStream_t st,
-                                 StageTimer* tm) {
+hipError_t launch_merge(const Batch& b, const WsPtrs& w, bool map, hipStream_t st, StageTimer* tm) {
   if (b.n_total > 0) {
     Scope sc(tm, kStMerge, st);
     // windows: at most one per kWindow pairs of capacity and one per chunk; a
@@ -667,11 +671,16 @@ hipError_t launch_preprocess_bwd(const Batch& b, const WsPtrs& w, int grad_flags
     // holds at once
     const int64_t most = w.cap / kWindow + b.c_total;
     const int grid = (int)(most < 16384 ? most : 16384);
-    if (grad_flags & RTGS_GRAD_MAP)
+    if (map)
       k_merge<10><<<grid, 256, 0, st>>>(b, w);
     else
       k_merge<6><<<grid, 256, 0, st>>>(b, w);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_preprocess_bwd(const Batch& b, const WsPtrs& w, int grad_flags, hipStream_t st,
+                                 StageTimer* tm) {
   if (b.b_total > 0) {
     Scope sc(tm, kStPreprocessBwd, st);
     if (grad_flags & RTGS_GRAD_ADAM)

@@ -570,6 +570,7 @@ void k_raster_bwd(Batch B, WsPtrs W) {
   __shared__ __align__(16) float s_tab[kGrp * bwd_tab_words(kMaxCols)];
   __shared__ float2 s_xy[IRR ? 64 : 1];                     // sample centres
   int tile, wave;
+  if (W.sum_lo > 0 && (int64_t)W.sum_lo >= W.counters[0]) return;   // a pass past the last pair
   if (!wave_by_work(W, B.t_total, tile, wave)) return;
   const int lane = threadIdx.x;
   const int sidx = BAL ? (int)W.lane_perm[(int64_t)tile * kBlock + wave * 64 + lane]
@@ -638,7 +639,8 @@ void k_raster_bwd(Batch B, WsPtrs W) {
   // what the lane stores of a group's sums, and where in a pair's slots: lane
   // (h, p, bit 3, entry) sum 3 h + p, with bit 3 sum 3 h + 2 (p = 0) or the flag
   // (p = 1); lane (h, p, bit 3, bit 2, value) the w sum of entry 4 h + 2 bit 3 + p
-  const uint32_t cap = (uint32_t)W.cap;          // below 2^31
+  const uint32_t room = W.sum_n;                 // pairs whose sums are kept, below 2^31
+  uint8_t* const live = W.live + (int64_t)W.sum_lo * 4 + wave;
   const int lh = lane >> 5, lp = (lane >> 4) & 1, sum = 3 * lh + (lane & 8 ? 2 : lp);
   const int we = 4 * lh + (lane & 8 ? 2 : 0) + lp;
   const bool sum_lane = !((lane & 8) && lp);
@@ -720,10 +722,11 @@ void k_raster_bwd(Batch B, WsPtrs W) {
       if (lane < 4 * kGrp) {
         const int part = lane & 3;
         s_rec[lane] = COLS == 0 && part == 1 ? conic_log2(rec) : rec;
-        // the pair's slot: Gaussian-major, then row-major in its tile rectangle
+        // the pair's slot: Gaussian-major, then row-major in its tile rectangle,
+        // from the first pair whose sums are kept (those before it come out above 2^31)
         if (part == 3)
           *reinterpret_cast<int2*>(s_tab + (lane >> 2) * kTab + 3 * COLS + 2) =
-              make_int2(pos_next, (int)(goff - __float_as_uint(rec.x)) +
+              make_int2(pos_next, (int)(goff - W.sum_lo - __float_as_uint(rec.x)) +
                                       lty * __float_as_int(rec.y) + ltx);
       }
       if (queued > n) fetch(head + kGrp, min(kGrp, queued - n));
@@ -904,15 +907,15 @@ void k_raster_bwd(Batch B, WsPtrs W) {
         {
           // lane (h, p, bit 3, entry ge): sum 3 h + p; with bit 3: 3 h + 2, and the flag
           const uint32_t pair = __float_as_uint(s_tab[ge * kTab + 3 * COLS + 3]);
-          const bool has = ((some >> ge) & 1u) && pair < cap;
+          const bool has = ((some >> ge) & 1u) && pair < room;
           const float z = lane & 8 ? x[1] : x[0];
           if (has && sum_lane) sum_dst[(int64_t)pair * (4 * NV)] = z;
-          if (has && flag_lane) W.live[(int64_t)pair * 4 + wave] = 1;
+          if (has && flag_lane) live[(int64_t)pair * 4] = 1;
         }
         if (NV == 10) {
           // lane (h, p, bit 3, bit 2, value) of the w sums
           const uint32_t pair = __float_as_uint(s_tab[we * kTab + 3 * COLS + 3]);
-          if (((some >> we) & 1u) && pair < cap && w_lane) w_dst[(int64_t)pair * (4 * NV)] = y;
+          if (((some >> we) & 1u) && pair < room && w_lane) w_dst[(int64_t)pair * (4 * NV)] = y;
         }
         wave_lds_order();
       }

@@ -121,7 +121,8 @@ struct WsLayout {
   uint64_t keys_tm;     // uint64[cap]: the long lists gathered tile-major for their sort; likewise
   uint64_t ids;         // uint32[cap]
   uint64_t hits;        // uint64[cap / 64 + T][4]: masks of the list entries each quadrant can reach
-  uint64_t partial;     // float[cap][4][10]: sums of each (tile, Gaussian) pair's quadrants
+  uint64_t partial;     // float[pairs of a pass][4][10]: sums of each (tile, Gaussian) pair's
+                        // quadrants
   uint64_t live;        // uint8[cap][4]: 1 where partial holds sums (zero between backwards)
   uint64_t state_t;     // float[pixels]: recomputed final T
   uint64_t state_last;  // int32[pixels]: recomputed last position
@@ -137,6 +138,7 @@ struct WsLayout {
   int64_t t_total;
   int64_t b_total;
   int64_t cap;
+  int64_t sum_span;     // pairs of a pass of the backward (cap: all in one)
 };
 
 struct Counts {
@@ -144,7 +146,7 @@ struct Counts {
   int64_t t_max = 0;
 };
 
-WsLayout make_layout(const Counts& c, int64_t cap, bool frags = false);
+WsLayout make_layout(const Counts& c, int64_t cap, bool frags = false, bool compact = false);
 
 // What the raster kernels read of one Gaussian, packed into one 64-byte
 // line so that staging a list entry touches a single cache line.
@@ -194,6 +196,10 @@ struct WsPtrs {
   uint32_t* fcount;
   float2* fdata;
   int64_t cap;
+  // what a raster backward and its merge work on: the sums of pairs [lo, lo + n) have
+  // room in partial, the windows that begin in [lo, lo + span) are merged (all
+  // pairs, or one pass of a compact workspace)
+  uint32_t sum_lo, sum_n, sum_span;
 };
 
 WsPtrs ws_ptrs(void* ws, const WsLayout& L);
@@ -247,6 +253,7 @@ hipError_t launch_raster_fwd(const Batch& b, const WsPtrs& w, bool stats, bool f
                              hipStream_t st, StageTimer* tm);
 hipError_t launch_raster_bwd(const Batch& b, const WsPtrs& w, int pose_only, bool alpha_grad,
                              bool frags, bool bal, hipStream_t st, StageTimer* tm);
+hipError_t launch_merge(const Batch& b, const WsPtrs& w, bool map, hipStream_t st, StageTimer* tm);
 hipError_t launch_preprocess_bwd(const Batch& b, const WsPtrs& w, int grad_flags, hipStream_t st,
                                  StageTimer* tm);
 hipError_t launch_prune(const float* g_means, const float* g_cov3d, const uint8_t* visible,

@@ -14,9 +14,11 @@ from __future__ import annotations
 
 import ctypes
 import math
+import collections
 import dataclasses
 import os
 import threading
+import weakref
 
 import torch
 
@@ -33,6 +35,7 @@ RTGS_FWD_STATS = 2
 RTGS_FWD_REUSE_LISTS = 4
 RTGS_FWD_SAVE_FRAGMENTS = 16
 RTGS_FWD_BALANCE_LANES = 32
+RTGS_FWD_COMPACT_SUMS = 64
 RTGS_PROFILE_STAGES = 16
 STAGES = ("init", "preprocess", "scan", "emit", "sort", "raster_fwd", "adam", "raster_bwd",
           "preprocess_bwd", "pose_reduce", "bin_count", "merge")
@@ -613,6 +616,40 @@ def rtgs_selftest_wave_sum(inp, out, stream=None):
 
 
 # --------------------------------------------------------------------------- managed renderer
+class _Room:
+    """Workspaces of full size while those alive stay within `limit` bytes,
+    compact ones beyond it and where the full size cannot be allocated."""
+
+    def __init__(self, limit):
+        self.limit = limit
+        self._used = 0
+        self._alive = set()                  # weak references to the full ones
+        self._gone = collections.deque()     # bytes of those freed since the last call
+        self._lock = threading.Lock()
+
+    def workspace(self, size, device):
+        """size(flag) is the bytes with that workspace flag (0: full)."""
+        need = size(0)
+        with self._lock:
+            while self._gone:
+                self._used -= self._gone.popleft()
+            full = self._used + need <= self.limit
+            if full:
+                self._used += need
+        if full:
+            try:
+                ws = torch.empty(need, dtype=torch.uint8, device=device)
+            except torch.cuda.OutOfMemoryError:
+                self._gone.append(need)
+            else:
+                def freed(ref):
+                    self._alive.discard(ref)
+                    self._gone.append(need)
+                self._alive.add(weakref.ref(ws, freed))
+                return ws
+        return torch.empty(size(RTGS_FWD_COMPACT_SUMS), dtype=torch.uint8, device=device)
+
+
 def _tiles(w, h):
     return ((w + 15) // 16) * ((h + 15) // 16)
 
@@ -624,7 +661,13 @@ class Renderer:
     pair capacity and re-renders with a larger buffer if it overflowed (one
     host sync per forward).  check="deferred": no per-call sync; call
     ``verify()`` at a point of your choosing (it raises if any forward since
-    the last verify overflowed, after growing the capacity)."""
+    the last verify overflowed, after growing the capacity).
+
+    Every state that awaits its backward holds a workspace.  While those alive
+    take at most an eighth of the card they have room for the gradient sums of
+    all pairs (169 bytes a pair); further ones are compact
+    (RTGS_FWD_COMPACT_SUMS, 49 bytes a pair: the same results, but the raster
+    backward runs in passes)."""
 
     def __init__(self, device=0, check="every", pairs_per_gaussian=12.0, min_capacity=1 << 16):
         self.handle = Handle(device)
@@ -634,12 +677,15 @@ class Renderer:
         self.min_cap = min_capacity
         self.cap = 0
         self.ws = None
+        self._room = _Room(torch.cuda.get_device_properties(device).total_memory // 8)
 
     def _ensure(self, ns, ws_, hs, cap):
         cap = max(int(cap), self.min_cap)
         if cap > self.cap:
             self.cap = cap
         need = rtgs_workspace_size_batched(ns, ws_, hs, self.cap)
+        if need > self._room.limit:
+            need = rtgs_workspace_size_batched(ns, ws_, hs, self.cap, RTGS_FWD_COMPACT_SUMS)
         if self.ws is None or self.ws.numel() < need:
             self.ws = torch.empty(need + 256, dtype=torch.uint8, device=self.device)
         return self.ws, self.cap
@@ -727,8 +773,8 @@ class Renderer:
         est = int(self.ppg * n) + 4 * _tiles(w, h)
         cap = max(self.cap, est, self.min_cap)
         while True:
-            need = rtgs_workspace_size(n, w, h, cap, fflag)
-            ws = torch.empty(need, dtype=torch.uint8, device=dev)
+            ws = self._room.workspace(
+                lambda compact: rtgs_workspace_size(n, w, h, cap, fflag | compact), dev)
             out = FwdState(ws=ws, cap=cap, cam=cam, n=n, sample_log2=sample_log2,
                            frags=save_fragments,
                            color=torch.empty(3, h, w, device=dev),

@@ -183,6 +183,7 @@ class Engine:
         self.specs = list(specs)
         self.ex = executor
         self.cfg = cfg
+        executor.ws_budget = cfg.ws_budget
         self.clock = clock or getattr(executor, "clock", time.perf_counter)
         self.open = [False] * len(self.specs)
         self.pending = collections.deque()     # frames waiting (arrived)
@@ -562,6 +563,8 @@ class GpuExecutor:
     iterations update the single version in place (a session's frames then
     run one after another)."""
 
+    ws_budget = ServeConfig.ws_budget     # bytes of a step's workspace (the engine's)
+
     def __init__(self, device=0, lr_pose=(1e-3, 3e-3), track_noise_seed=0, n_targets=4,
                  capacity_factor=2.0, prune=False, prune_ratio=0.1, prune_cap=0.5,
                  prune_lam=0.8, record_poses=False, fused=True):
@@ -608,7 +611,18 @@ class GpuExecutor:
         return int(self.capacity_factor * (12 * spec.n + 4 * _tiles(spec.width, spec.height)))
 
     def step_bytes(self, spec, frame):
-        return self.rtgs.rtgs_workspace_size(spec.n, spec.width, spec.height, self._cap(spec))
+        # the least a step can run with (see _workspace_bytes)
+        return self.rtgs.rtgs_workspace_size(spec.n, spec.width, spec.height, self._cap(spec),
+                                             self.rtgs.RTGS_FWD_COMPACT_SUMS)
+
+    def _workspace_bytes(self, ns, widths, heights, cap):
+        """A step's workspace: full within the budget, compact beyond it (the
+        same results, a slower raster backward)."""
+        size = self.rtgs.rtgs_workspace_size_batched
+        full = size(ns, widths, heights, cap)
+        if full <= self.ws_budget:
+            return full
+        return size(ns, widths, heights, cap, self.rtgs.RTGS_FWD_COMPACT_SUMS)
 
     def _eye(self):
         return self.torch.eye(3, 4, dtype=self.torch.float32, device=self.dev).contiguous()
@@ -869,7 +883,7 @@ class GpuExecutor:
                            x.params, phase)
             cap += self._cap(self.sessions[x.session]["spec"])
         arr = (rtgs.CSession * k)(*[x.cs for x in frames])
-        ws = torch.empty(rtgs.rtgs_workspace_size_batched(
+        ws = torch.empty(self._workspace_bytes(
             [x.n for x in frames], [x.out["depth"].shape[1] for x in frames],
             [x.out["depth"].shape[0] for x in frames], cap), dtype=torch.uint8, device=self.dev)
         # the forward also writes each frame's loss gradient (its session's l1)
