@@ -384,7 +384,8 @@ __global__ __launch_bounds__(64) void k_raster_fwd(Batch B, WsPtrs W) {
   int stop = end;               // list position where the pixel stopped
   int nblend = 0;
   uint32_t fcur = 0;            // saved fragments of this wave so far
-  const int64_t fbase = FRAG ? frag_base(start, end, wave) : 0;
+  float2* fout = FRAG ? W.fdata + frag_base(start, end, wave) : nullptr;
+  unsigned long long fmask = 0; // lanes 0 to 3: who blended that entry of a group of four
   const float* const col_words = reinterpret_cast<const float*>(s_col) + (lane & 15);
   int walked = 0, done = 0;     // entries walked up to the lane's last blended one; in all
   // COLS: the columns and rows that the samples lie in (0: any number)
@@ -482,12 +483,12 @@ __global__ __launch_bounds__(64) void k_raster_fwd(Batch B, WsPtrs W) {
           T = blend ? tn : (seen ? -fabsf(T) : T);
           lastk = blend ? k : lastk;
           if (STATS) nblend += blend ? 1 : 0;
-          if (FRAG && k < n) {
+          if (FRAG) {                   // (entries past the last: no lane)
             const unsigned long long bm = __builtin_amdgcn_ballot_w64(blend);
-            if (lane == 0) W.fmask[(int64_t)s_pos[head + k] * 4 + wave] = bm;
+            if (lane == (k & 3)) fmask = bm;
             if (blend)
-              W.fdata[fbase + fcur + lane_rank(bm)] =
-                  make_float2(raw > kAlphaMax ? -f.alpha : f.alpha, f.om);
+              fout[lane_rank(bm)] = make_float2(raw > kAlphaMax ? -f.alpha : f.alpha, f.om);
+            fout += __popcll(bm);
             fcur += (uint32_t)__popcll(bm);
           }
           return w;
@@ -502,6 +503,9 @@ __global__ __launch_bounds__(64) void k_raster_fwd(Batch B, WsPtrs W) {
           C = __builtin_amdgcn_mfma_f32_4x4x1f32(a, weight(k + 1), C, 2, 1, 0);
           C = __builtin_amdgcn_mfma_f32_4x4x1f32(a, weight(k + 2), C, 2, 2, 0);
           C = __builtin_amdgcn_mfma_f32_4x4x1f32(a, weight(k + 3), C, 2, 3, 0);
+          // the group's masks, a lane an entry
+          if (FRAG && lane < 4 && k + lane < n)
+            W.fmask[(int64_t)s_pos[head + k + lane] * 4 + wave] = fmask;
         }
         if (lastk >= 0) {
           last = s_pos[head + lastk];
@@ -890,8 +894,9 @@ void k_raster_bwd(Batch B, WsPtrs W) {
           const float Tj = Tc * rom;                     // T before this fragment (rcp(1) = 1)
           const float w = al * Tj;
           // (0 where the lane did not blend it: a colour or depth that is not finite
-          // reaches the pixels that blended it alone)
-          const float cg = contrib ? cg4[i] : 0.f;
+          // reaches the pixels that blended it alone; saved fragments queue no
+          // entry that no lane blended)
+          const float cg = FRAG || contrib ? cg4[i] : 0.f;
           // dL/dalpha_j = T_j (c_j - S_j) . g + T_final gA / (1 - alpha_j)
           const float dla = GA ? __builtin_fmaf(Tj, cg - SG, gAT * rom) : Tj * (cg - SG);
           SG = __builtin_fmaf(al, cg, om * SG);
@@ -1026,8 +1031,10 @@ static void raster_fwd_variant(const Batch& b, const WsPtrs& w, bool frags, bool
   if (frags) {
     if (bal)
       k_raster_fwd<STATS, true, true, false, true><<<grid, 64, 0, st>>>(b, w);
-    else
+    else if (irr)
       k_raster_fwd<STATS, true, false, false, true><<<grid, 64, 0, st>>>(b, w);
+    else
+      k_raster_fwd<STATS, true, false, false, false><<<grid, 64, 0, st>>>(b, w);
   } else if (bal) {
     k_raster_fwd<STATS, false, true, false, true><<<grid, 64, 0, st>>>(b, w);
   } else if (irr) {
