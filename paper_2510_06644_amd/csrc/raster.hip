@@ -1084,15 +1084,25 @@ hipError_t launch_raster_fwd(const Batch& b, const WsPtrs& w0, bool stats, bool 
 // are on the chip at once then (up to 1024 tiles; a fifth would not be used),
 // otherwise five, or six for all gradients, at the price of a few spilled
 // registers.  Measured with four and five: 836 tiles (1200x680 at 1 in 4, 500k)
-// 120 and 128 us; six frames with downsampled ones among them (10.5k tiles) 297
-// and 284 us.  All gradients with four, five and six: 1200x680 / 300k 145, 138 and
-// 133 us, / 500k 128 and 123, three mapped frames 213 and 202 (the latter two five
-// and six); pose only at 640x480 / 100k with five and six 62 and 63.  All
-// gradients of downsampled frames need 124 registers and stay at four.
+// 120 and 128 us, 900 tiles of three frames (640x480 at 1 in 4, 100k) 125 and 128; six
+// frames with downsampled ones among them (10.5k tiles) 297 and 284 us.  All
+// gradients with four, five and six: 1200x680 / 300k 145, 138 and 133 us, / 500k 128
+// and 123, three mapped frames 213 and 202 (the latter two five and six).  All
+// gradients of downsampled frames need 124 registers and stay at four; the pose's on
+// the pixel grid need 90 at most, five waves under any rule.
+template <int NV, bool GA, bool IRR, int EU>
+static void raster_bwd_waves(const Batch& b, const WsPtrs& w, int grid, hipStream_t st) {
+  if (b.n_sessions == 1)
+    k_raster_bwd<NV, GA, false, false, true, IRR, EU><<<grid, 64, 0, st>>>(b, w);
+  else
+    k_raster_bwd<NV, GA, false, false, false, IRR, EU><<<grid, 64, 0, st>>>(b, w);
+}
+
 template <int NV, bool GA>
 static void raster_bwd_variant(const Batch& b, const WsPtrs& w, bool frags, bool bal, int grid,
                                hipStream_t st) {
-  const bool one = b.n_sessions == 1, irr = b.any_sub != 0, few = b.t_total <= kFewTiles;
+  const bool irr = b.any_sub != 0, few = b.t_total <= kFewTiles;
+  constexpr bool kMap = NV == 10;
   if (frags) {
     if (bal)
       k_raster_bwd<NV, GA, true, true, false, true, 4><<<grid, 64, 0, st>>>(b, w);
@@ -1101,20 +1111,15 @@ static void raster_bwd_variant(const Batch& b, const WsPtrs& w, bool frags, bool
   } else if (bal) {
     k_raster_bwd<NV, GA, false, true, false, true, 4><<<grid, 64, 0, st>>>(b, w);
   } else if (irr) {
-    constexpr int EU = NV == 10 ? 4 : 5;
-    if (one && few)
-      k_raster_bwd<NV, GA, false, false, true, true, 4><<<grid, 64, 0, st>>>(b, w);
-    else if (one)
-      k_raster_bwd<NV, GA, false, false, true, true, EU><<<grid, 64, 0, st>>>(b, w);
+    if (few)
+      raster_bwd_waves<NV, GA, true, 4>(b, w, grid, st);
     else
-      k_raster_bwd<NV, GA, false, false, false, true, EU><<<grid, 64, 0, st>>>(b, w);
+      raster_bwd_waves<NV, GA, true, kMap ? 4 : 5>(b, w, grid, st);
   } else {
-    if (one && few)
-      k_raster_bwd<NV, GA, false, false, true, false, 4><<<grid, 64, 0, st>>>(b, w);
-    else if (one)
-      k_raster_bwd<NV, GA, false, false, true, false, NV == 10 ? 6 : 5><<<grid, 64, 0, st>>>(b, w);
+    if (few)
+      raster_bwd_waves<NV, GA, false, kMap ? 4 : 5>(b, w, grid, st);
     else
-      k_raster_bwd<NV, GA, false, false, false, false, NV == 10 ? 6 : 5><<<grid, 64, 0, st>>>(b, w);
+      raster_bwd_waves<NV, GA, false, kMap ? 6 : 5>(b, w, grid, st);
   }
 }
 
