@@ -689,8 +689,8 @@ hipError_t launch_preprocess_bwd(const Batch& b, const WsPtrs& w, int grad_flags
       gauss_bwd<10, false, false>(b, w, grad_flags, st);
     else if (grad_flags & RTGS_GRAD_SCORE)
       gauss_bwd<6, false, true>(b, w, grad_flags, st);
-    else
-      gauss_bwd<6, false, false>(b, w, grad_flags, st);
+    else                                // the pose alone
+      gauss_bwd<6, false, false, true>(b, w, grad_flags, st);
   }
   if ((grad_flags & RTGS_GRAD_POSE) && b.n_sessions > 0) {
     Scope sc(tm, kStPoseReduce, st);
