@@ -139,7 +139,6 @@ WsLayout make_layout(const Counts& c, int64_t cap, bool frags, bool compact) {
   L.table = take(sizeof(SessionDev) * RTGS_MAX_SESSIONS);
   L.counters = take(64);
   L.rec = take(64 * n);
-  L.ext = take(8 * n);
   L.rect = take(16 * n);
   L.cnt = take(4 * n);
   L.goff = take(4 * n);
@@ -193,7 +192,6 @@ WsPtrs ws_ptrs(void* ws, const WsLayout& L) {
   w.table = reinterpret_cast<SessionDev*>(base + L.table);
   w.counters = reinterpret_cast<long long*>(base + L.counters);
   w.rec = reinterpret_cast<GaussRec*>(base + L.rec);
-  w.ext = reinterpret_cast<float2*>(base + L.ext);
   w.rect = reinterpret_cast<int4*>(base + L.rect);
   w.cnt = reinterpret_cast<uint32_t*>(base + L.cnt);
   w.goff = reinterpret_cast<uint32_t*>(base + L.goff);

@@ -145,8 +145,9 @@ __global__ __launch_bounds__(kGaussPerBlock) void k_preprocess(Batch B, WsPtrs W
     r.conic = make_float4((float)(P.syy * inv), (float)(-P.sxy * inv), (float)(P.sxx * inv),
                           (float)o);
     r.col = make_float4(S.colors[3 * li + 0], S.colors[3 * li + 1], S.colors[3 * li + 2], zf);
+    r.ext.y = ex;
     r.ext.z = (float)t;
-    W.ext[gid] = make_float2(ex, ey);
+    r.ext.w = ey;
     // padded pixel range in float32, fixed operation order (see the replay)
     const float lox = floorf((uh - ex) - 1.5f), hix = ceilf((uh + ex) + 0.5f);
     const float loy = floorf((vh - ey) - 1.5f), hiy = ceilf((vh + ey) + 0.5f);
@@ -163,14 +164,13 @@ __global__ __launch_bounds__(kGaussPerBlock) void k_preprocess(Batch B, WsPtrs W
     // a negative alpha-ellipse bound fails every quadrant test: a culled or
     // masked Gaussian left in a reused list costs the rasterizer nothing
     r.ext.z = -1.f;
-    W.ext[gid] = make_float2(0.f, 0.f);
+    r.ext.y = r.ext.w = 0.f;
   }
   if (REUSE) rect = W.rect[gid];
   // the lists' rectangle, from which the raster backward takes the pair's slot
   const int rw = rect.z - rect.x + 1;
-  r.ext.x = __int_as_float(rect.y * rw + rect.x);
-  r.ext.y = __int_as_float(rw);
-  r.ext.w = 0.f;
+  static_assert(kMaxTilesPerSession <= 1 << 15, "tile and width in half a word each");
+  r.ext.x = __int_as_float(((rect.y * rw + rect.x) << 16) | rw);
   W.rec[gid] = r;
   if (REUSE) {
     if (S.visible) S.visible[li] = rect.z >= rect.x ? 1 : 0;
@@ -639,10 +639,10 @@ __global__ void k_debug_stage(Batch B, WsPtrs W, float* stage, int* rect, int* r
     if (stage) {
       const GaussRec R = W.rec[i];
       const float4 r0 = R.pos, r1 = R.conic, r2 = R.col;
-      const float2 e = W.ext[i];
+      const float4 e = R.ext;
       float* o = stage + 12 * (int64_t)i;
       o[0] = r0.x; o[1] = r0.y; o[2] = r1.x; o[3] = r1.y; o[4] = r1.z; o[5] = r1.w;
-      o[6] = r2.w; o[7] = e.x; o[8] = e.y; o[9] = r2.x; o[10] = r2.y; o[11] = r2.z;
+      o[6] = r2.w; o[7] = e.y; o[8] = e.w; o[9] = r2.x; o[10] = r2.y; o[11] = r2.z;
     }
     if (rect) {
       const int4 r = W.rect[i];

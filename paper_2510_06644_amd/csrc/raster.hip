@@ -816,8 +816,8 @@ void k_raster_bwd(Batch B, WsPtrs W) {
         // from the first pair whose sums are kept (those before it come out above 2^31)
         if (part == 3)
           *reinterpret_cast<int2*>(s_tab + (lane >> 2) * kTab + 3 * COLS + 2) =
-              make_int2(pos_next, (int)(goff - W.sum_lo - __float_as_uint(rec.x)) +
-                                      lty * __float_as_int(rec.y) + ltx);
+              make_int2(pos_next, (int)(goff - W.sum_lo - (__float_as_uint(rec.x) >> 16)) +
+                                      lty * (int)(__float_as_uint(rec.x) & 0xffffu) + ltx);
       }
       if (queued > n) fetch(head + kGrp, min(kGrp, queued - n));
       wave_lds_order();

@@ -97,7 +97,6 @@ struct WsLayout {
   uint64_t table;       // SessionDev[RTGS_MAX_SESSIONS]
   uint64_t counters;    // int64[8]: 0 pairs of this call, 2 entries of big_tiles
   uint64_t rec;         // GaussRec[N]: the 64-byte raster record of each Gaussian
-  uint64_t ext;         // float2[N]: half-widths of the alpha = 1/255 box (debug output)
   uint64_t rect;        // int4[N]: tile rectangle
   uint64_t cnt;         // uint32[N]: tiles touched
   uint64_t goff;        // uint32[N]: first slot of the Gaussian's pairs, Gaussian-major
@@ -154,7 +153,8 @@ struct alignas(64) GaussRec {
   float4 pos;     // u_hi, v_hi, u_lo, v_lo (centre as a float32 pair)
   float4 conic;   // a, b, c (inverse 2D covariance), opacity
   float4 col;     // r, g, b, depth z
-  float4 ext;     // tile rectangle as bits: y0 * width + x0, width (int); t = 2 ln(255 o); 0
+  float4 ext;     // tile rectangle as bits: (y0 * width + x0) << 16 | width; half-widths of the
+                  // alpha = 1/255 box in .y and .w (debug output); t = 2 ln(255 o) in .z
 };
 static_assert(sizeof(GaussRec) == 64, "one line per record");
 
@@ -163,7 +163,6 @@ struct WsPtrs {
   SessionDev* table;
   long long* counters;
   GaussRec* rec;
-  float2* ext;
   int4* rect;
   uint32_t* cnt;
   uint32_t* goff;

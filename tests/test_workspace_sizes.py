@@ -60,3 +60,10 @@ def test_a_step_of_sixteen_large_frames(spec, full):
     got = ex._workspace_bytes(*args)
     assert got <= cfg.ws_budget
     assert got == rtgs.rtgs_workspace_size_batched(*args, 0 if full else COMPACT)
+
+
+def test_bytes_of_a_gaussian():
+    # record 64, rectangle 16, count, first slot and key 12, merged gradient 40, list entry
+    # 8, and two bytes for what a chunk of 1024 adds
+    a, b = (rtgs.rtgs_workspace_size(n, 16, 16, 0) for n in (1 << 20, 1 << 21))
+    assert (b - a) / (1 << 20) <= 64 + 16 + 12 + 40 + 8 + 2
