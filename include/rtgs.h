@@ -564,8 +564,8 @@ int32_t rtgs_debug_stage(const int32_t* n, const int32_t* width,
 int32_t rtgs_profile_enable(rtgs_handle_t h, int32_t stage_mask);
 int32_t rtgs_profile_read(rtgs_handle_t h, double* total_ms, int64_t* launches);
 
-/* Test hook for the wavefront reduce-scatter of the backward merge (ten
- * values per lane, as in the full-gradient backward): for each wave w of
+/* Test hook for the wavefront reduce-scatter of the raster backward (six
+ * values per lane; here of values 0 to 5, then 4 to 9): for each wave w of
  * n_waves and value i < 10, out[10 w + i] = sum over lanes l < 64 of
  * in[(10 w + i) * 64 + l].  in and out are device arrays. */
 int32_t rtgs_selftest_wave_sum(const float* in, float* out, int32_t n_waves,

@@ -659,24 +659,21 @@ __global__ void k_debug_stage(Batch B, WsPtrs W, float* stage, int* rect, int* r
   }
 }
 
+// The reduce-scatter of the raster backward on values 0 to 5 and 4 to 9, each
+// total stored by the lane that stores it there (of the eight l, added up here).
 __global__ void k_wave_sum_test(const float* in, float* out, int n_waves) {
   constexpr int NV = kWaveSumValues;
   const int w = blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
   if (w >= n_waves) return;     // whole waves exit together
-  const int lane = threadIdx.x & 63;
-  float v[NV], x[3];
+  const int lane = threadIdx.x & 63, value = rows8_value(lane);
+  for (int first = 0; first <= NV - 6; first += NV - 6) {
+    float v[6], x[2];
 #pragma unroll
-  for (int i = 0; i < NV; ++i) v[i] = in[((int64_t)w * NV + i) * 64 + lane];
-  rows8_reduce_scatter<NV>(v, x);
-#pragma unroll
-  for (int j = 0; j < 3; ++j)
-    for (int off = 4; off >= 1; off >>= 1) x[j] += __shfl_xor(x[j], off);
-  if ((lane & 15) == 0) {
-    const int odd = (lane >> 4) & 1;
-    float* o = out + (int64_t)w * NV + (lane >> 5) * (NV / 2);
-#pragma unroll
-    for (int j = 0; j < NV / 4; ++j) o[odd + 2 * j] = x[j];
-    if (!odd) o[NV / 2 - 1] = x[NV / 4];
+    for (int i = 0; i < 6; ++i) v[i] = in[((int64_t)w * NV + first + i) * 64 + lane];
+    rows8_reduce_scatter(v, x);
+    float t = lane & 8 ? x[1] : x[0];
+    for (int off = 4; off >= 1; off >>= 1) t += __shfl_xor(t, off);
+    if ((lane & 7) == 0 && value >= 0) out[(int64_t)w * NV + first + value] = t;
   }
 }
 

@@ -731,9 +731,9 @@ void k_raster_bwd(Batch B, WsPtrs W) {
   // (p = 1); lane (h, p, bit 3, bit 2, value) the w sum of entry 4 h + 2 bit 3 + p
   const uint32_t room = W.sum_n;                 // pairs whose sums are kept, below 2^31
   uint8_t* const live = W.live + (int64_t)W.sum_lo * 4 + wave;
-  const int lh = lane >> 5, lp = (lane >> 4) & 1, sum = 3 * lh + (lane & 8 ? 2 : lp);
+  const int lh = lane >> 5, lp = (lane >> 4) & 1, sum = rows8_value(lane);
   const int we = 4 * lh + (lane & 8 ? 2 : 0) + lp;
-  const bool sum_lane = !((lane & 8) && lp);
+  const bool sum_lane = sum >= 0;
   const bool flag_lane = (lane & 8) && lp && lh == 0;
   const bool w_lane = NV == 10 && !(lane & 4);
   float* const sum_dst = W.partial + wave * NV + sum;
@@ -983,8 +983,8 @@ void k_raster_bwd(Batch B, WsPtrs W) {
 #pragma unroll
           for (int i = 1; i < 8; ++i) v[5] = __builtin_fmaf(ww[i], G[i % (NV == 10 ? 4 : 8)], v[5]);
         }
-        float x[3];
-        rows8_reduce_scatter<6>(v, x);
+        float x[2];
+        rows8_reduce_scatter(v, x);
         // the w sums over the 16 groups of pixels (NV = 10): lane bits 5 to 2
         float r[4];
 #pragma unroll

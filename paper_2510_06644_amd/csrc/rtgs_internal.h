@@ -456,30 +456,27 @@ __device__ __forceinline__ float swap16_add(float a, float b) {
   return __uint_as_float(x) + __uint_as_float(y);
 }
 
-// Reduce-scatter of NV (even, NV / 2 odd, <= 10) per-lane values over the 8
-// lanes l, l + 8, ..., l + 56 of each l < 8: two lane-swap steps each halve
-// the number of values a lane carries while adding pairs of lanes, the last
-// value after the first step is summed over both rows, and a rotation by 8
-// inside each 16-lane row adds the last pair.  Lane 32 h + 16 p + 8 x + l (any
-// x) ends with the totals of values h NV / 2 + p + 2 j in x[j] for
-// j < NV / 4, and of value h NV / 2 + NV / 2 - 1 in x[NV / 4] (any p).
-template <int NV>
-__device__ __forceinline__ void rows8_reduce_scatter(const float (&v)[NV], float (&x)[3]) {
-  constexpr int H = NV / 2;
-  static_assert(NV % 2 == 0 && H % 2 == 1 && H <= 5, "two halves of an odd count");
-  float w[H];
+// Reduce-scatter of six per-lane values over the 8 lanes l, l + 8, ..., l + 56 of
+// each l < 8: two lane-swap steps each halve the number of values a lane carries
+// while adding pairs of lanes, the last value after the first step is summed over
+// both rows, and a rotation by 8 inside each 16-lane row adds the last pair.  Lane
+// 32 h + 16 p + 8 x + l (any x) ends with the totals of value 3 h + p in x[0] and of
+// value 3 h + 2 (any p) in x[1].
+__device__ __forceinline__ void rows8_reduce_scatter(const float (&v)[6], float (&x)[2]) {
+  float w[3];
 #pragma unroll
-  for (int i = 0; i < H; ++i) w[i] = swap32_add(v[i], v[i + H]);
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    if (2 * j < H) {
-      const float s = 2 * j + 1 < H ? swap16_add(w[2 * j], w[(2 * j + 1) % H])
-                                    : swap16_add(w[2 * j], w[2 * j]);
-      x[j] = s + dpp_f<kDppRowRor8, 0xf, true>(s);
-    } else {
-      x[j] = 0.f;
-    }
-  }
+  for (int i = 0; i < 3; ++i) w[i] = swap32_add(v[i], v[i + 3]);
+  x[0] = swap16_add(w[0], w[1]);
+  x[1] = swap16_add(w[2], w[2]);
+  x[0] += dpp_f<kDppRowRor8, 0xf, true>(x[0]);
+  x[1] += dpp_f<kDppRowRor8, 0xf, true>(x[1]);
+}
+
+// The value whose total a lane stores then: of x[1] with bit 3 of the lane, of
+// x[0] without; none (-1) for the lanes that hold a total a second time.
+__device__ __forceinline__ int rows8_value(int lane) {
+  const int h = lane >> 5, p = (lane >> 4) & 1;
+  return lane & 8 ? (p ? -1 : 3 * h + 2) : 3 * h + p;
 }
 
 // One Adam element update (t the step count after it):
