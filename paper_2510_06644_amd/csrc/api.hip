@@ -163,6 +163,7 @@ WsLayout make_layout(const Counts& c, int64_t cap, bool frags, bool compact) {
   L.state_t = take(4 * (uint64_t)c.px_total);
   L.state_last = take(4 * (uint64_t)c.px_total);
   L.lane_perm = take(256 * t);
+  L.small = take(4 * t);
   L.order_n = take(4 * 8 * kOrderClasses);
   L.order = take(4 * 8 * kOrderClasses * 4 * ((t + 7) / 8));
   // after what a forward leaves for its backward, so that all of that lies at the
@@ -218,6 +219,7 @@ WsPtrs ws_ptrs(void* ws, const WsLayout& L) {
   w.state_t = reinterpret_cast<float*>(base + L.state_t);
   w.state_last = reinterpret_cast<int32_t*>(base + L.state_last);
   w.lane_perm = reinterpret_cast<uint8_t*>(base + L.lane_perm);
+  w.small = reinterpret_cast<uint8_t*>(base + L.small);
   w.order_n = reinterpret_cast<uint32_t*>(base + L.order_n);
   w.order = reinterpret_cast<uint32_t*>(base + L.order);
   if (L.fdata) {

@@ -126,6 +126,7 @@ struct WsLayout {
   uint64_t state_t;     // float[pixels]: recomputed final T
   uint64_t state_last;  // int32[pixels]: recomputed last position
   uint64_t lane_perm;   // uint8[T][256]: sample of each lane (lanes assigned by previous work)
+  uint64_t small;       // uint8[4 T]: quadrants with little work, not in the order
   uint64_t order_n;     // uint32[8][kOrderClasses]: quadrants filed per XCD band and work class
   uint64_t order;       // uint32[8][kOrderClasses][4 ceil(T / 8)]: 4 tile + quadrant
   // saved fragments (workspace sized with RTGS_FWD_SAVE_FRAGMENTS, else absent)
@@ -189,6 +190,7 @@ struct WsPtrs {
   float* state_t;
   int32_t* state_last;
   uint8_t* lane_perm;
+  uint8_t* small;
   uint32_t* order_n;
   uint32_t* order;             // null: the forward files nothing
   unsigned long long* fmask;   // null without saved fragments
