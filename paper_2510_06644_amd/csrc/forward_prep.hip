@@ -610,9 +610,6 @@ __global__ __launch_bounds__(kBinThreads) void k_emit(Batch B, WsPtrs W) {
   }
   if (W.chunk_off[B.c_total] <= (uint64_t)W.cap)
     list_windows(W, blockIdx.x, S.gauss_base + c * kChunk, base, total, s_off, s_wave);
-  // no pair of this call's lists has sums yet
-  for (uint32_t k = threadIdx.x; k < total; k += kBinThreads)
-    if ((int64_t)base + k < W.cap) reinterpret_cast<uint32_t*>(W.live)[base + k] = 0u;
   const uint32_t g0 = S.gauss_base + c * kChunk;
   const bool staged = total <= kStagePairs;
   chunk_pairs(S, s_rect, c, s_off, total, [&](int i, int tile) {
