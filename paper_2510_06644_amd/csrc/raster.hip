@@ -33,7 +33,7 @@ namespace {
 // The tile and quadrant of a one-wave workgroup of the forward.  Workgroups
 // are dealt round-robin to the 8 XCDs; each XCD gets a contiguous band of
 // tiles, the four quadrants of a tile in a row, so neighbours share its L2
-// (runs of 4 or 16 tiles dealt in turn: 3 of 88 us slower).
+// (runs of 4 or 16 tiles dealt in turn: 3 of 87 us slower).
 __device__ __forceinline__ bool wave_of_block(int t_total, int& tile, int& wave) {
   const int per = (t_total + 7) >> 3;
   tile = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 5);
@@ -42,7 +42,7 @@ __device__ __forceinline__ bool wave_of_block(int t_total, int& tile, int& wave)
 }
 
 // The backward takes a band's quadrants by falling work: at 12.9k waves on
-// 5120 places the last waves to start decide when the kernel ends (taken in
+// 6144 places (six a SIMD) the last waves to start decide when the kernel ends (taken in
 // tile order it drained for 62 of 166 us at 1200x680 / 300k).  The forward
 // files each quadrant under the entries it walked up to its last blended one,
 // kOrderStep to a class.  Quadrants without work are not filed, nor those with
@@ -345,10 +345,10 @@ constexpr int tab_words(int cols) { return 3 * cols + 2; }
 //    an exact FMA per element; the A operand of four entries is one LDS read,
 //    lane l holding value l & 3 of entry (l >> 2) & 3, broadcast by blocks.
 //  * A stopped pixel's T is negative, so `T' < 1e-4` also keeps it stopped.
-// Measured at 1200x680 / 300k: 92 -> 88 us (51.8M -> 36M wave VALU
-// instructions; 71 us of issue, exp at quarter rate included, the rest the
-// last waves draining); 640x480 / 100k 55 -> 49 us, 320x240 / 20k 21.6 -> 18 us;
-// 1200x680 at 1 in 4 / 500k 109 -> 78 us by the tables of 16 columns.
+// Measured (kernel trace) at 1200x680 / 300k: 92 -> 84 us (51.8M -> 35.0M wave
+// VALU instructions; 70 us of issue, exp at quarter rate included, the rest the
+// last waves draining); 640x480 / 100k 55 -> 47 us, 320x240 / 20k 21.6 -> 17 us;
+// 1200x680 at 1 in 4 / 500k 109 -> 71 us by the tables of 16 columns.
 // Before, four waves of a tile shared batches of 256 entries, 29 VALU
 // instructions a walked entry.
 //
@@ -643,9 +643,9 @@ constexpr int bwd_tab_words(int cols) { return 3 * cols + 4; }
 // (Moments of n about the quadrant's middle, one 16x16x4 MFMA chain a group and
 // shifted to the centre in double, cost digits: narrow Gaussians cancel.)
 //
-// Measured at 1200x680 / 300k, NV = 10: 241 -> 133 us (109M -> 62M wave VALU
-// instructions, 121 us of issue; the rest the last waves draining); pose only at
-// 640x480 / 100k 109 -> 62 us, 1200x680 at 1 in 4 / 500k 135 -> 120 us.
+// Measured (kernel trace) at 1200x680 / 300k, NV = 10: 241 -> 133 us (109M -> 63M
+// wave VALU instructions, 123 us of issue; the rest the last waves draining); pose
+// only at 640x480 / 100k 109 -> 59 to 63 us, 1200x680 at 1 in 4 / 500k 135 -> 123 us.
 // Before, four waves of a tile met at two barriers per 64 entries, summed ten
 // values over the wave per entry (lane swaps and DPP, 29 instructions), and
 // every pair without a gradient was written as zeros.  One wave a quadrant with
@@ -657,7 +657,7 @@ constexpr int bwd_tab_words(int cols) { return 3 * cols + 4; }
 // and entries no lane of the wave blended are skipped without arithmetic; the
 // values are those the forward computed, so the gradients are bitwise those
 // of the re-evaluating form.
-// BAL: the forward assigned lanes by previous work (lane_schedule); the same
+// BAL: the forward assigned lanes by previous work (k_lane_schedule); the same
 // samples go to the same lanes here (the saved quadrant bits are per wave).
 // IRR: some tile's samples may not form the 8x8 pixel grid of its quadrants
 // (downsampled frames, BAL).  A uniform branch outside the loops takes the grid's
