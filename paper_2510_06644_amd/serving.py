@@ -183,7 +183,8 @@ class Engine:
         self.specs = list(specs)
         self.ex = executor
         self.cfg = cfg
-        executor.ws_budget = cfg.ws_budget
+        if hasattr(executor, "ws_budget"):
+            executor.ws_budget = cfg.ws_budget
         self.clock = clock or getattr(executor, "clock", time.perf_counter)
         self.open = [False] * len(self.specs)
         self.pending = collections.deque()     # frames waiting (arrived)
